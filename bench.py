@@ -81,10 +81,19 @@ WORKLOADS = {
 }
 PEAKS_TFLOPS = {"fp32": 157.3, "bf16": 2500.0, "fp16": 2500.0}
 PEAK_HBM_GBS = 8000.0
+
+
+def fp32_matrix_peak(J):
+    """FP32 coupling products run on the BF16 matrix cores in exact pieces:
+    three products per amplitude and coupling when the couplings are exact in
+    FP8, six otherwise."""
+    return PEAKS_TFLOPS["bf16"] / (3 if fp8_exact(J) and os.environ.get("GD_J8_COPY", "1") != "0" else 6)
+
+
 PEAK_VALU_F32 = 78.6    # FP32 vector FMA without packed math (256 CUs, 2.4 GHz)
 
 
-KERNEL_SOURCES = {"dense_step_f32": ("gd_dense.hip", "gd_epilogue.h"),
+KERNEL_SOURCES = {"dense_step_split": ("gd_split.h", "gd_epilogue.h"),
                   "dense_step_lp": ("gd_dense_lp.h", "gd_epilogue.h"),
                   "gemv_step_k": ("gd_gemv.h", "gd_epilogue.h")}
 
@@ -101,7 +110,7 @@ def fp8_exact(J):
     return bool(np.isin(Jo, vals).all())
 
 
-def kernel_traffic(config_id, kern="dense_step_f32", workload="xy1024"):
+def kernel_traffic(config_id, kern="dense_step_split", workload="xy1024"):
     """HBM bytes per launch of a coupling kernel from its committed counter
     summary (profiles/<kernel>_<workload>_counters.txt: one
     traffic_bytes_per_launch for kernel_config_id, or one
@@ -771,7 +780,7 @@ def headline(args):
         launches = st.kernel_launches - st0.kernel_launches
         avg_s = (st.kernel_ms - st0.kernel_ms) / 1e3 / max(launches, 1)
         flops_launch = 2.0 * n * n * R
-        peak = PEAKS_TFLOPS["fp32" if prec == gd.GD_PREC_FP32 else "bf16"]
+        peak = fp32_matrix_peak(J) if prec == gd.GD_PREC_FP32 else PEAKS_TFLOPS["bf16"]
         achieved = flops_launch / avg_s / 1e12
         legs[name] = {
             "value": n * R * K / el, "ms_per_step": el / K * 1e3, "dtype": dtype,
@@ -779,9 +788,9 @@ def headline(args):
             "device_check_equals_fp64_rescore": bool(np.array_equal(E, Ed) and best == best_d),
             "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                          "frac": achieved / peak,
-                         "traffic": kernel_traffic(st.kernel_config, "dense_step_f32" if prec == gd.GD_PREC_FP32
+                         "traffic": kernel_traffic(st.kernel_config, "dense_step_split" if prec == gd.GD_PREC_FP32
                                                     else "dense_step_lp", "ising4096"),
-                         "kernel": "dense_step_f32" if prec == gd.GD_PREC_FP32 else "dense_step_lp",
+                         "kernel": "dense_step_split" if prec == gd.GD_PREC_FP32 else "dense_step_lp",
                          "launches": int(launches), "avg_launch_us": avg_s * 1e6,
                          "flops_per_launch": flops_launch},
         }
@@ -1027,6 +1036,7 @@ def main():
     small = (-(-n // 64) * 64 <= 128 and prec_name == "fp32")
     gemv = st.kernel_config >= 100 and not small
     achieved = flops_launch / avg_s / 1e12
+    peak = fp32_matrix_peak(J) if prec_name == "fp32" else PEAKS_TFLOPS[prec_name]
     if gemv:
         # J-streaming matrix-vector kernel: algorithmic HBM bytes of one launch
         # = the couplings once (FP32, or FP8 when stored so) + the state of R
@@ -1068,11 +1078,11 @@ def main():
                       "kernel": "small_step_k", "coupling_evaluations": int(launches),
                       "avg_evaluation_us": avg_s * 1e6, "flops_per_evaluation": flops_launch}
                      if small else
-                     {"bound": "mfma", "achieved": achieved, "peak": PEAKS_TFLOPS[prec_name],
-                      "unit": "TFLOP/s", "frac": achieved / PEAKS_TFLOPS[prec_name],
-                      "traffic": (kernel_traffic(st.kernel_config, "dense_step_f32")
+                     {"bound": "mfma", "achieved": achieved, "peak": peak,
+                      "unit": "TFLOP/s", "frac": achieved / peak,
+                      "traffic": (kernel_traffic(st.kernel_config, "dense_step_split")
                                   if args.workload == "xy1024" else None),
-                      "kernel": "dense_step_f32" if prec_name == "fp32" else "dense_step_lp",
+                      "kernel": "dense_step_split" if prec_name == "fp32" else "dense_step_lp",
                       "launches": int(launches),
                       "avg_launch_us": avg_s * 1e6, "flops_per_launch": flops_launch}),
         "best_energy": float(E[best]),

@@ -80,7 +80,9 @@ typedef enum gd_integrator { GD_EULER = 0, GD_RK4 = 1 } gd_integrator;
  * the amplitude/gain update and the energies are FP32 (energies are also
  * re-scored in FP64) in every mode. */
 typedef enum gd_precision {
-    GD_PREC_FP32 = 0,  /* J and Psi in FP32 (when every coupling is exact in FP8 E4M3 the
+    GD_PREC_FP32 = 0,  /* J and Psi in FP32 (the coupling product of many trajectories multiplies
+                          exact BF16 pieces of them on the matrix cores, FP32 sums: closer to
+                          64 bits than FP32 matrix instructions; when every coupling is exact in FP8 E4M3 the
                           few-trajectory kernels stream a one-byte copy of J, widened exactly
                           and summed in the FP32 order: the same results bit for bit;
                           the environment variable GD_J8_COPY=0 turns the copy off) */

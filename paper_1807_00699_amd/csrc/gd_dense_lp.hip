@@ -29,6 +29,10 @@ DenseConfig dense_lp_config(bool complex_mode, int idx) {
     return c;
 }
 
+bool dense_lp_config_fits(const DenseConfig &c, int Np, int Rp) {
+    return Np % c.bm == 0 && Np % c.bk == 0 && Rp % c.traj_tile == 0 && Np >= c.min_np;
+}
+
 hipError_t launch_dense_step_lp(const DenseConfig &cfg, bool complex_mode, int mode, int op,
                                 bool j_fp8, const DenseStepArgs &a, hipStream_t st) {
     if (op != OP_BF16 && op != OP_F16) return hipErrorInvalidValue;

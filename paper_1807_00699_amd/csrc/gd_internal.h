@@ -30,7 +30,7 @@ constexpr int kRowTile = 64;
 // [Rp][Np] floats (trajectory-major, spin contiguous, zero padded); complex
 // amplitudes use two consecutive planes (re, im) of plane_stride floats.
 struct DenseStepArgs {
-    const void *J;         // [Np][Np] coupling, operand precision (FP32 / BF16 / FP16)
+    const void *J;         // couplings in the form the launched kernel reads
     const void *B;         // GEMM operand planes (FP32, or BF16/FP16 shadow)
     const float *psi_in;   // stage-input amplitudes at (r, i) (FP32 planes)
     float *psi_out;        // output amplitudes (next stage / next step)
@@ -73,17 +73,22 @@ struct DenseConfig {
     int min_np = 0; // smallest padded size the variant runs
 };
 
-int dense_config_count(bool complex_mode);
-DenseConfig dense_config(bool complex_mode, int idx);
-bool dense_config_fits(const DenseConfig &c, int Np, int Rp);
-
-hipError_t launch_dense_step(const DenseConfig &cfg, bool complex_mode, int mode, int op,
+// FP32 steps on the BF16 matrix cores (gd_split.h): J in FP8 E4M3 (j_fp8) when
+// every coupling is exact there, else in three BF16 pieces.  Every variant
+// runs every size (row tiles past Np and trajectories past R are not written).
+int split_config_count();
+DenseConfig split_config(bool complex_mode, bool j_fp8, int idx);
+// out: J in the order those kernels read it (Np^2 bytes from the row-major
+// FP8 copy J8, or, J8 null, 6 Np^2 bytes from the FP32 J)
+hipError_t launch_tile_couplings(const float *J, const void *J8, void *out, int Np, hipStream_t st);
+hipError_t launch_split_step(const DenseConfig &cfg, bool complex_mode, int mode, bool j_fp8,
                              const DenseStepArgs &a, hipStream_t st);
 
 // Reduced-precision variants (gd_dense_lp.hip): BF16/FP16 operands, FP32
 // accumulation; J either in the operand type or FP8 E4M3 (j_fp8).
 int dense_lp_config_count();
 DenseConfig dense_lp_config(bool complex_mode, int idx);
+bool dense_lp_config_fits(const DenseConfig &c, int Np, int Rp);
 hipError_t launch_dense_step_lp(const DenseConfig &cfg, bool complex_mode, int mode, int op,
                                 bool j_fp8, const DenseStepArgs &a, hipStream_t st);
 
@@ -94,6 +99,8 @@ hipError_t launch_dense_step_lp(const DenseConfig &cfg, bool complex_mode, int m
 // 32, the row tile of its energy partials).
 constexpr int kGemvBase = 100;
 constexpr int kGemvMaxCols = 16;
+// FP32 variants of gd_split.h with 32-column tiles competing there: ids kFewBase + index
+constexpr int kFewBase = 110;
 int gemv_config_count();
 DenseConfig gemv_config(int idx);
 // variant idx runs C = R (real) or 2R (complex) columns at Np spins with

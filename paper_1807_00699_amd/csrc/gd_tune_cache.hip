@@ -45,8 +45,8 @@ std::string header() {
         cus = p.multiProcessorCount;
     }
     std::ostringstream h;
-    h << "gd-autotune 1 " << arch << " " << cus << " variants " << dense_config_count(false) << ","
-      << dense_config_count(true) << "," << dense_lp_config_count() << "," << gemv_config_count() << ","
+    h << "gd-autotune 1 " << arch << " " << cus << " variants " << split_config_count() << ","
+      << dense_lp_config_count() << "," << gemv_config_count() << ","
       << batch_config_count() << " build " << __DATE__ << "_" << __TIME__;
     return h.str();
 }
