@@ -2,6 +2,7 @@
 // of the amplitudes onto the spin domains of Eq. (h), deterministic energy
 // reductions and the FP64 re-scoring of Eq. (h).
 #include "gd_epilogue.h"
+#include "gd_readout.h"
 
 #include <algorithm>
 
@@ -44,62 +45,6 @@ __global__ void unpack_planes_k(const float *__restrict__ planes, float *__restr
 __device__ inline void store_shadow(void *dst, long long k, float v, int op) {
     if (op == OP_BF16) static_cast<__hip_bfloat16 *>(dst)[k] = __float2bfloat16(v);
     else if (op == OP_F16) static_cast<__half *>(dst)[k] = __float2half(v);
-}
-
-constexpr double kTwoPi = 6.283185307179586476925286766559;   // nearest double to 2 pi
-
-// q-state clock readout in FP64: theta = arg Psi in [0, 2pi) (Psi = 0 ->
-// theta = 0), k = floor(q theta / 2pi + 1/2) mod q.
-__device__ inline int clock_state(double x, double y, int q) {
-    double th = (x == 0.0 && y == 0.0) ? 0.0 : atan2(y, x);
-    if (th < 0.0) th += kTwoPi;
-    const long long c = (long long)floor((double)q * th / kTwoPi + 0.5);
-    return (int)(((c % q) + q) % q);
-}
-
-// Planes of clock state k: d0 = cos(2 pi k / q); d1 = sin(2 pi k / q), held
-// as sin / (sqrt(3)/2) in {0, +-1} for q = 3 and 6 so that both planes are
-// exact (their product then carries the weight 3/4).
-__device__ inline void clock_planes(int k, int q, double &d0, double &d1) {
-    switch (q) {
-    case 2: d0 = k ? -1.0 : 1.0; d1 = 0.0; return;
-    case 3: d0 = k ? -0.5 : 1.0; d1 = k == 0 ? 0.0 : (k == 1 ? 1.0 : -1.0); return;
-    case 4: d0 = k == 0 ? 1.0 : (k == 2 ? -1.0 : 0.0); d1 = k == 1 ? 1.0 : (k == 3 ? -1.0 : 0.0); return;
-    case 6:   // cos: 1, 1/2, -1/2, -1, -1/2, 1/2; sin / (sqrt(3)/2): 0, 1, 1, 0, -1, -1
-        d0 = k == 0 ? 1.0 : (k == 3 ? -1.0 : ((k == 1 || k == 5) ? 0.5 : -0.5));
-        d1 = (k == 0 || k == 3) ? 0.0 : (k < 3 ? 1.0 : -1.0);
-        return;
-    default: sincospi(2.0 * k / q, &d1, &d0); return;
-    }
-}
-
-// Discretised planes (d0, d1) of one amplitude in FP64 for readout `ro`;
-// `k` receives the clock state (RO_CLOCK) or 0/1 for the sign readouts.
-__device__ inline void readout_planes(double x, double y, int ro, int q, double &d0, double &d1,
-                                      int &k) {
-    d1 = 0.0;
-    k = 0;
-    switch (ro) {
-    case RO_SIGN:
-    case RO_SIGN_RE:
-        d0 = (x < 0.0) ? -1.0 : 1.0;   // sign(+-0) = +1
-        k = x < 0.0;
-        return;
-    case RO_PHASOR: {
-        if (x == 0.0 && y == 0.0) {
-            d0 = 1.0;
-            return;
-        }
-        const double m = sqrt(x * x + y * y);
-        d0 = x / m;
-        d1 = y / m;
-        return;
-    }
-    default:
-        k = clock_state(x, y, q);
-        clock_planes(k, q, d0, d1);
-        return;
-    }
 }
 
 // Readout onto the spin domains of Eq. (h).
@@ -337,181 +282,6 @@ energy_fp64_k(const float *__restrict__ J, const double *__restrict__ D64, const
     if (tid < E64_T) partial[(long long)mt * Rp + r0 + tid] = red[0][tid] + red[1][tid];
 }
 
-// Device energy check of a small problem, closing the launch of its steps:
-// trajectory r's Eq. (h) energy E_r = sum_i [-(d0_i T0_i + w d1_i T1_i) +
-// g_i d0_i], d the readout planes of the model (formed in FP64, held in FP32
-// as in the coupling kernels' energy mode), T = J d summed in FP32 in j
-// order, the Np terms added in FP64 in a fixed tree.  d0s, d1s, reds: this
-// trajectory's LDS rows; every thread of the workgroup calls it.
-template <bool CPLX, int NPX>
-__device__ inline void small_energy(const DenseStepArgs &a, const float *Js, float *d0s, float *d1s,
-                                    double *reds, int i, int r, float x, float y, int ro, int q,
-                                    double *__restrict__ E) {
-    double e0 = 0.0, e1 = 0.0;
-    if (r < a.R && i < a.n) {
-        int k;
-        readout_planes(x, y, ro, q, e0, e1, k);
-    }
-    const float d0 = float(e0), d1 = float(e1);
-    d0s[i] = d0;
-    if (CPLX) d1s[i] = d1;
-    __syncthreads();
-    float t0 = 0.0f, t1 = 0.0f;
-    for (int j = 0; j < NPX; ++j) {
-        const float w = Js[j * NPX + i];
-        t0 = fmaf(w, d0s[j], t0);
-        if (CPLX) t1 = fmaf(w, d1s[j], t1);
-    }
-    double term = -(double)d0 * (double)t0 + (double)a.g[i] * (double)d0;
-    if (CPLX) term -= (double)a.im_weight * ((double)d1 * (double)t1);
-    reds[i] = term;
-    __syncthreads();
-    for (int w = NPX / 2; w > 0; w >>= 1) {
-        if (i < w) reds[i] += reds[i + w];
-        __syncthreads();
-    }
-    if (i == 0 && r < a.R) E[r] = reds[0];
-}
-
-// Many integration steps of a small dense problem in one launch (Np <= 128,
-// FP32 operands): a workgroup holds J and the
-// amplitudes of 256 / Np trajectories in LDS for all the steps, one thread
-// per (spin, trajectory) with its amplitude and gain in registers.  Per
-// coupling evaluation: C_ir = sum_j J_ij Psi_jr in j order (J is symmetric,
-// so lanes on consecutive i read row j contiguously), then Eq. (main) and
-// Eq. (gamma) as in the dense kernels: an explicit Euler step, or the four
-// stages of the classical RK4 step on the joint state (Psi, gamma); then the
-// noise increment of step t0 + st (amplitude a.noise_amp, key derived from
-// `seed` and the step index as on the host).  With E: the energy check of
-// the final state (readout ro, clock order q) into E[r].
-template <bool CPLX, int NPX, bool RK4>
-__global__ void __launch_bounds__(256)
-small_step_k(DenseStepArgs a, int steps, unsigned long long seed, long long t0, int ro, int q,
-             double *E) {
-    constexpr int TR = 256 / NPX;
-    constexpr int PL = CPLX ? 2 : 1;
-    __shared__ float Js[NPX * NPX];
-    __shared__ float xs[PL][TR][NPX];
-    __shared__ float ds[PL][TR][NPX];
-    __shared__ double red[TR][NPX];
-    const int tid = threadIdx.x;
-    const int i = tid % NPX, tl = tid / NPX;
-    const int r = blockIdx.x * TR + tl;
-    const long long idx = (long long)r * NPX + i;
-    const long long ps = a.plane_stride;
-    const float *J = static_cast<const float *>(a.J);
-    for (int q = tid; q < NPX * NPX; q += 256) Js[q] = J[q];
-    float x = a.psi_in[idx];
-    float y = CPLX ? a.psi_in[ps + idx] : 0.0f;
-    float g = a.gam_in[idx];
-    const float ep = a.eps[i], hh = a.h1[i];
-    const bool valid = r < a.R && i < a.n;
-    // sums over the amplitudes in LDS, then the right-hand side at (sx, sy, sg)
-    auto rhs = [&](float sx, float sy, float sg, float &fr, float &fi, float &fg) {
-        float cr = 0.0f, ci = 0.0f;
-        // 16 terms at a time: their LDS reads are issued together, then the
-        // multiply-adds run in j order
-        for (int j0 = 0; j0 < NPX; j0 += 16) {
-            float w[16], v0[16], v1[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                w[u] = Js[(j0 + u) * NPX + i];
-                v0[u] = xs[0][tl][j0 + u];
-                v1[u] = CPLX ? xs[PL - 1][tl][j0 + u] : 0.0f;
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                cr = fmaf(w[u], v0[u], cr);
-                if (CPLX) ci = fmaf(w[u], v1[u], ci);
-            }
-        }
-        const float rho = CPLX ? sx * sx + sy * sy : sx * sx;
-        const float lin = sg - a.gamma_c - rho;
-        fr = sx * lin + cr * a.inv_s + hh;
-        fi = CPLX ? sy * lin + ci * a.inv_s : 0.0f;
-        fg = ep * (a.rho_th - rho);
-        if (CPLX && a.q >= 2) {
-            // resonant term h_q conj(Psi)^(q-1), as in the dense kernels
-            float pr = sx, pi = -sy;
-            for (int k = 2; k < a.q; ++k) {
-                const float tr = pr * sx + pi * sy;
-                const float ti = pi * sx - pr * sy;
-                pr = tr;
-                pi = ti;
-            }
-            fr += a.hq * pr;
-            fi += a.hq * pi;
-        }
-    };
-    // publish amplitudes (sx, sy) once every thread has read the previous ones
-    auto publish = [&](float sx, float sy) {
-        __syncthreads();
-        xs[0][tl][i] = sx;
-        if (CPLX) xs[PL - 1][tl][i] = sy;
-        __syncthreads();
-    };
-    publish(x, y);
-    const float dt = a.dt;
-    auto add_noise = [&](int st) {
-        if (a.noise_amp != 0.0f && valid) {
-            float g0, g1;
-            noise_pair(mix64(seed ^ mix64((unsigned long long)(t0 + st))), r, i, g0, g1);
-            x += a.noise_amp * g0;
-            if (CPLX) y += a.noise_amp * g1;
-        }
-    };
-    for (int st = 0; st < steps; ++st) {
-        float fr, fi, fg;
-        if constexpr (!RK4) {
-            rhs(x, y, g, fr, fi, fg);
-            if (valid) {
-                x = x + dt * fr;
-                y = y + dt * fi;
-                g = g + dt * fg;
-            }
-            add_noise(st);
-            publish(x, y);
-        } else {
-            // stage inputs s = y + c k with c = dt/2, dt/2, dt; accumulator
-            // k1 + 2 k2 + 2 k3 (rows outside n keep their state)
-            float ar, ai, ag, sx, sy, sg;
-            rhs(x, y, g, fr, fi, fg);                                    // k1
-            ar = fr; ai = fi; ag = fg;
-            sx = valid ? x + 0.5f * dt * fr : x;
-            sy = valid ? y + 0.5f * dt * fi : y;
-            sg = valid ? g + 0.5f * dt * fg : g;
-            publish(sx, sy);
-            rhs(sx, sy, sg, fr, fi, fg);                                 // k2
-            ar += 2.0f * fr; ai += 2.0f * fi; ag += 2.0f * fg;
-            sx = valid ? x + 0.5f * dt * fr : x;
-            sy = valid ? y + 0.5f * dt * fi : y;
-            sg = valid ? g + 0.5f * dt * fg : g;
-            publish(sx, sy);
-            rhs(sx, sy, sg, fr, fi, fg);                                 // k3
-            ar += 2.0f * fr; ai += 2.0f * fi; ag += 2.0f * fg;
-            sx = valid ? x + dt * fr : x;
-            sy = valid ? y + dt * fi : y;
-            sg = valid ? g + dt * fg : g;
-            publish(sx, sy);
-            rhs(sx, sy, sg, fr, fi, fg);                                 // k4
-            const float c6 = dt * (1.0f / 6.0f);
-            if (valid) {
-                x = x + c6 * (ar + fr);
-                y = y + c6 * (ai + fi);
-                g = g + c6 * (ag + fg);
-            }
-            add_noise(st);
-            publish(x, y);
-        }
-    }
-    a.psi_out[idx] = x;
-    if (CPLX) a.psi_out[ps + idx] = y;
-    a.gam_out[idx] = g;
-    // non-finite values persist once they appear, so the final state tells
-    if (r < a.R && !(__builtin_isfinite(x) && __builtin_isfinite(y) && __builtin_isfinite(g))) a.flags[r] = 1;
-    if (E) small_energy<CPLX, NPX>(a, Js, ds[0][tl], ds[PL - 1][tl], red[tl], i, r, x, y, ro, q, E);
-}
-
 __global__ void make_shadow_k(const float *__restrict__ src, void *dst, long long count, int op) {
     for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < count;
          t += (long long)gridDim.x * blockDim.x)
@@ -608,26 +378,6 @@ hipError_t launch_energy_fp64(const float *J, const float *psi, const float *g, 
         energy_fp64_k<2><<<grid, 256, 0, st>>>(J, D64, g, partial, Np, Rp, plane_stride, w);
     else
         energy_fp64_k<1><<<grid, 256, 0, st>>>(J, D64, g, partial, Np, Rp, plane_stride, w);
-    return hipGetLastError();
-}
-
-hipError_t launch_small_steps(bool complex_mode, bool rk4, const DenseStepArgs &a, int steps,
-                              unsigned long long seed, long long t0, int readout, int q, double *E,
-                              hipStream_t st) {
-    if (steps < 1 || (a.Np != 64 && a.Np != 128)) return hipErrorInvalidValue;
-    if (E && readout == RO_CLOCK && (q < 2 || q > 8)) return hipErrorInvalidValue;
-    const int tr = 256 / a.Np;
-    if (a.Rp % tr) return hipErrorInvalidValue;
-    const dim3 grid(a.Rp / tr);
-#define GD_SMALL(C, N, K) small_step_k<C, N, K><<<grid, 256, 0, st>>>(a, steps, seed, t0, readout, q, E)
-    if (a.Np == 64) {
-        if (complex_mode) { if (rk4) GD_SMALL(true, 64, true); else GD_SMALL(true, 64, false); }
-        else { if (rk4) GD_SMALL(false, 64, true); else GD_SMALL(false, 64, false); }
-    } else {
-        if (complex_mode) { if (rk4) GD_SMALL(true, 128, true); else GD_SMALL(true, 128, false); }
-        else { if (rk4) GD_SMALL(false, 128, true); else GD_SMALL(false, 128, false); }
-    }
-#undef GD_SMALL
     return hipGetLastError();
 }
 

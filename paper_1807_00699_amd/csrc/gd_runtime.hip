@@ -170,6 +170,7 @@ struct gd_solver {
     // (the same results bit for bit); GD_J8_COPY=0 keeps FP32 J only
     void *dJ8 = nullptr;
     void *dJt = nullptr;       // FP32 solvers: J (FP8, or three BF16 pieces) as the split kernels read it
+    float *dJs = nullptr;      // FP32 solvers with Np <= 128: J as the fused small-problem kernel reads it
     void *shadow[3] = {nullptr, nullptr, nullptr};   // operand copies of psi[k]
     void *shadowD = nullptr;   // operand copy of the discretised state
     // state
@@ -463,6 +464,16 @@ int enqueue_step(gd_solver *s, const DenseConfig &cfg, float dt_override, bool t
     return GD_OK;
 }
 
+// J in the order the split kernels read it, laid out once per solver
+int tile_couplings(gd_solver *s) {
+    if (s->op != OP_F32 || s->dJt) return GD_OK;
+    const size_t m = (size_t)s->Np * s->Np;
+    const int rc = dalloc(reinterpret_cast<uint8_t **>(&s->dJt), s->dJ8 ? m : 6 * m);
+    if (rc != GD_OK) return rc;
+    GD_HIP(launch_tile_couplings(s->dJ, s->dJ8, s->dJt, s->Np, s->stream));
+    return GD_OK;
+}
+
 // Pick the coupling kernel variant: GD_DENSE_CONFIG forces one; otherwise each
 // variant that fits (the GEMM tiles, and for at most kGemvMaxCols GEMM columns
 // also the J-streaming matrix-vector kernels, ids kGemvBase + k) is timed on
@@ -500,11 +511,17 @@ int choose_config(gd_solver *s) {
         if (id < 0 || id >= nc) return false;
         return !lp || dense_lp_config_fits(cfg_of(id), s->Np, s->Rp);
     };
-    if (!lp && !s->dJt) {
-        const size_t m = (size_t)s->Np * s->Np;
-        const int rc = dalloc(reinterpret_cast<uint8_t **>(&s->dJt), s->dJ8 ? m : 6 * m);
+    // the fused kernel needs its own form of J; the coupling kernels' form is
+    // laid out when they first run (energy checks outside a run, pinned variants)
+    const bool fused = !lp && !s->mod() && s->Np <= 128;
+    if (fused && !s->dJs) {
+        const int rc = dalloc(&s->dJs, (size_t)s->Np * s->Np);
         if (rc != GD_OK) return rc;
-        GD_HIP(launch_tile_couplings(s->dJ, s->dJ8, s->dJt, s->Np, s->stream));
+        GD_HIP(launch_small_couplings(s->dJ, s->dJs, s->Np, s->stream));
+    }
+    if (!fused) {
+        const int rc = tile_couplings(s);
+        if (rc != GD_OK) return rc;
     }
     if (const char *env = std::getenv("GD_DENSE_CONFIG")) {
         int id = std::atoi(env);
@@ -946,6 +963,7 @@ void gd_destroy(gd_solver *s) {
     if (s->dJlp) (void)hipFree(s->dJlp);
     if (s->dJ8) (void)hipFree(s->dJ8);
     if (s->dJt) (void)hipFree(s->dJt);
+    if (s->dJs) (void)hipFree(s->dJs);
     for (hipEvent_t e : s->events) (void)hipEventDestroy(e);
     for (hipEvent_t e : {s->ev_chk[0], s->ev_chk[1], s->ev_run0, s->ev_end})
         if (e) (void)hipEventDestroy(e);
@@ -1057,6 +1075,7 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     const bool rk4 = s->integrator() == GD_RK4;
     const bool small_ok = !s->mod() && s->op == OP_F32 && s->Np <= 128 &&
                           std::getenv("GD_DENSE_CONFIG") == nullptr;
+    if (!small_ok && !s->mod() && (rc = tile_couplings(s)) != GD_OK) return rc;
     // The matrix-vector kernels of few trajectories run for microseconds, so
     // they are always replayed from graphs (with GD_F_PROFILE one event pair
     // brackets each replay and its launches, in-graph dispatch gaps included).
@@ -1124,6 +1143,7 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
             while (k < chunk) {
                 const int m = int(std::min<int64_t>(chunk - k, kSmallStepsPerLaunch));
                 DenseStepArgs a = base_args(s);
+                a.J = s->dJs;
                 a.psi_in = s->psi[s->cur];
                 a.psi_out = s->psi[s->cur ^ 1];
                 a.gam_in = s->gam;
@@ -1249,6 +1269,10 @@ static int energies(gd_solver *s, double *E, int32_t *best, bool fp64) {
     if (s->batch) return batch_energy(s->batch, E, best);
     if (!s->have_state) return fail(GD_E_STATE, "no state: call gd_set_init or gd_run first");
     if (!E) return fail(GD_E_INVALID_ARG, "E is NULL");
+    if (!fp64) {
+        const int rc = tile_couplings(s);
+        if (rc != GD_OK) return rc;
+    }
     const float *cur = s->psi[s->cur];
     GD_HIP(launch_discretise(cur, s->D, s->shadowD, s->op, s->ro, s->prm.q, nullptr, nullptr, nullptr,
                              s->flags, s->n, s->R, s->Np, s->Rp, s->P, s->plane(), s->stream));
