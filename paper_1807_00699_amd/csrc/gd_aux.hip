@@ -29,16 +29,30 @@ __global__ void pack_planes_k(const float *__restrict__ user, float *__restrict_
     }
 }
 
-__global__ void unpack_planes_k(const float *__restrict__ planes, float *__restrict__ user, int n,
-                                int R, int Np, int Rp, int P) {
-    const long long total = (long long)R * n;
-    const long long pstride = (long long)Rp * Np;
-    for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total;
-         t += (long long)gridDim.x * blockDim.x) {
-        const int r = int(t / n), i = int(t % n);
-        const long long src = (long long)r * Np + i;
-        if (P == 1) user[t] = planes[src];
-        else for (int p = 0; p < P; ++p) user[t * 2 + p] = planes[p * pstride + src];
+// Four spins of one trajectory per thread; `vec`: rows of the user's array are
+// 16-byte aligned (n a multiple of 4).  Bound by HBM.
+template <int P>
+__global__ void __launch_bounds__(256) unpack_planes_k(const float *__restrict__ planes, float *__restrict__ user,
+                                                       int n, int R, int Np, long long ps, bool vec) {
+    const int i = 4 * (blockIdx.x * 256 + threadIdx.x);
+    if (i >= n) return;
+    for (int r = blockIdx.y; r < R; r += gridDim.y) {
+        const float *src = planes + (long long)r * Np + i;
+        float *dst = user + ((long long)r * n + i) * P;
+        f32x4 v[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) v[p] = *reinterpret_cast<const f32x4 *>(src + p * ps);
+        f32x4 o[P];
+#pragma unroll
+        for (int e = 0; e < 4 * P; ++e) o[e / 4][e % 4] = v[e % P][e / P];
+        if (vec) {
+#pragma unroll
+            for (int p = 0; p < P; ++p) *reinterpret_cast<f32x4 *>(dst + 4 * p) = o[p];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4 * P; ++e)
+                if (i + e / P < n) dst[e] = o[e / 4][e % 4];
+        }
     }
 }
 
@@ -288,7 +302,11 @@ __global__ void make_shadow_k(const float *__restrict__ src, void *dst, long lon
         store_shadow(dst, t, src[t], op);
 }
 
-__global__ void count_flags_k(const int *__restrict__ flags, int R, int *out) {
+// What the host reads at the end of a run, written straight to its pinned
+// memory: the number of trajectories with flags set and (run_e non-null) the
+// running best of the checks.
+__global__ void run_result_k(const int *__restrict__ flags, int R, const double *__restrict__ run_e,
+                             const int *__restrict__ run_i, RunResult *out) {
     __shared__ int s[256];
     int c = 0;
     for (int r = threadIdx.x; r < R; r += blockDim.x) c += flags[r] != 0;
@@ -298,7 +316,13 @@ __global__ void count_flags_k(const int *__restrict__ flags, int R, int *out) {
         if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[0] = s[0];
+    if (threadIdx.x == 0) {
+        out->diverged = s[0];
+        if (run_e) {
+            out->best_e = run_e[0];
+            out->best_i = run_i[0];
+        }
+    }
 }
 
 inline int grid_for(long long total) {
@@ -328,7 +352,11 @@ hipError_t launch_pack_planes(const float *user, float *planes, int n, int R, in
 
 hipError_t launch_unpack_planes(const float *planes, float *user, int n, int R, int Np, int Rp,
                                 int nplanes, hipStream_t st) {
-    unpack_planes_k<<<grid_for((long long)R * n), 256, 0, st>>>(planes, user, n, R, Np, Rp, nplanes);
+    const dim3 grid(unsigned((n + 1023) / 1024), unsigned(std::min(R, 65535)));
+    const long long ps = (long long)Rp * Np;
+    const bool vec = n % 4 == 0 && reinterpret_cast<uintptr_t>(user) % 16 == 0;
+    if (nplanes == 2) unpack_planes_k<2><<<grid, 256, 0, st>>>(planes, user, n, R, Np, ps, vec);
+    else unpack_planes_k<1><<<grid, 256, 0, st>>>(planes, user, n, R, Np, ps, vec);
     return hipGetLastError();
 }
 
@@ -391,8 +419,9 @@ hipError_t launch_make_shadow(const float *src, void *dst, long long count, int 
     return hipGetLastError();
 }
 
-hipError_t launch_count_flags(const int *flags, int R, int *out, hipStream_t st) {
-    count_flags_k<<<1, 256, 0, st>>>(flags, R, out);
+hipError_t launch_run_result(const int *flags, int R, const double *run_e, const int *run_i, RunResult *out,
+                             hipStream_t st) {
+    run_result_k<<<1, 256, 0, st>>>(flags, R, run_e, run_i, out);
     return hipGetLastError();
 }
 

@@ -219,8 +219,14 @@ hipError_t launch_energy_fp64(const float *J, const float *psi, const float *g, 
                               long long plane_stride, int readout, int q, hipStream_t st);
 // shadow copy of FP32 planes in BF16 / FP16
 hipError_t launch_make_shadow(const float *src, void *dst, long long count, int op, hipStream_t st);
-// any_flag: out[0] = number of r < R with flags[r] != 0
-hipError_t launch_count_flags(const int *flags, int R, int *out, hipStream_t st);
+// What the host reads at the end of a run (out: pinned host memory)
+struct RunResult {
+    double best_e;   // running best of the checks and its trajectory
+    int best_i;
+    int diverged;    // trajectories r < R with flags[r] != 0
+};
+hipError_t launch_run_result(const int *flags, int R, const double *run_e, const int *run_i, RunResult *out,
+                             hipStream_t st);
 // J in the order the small-problem kernel reads it (Np 64 or 128; Np^2 floats)
 hipError_t launch_small_couplings(const float *J, float *out, int Np, hipStream_t st);
 // `steps` Euler or RK4 steps of a small problem (Np 64 or 128; FP32; a.J from

@@ -183,7 +183,7 @@ struct gd_solver {
     float *K = nullptr;        // GD-mod couplings [R][Np][Np]
     double *D64 = nullptr;     // FP64 readout planes of the re-score (allocated on first use)
     double *partial = nullptr, *dE = nullptr;
-    int *flags = nullptr, *dBest = nullptr, *dCount = nullptr;
+    int *flags = nullptr, *dBest = nullptr;
     // minimum energy of each device check since gd_set_init / gd_set_state
     // (the first kTraceChecks checks) and the step of each
     double *dTrace = nullptr;
@@ -203,6 +203,7 @@ struct gd_solver {
         int i;
     };
     CheckSlot *hchk = nullptr;            // 2 slots (hipHostMalloc)
+    gd::RunResult *hres = nullptr;        // results of a run (hipHostMalloc at the first)
     hipEvent_t ev_chk[2] = {nullptr, nullptr};
     hipEvent_t ev_run0 = nullptr;         // start of the current gd_run
     hipEvent_t ev_end = nullptr;          // end of the current gd_run
@@ -241,11 +242,10 @@ void free_state(gd_solver *s) {
     if (s->dE) (void)hipFree(s->dE);
     if (s->flags) (void)hipFree(s->flags);
     if (s->dBest) (void)hipFree(s->dBest);
-    if (s->dCount) (void)hipFree(s->dCount);
     if (s->dTrace) (void)hipFree(s->dTrace);
     s->dTrace = nullptr;
     s->partial = s->dE = nullptr;
-    s->flags = s->dBest = s->dCount = nullptr;
+    s->flags = s->dBest = nullptr;
     s->have_state = false;
     s->R = s->Rp = 0;
 }
@@ -305,7 +305,6 @@ int alloc_state(gd_solver *s, int R) {
     if (rc == GD_OK) rc = dalloc(&s->dE, (size_t)s->Rp + 2);
     if (rc == GD_OK) rc = dalloc(&s->flags, (size_t)s->Rp);
     if (rc == GD_OK) rc = dalloc(&s->dBest, 2);   // best of the last check, running best
-    if (rc == GD_OK) rc = dalloc(&s->dCount, 1);
     if (rc == GD_OK) rc = dalloc(&s->dTrace, (size_t)kTraceChecks);
     if (rc != GD_OK) {
         free_state(s);
@@ -675,21 +674,34 @@ int upload_planes(gd_solver *s, const float *user, float *planes, int R) {
     return GD_OK;
 }
 
-int download_planes(gd_solver *s, const float *planes, float *user, int P) {
-    const size_t cnt = (size_t)s->R * s->n * P;
-    float *tmp = nullptr;
-    int rc = dalloc(&tmp, cnt);
-    if (rc != GD_OK) return rc;
-    hipError_t e = launch_unpack_planes(planes, tmp, s->n, s->R, s->Np, s->Rp, P, s->stream);
-    if (e == hipSuccess) {
-        if (s->prm.flags & GD_F_DEVICE_PTRS)
-            e = hipMemcpyAsync(user, tmp, cnt * sizeof(float), hipMemcpyDeviceToDevice, s->stream);
-        else
-            e = hipMemcpyAsync(user, tmp, cnt * sizeof(float), hipMemcpyDeviceToHost, s->stream);
+// Whether a kernel may write `bytes` at a caller's device pointer itself: on
+// this solver's device and inside its allocation (anything else goes through a
+// staging buffer and hipMemcpy, which refuses what is not valid).
+bool device_span(const gd_solver *s, const void *p, size_t bytes) {
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    if (hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice || at.device != s->device ||
+        hipMemGetAddressRange(&base, &size, const_cast<void *>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
     }
-    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
-    (void)hipFree(tmp);
-    if (e != hipSuccess) return fail(GD_E_DEVICE, std::string("download: ") + hipGetErrorString(e));
+    const uintptr_t b = reinterpret_cast<uintptr_t>(base), q = reinterpret_cast<uintptr_t>(p);
+    return q >= b && q - b <= size && bytes <= size - (q - b);
+}
+
+// Planes into the caller's [R][n] (or [R][n][2]) array, on the solver's stream:
+// straight into device memory, else through D (the readout planes' scratch,
+// rewritten before every use).
+int download_planes(gd_solver *s, const float *planes, float *user, int P) {
+    const size_t bytes = (size_t)s->R * s->n * P * sizeof(float);
+    const bool dev = (s->prm.flags & GD_F_DEVICE_PTRS) != 0;
+    if (dev && reinterpret_cast<uintptr_t>(user) % 4 == 0 && device_span(s, user, bytes)) {
+        GD_HIP(launch_unpack_planes(planes, user, s->n, s->R, s->Np, s->Rp, P, s->stream));
+        return GD_OK;
+    }
+    GD_HIP(launch_unpack_planes(planes, s->D, s->n, s->R, s->Np, s->Rp, P, s->stream));
+    GD_HIP(hipMemcpyAsync(user, s->D, bytes, dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s->stream));
     return GD_OK;
 }
 
@@ -968,6 +980,7 @@ void gd_destroy(gd_solver *s) {
     for (hipEvent_t e : {s->ev_chk[0], s->ev_chk[1], s->ev_run0, s->ev_end})
         if (e) (void)hipEventDestroy(e);
     if (s->hchk) (void)hipHostFree(s->hchk);
+    if (s->hres) (void)hipHostFree(s->hres);
     if (s->own_stream && s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
 }
@@ -1226,6 +1239,10 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     if (s->prm.flags & GD_F_ASYNC) return GD_OK;
     if ((rc = read_pending()) != GD_OK) return rc;
     if (clocked) GD_HIP(hipEventRecord(s->ev_end, s->stream));
+    // one wait for the steps and for what the host reads of them, written to
+    // pinned memory by the last kernel
+    if (!s->hres) GD_HIP(hipHostMalloc(reinterpret_cast<void **>(&s->hres), sizeof(RunResult)));
+    GD_HIP(launch_run_result(s->flags, s->R, deferred ? s->dE + s->Rp + 1 : nullptr, s->dBest + 1, s->hres, s->stream));
     GD_HIP(hipStreamSynchronize(s->stream));
     s->run_seconds += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     if (clocked) {
@@ -1243,19 +1260,12 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
         s->ev_used = 0;
         s->ev_launches = 0;
     }
-    GD_HIP(launch_count_flags(s->flags, s->R, s->dCount, s->stream));
-    int cnt = 0;
-    GD_HIP(hipMemcpyAsync(&cnt, s->dCount, sizeof(int), hipMemcpyDeviceToHost, s->stream));
-    double run_e = s->best_energy;
-    int run_i = s->best_index;
-    if (deferred) {
-        GD_HIP(hipMemcpyAsync(&run_e, s->dE + s->Rp + 1, sizeof(double), hipMemcpyDeviceToHost, s->stream));
-        GD_HIP(hipMemcpyAsync(&run_i, s->dBest + 1, sizeof(int), hipMemcpyDeviceToHost, s->stream));
-    }
-    GD_HIP(hipStreamSynchronize(s->stream));
+    const int cnt = s->hres->diverged;
     s->diverged = cnt;
-    s->best_energy = run_e;
-    s->best_index = run_i;
+    if (deferred) {
+        s->best_energy = s->hres->best_e;
+        s->best_index = s->hres->best_i;
+    }
     if (cnt) {
         char buf[64];
         std::snprintf(buf, sizeof buf, "%d trajectories became non-finite", cnt);
@@ -1324,19 +1334,22 @@ int gd_spins(gd_solver *s, void *out, int32_t fmt) {
         return fail(GD_E_INVALID_ARG, "int32 states need the Potts model");
     const size_t cnt = (size_t)s->R * s->n;
     const size_t bytes = cnt * (fmt == GD_SPINS_I8 ? 1 : 4);
-    void *tmp = nullptr;
-    GD_HIP(hipMalloc(&tmp, bytes));
+    // straight into the caller's device memory, else through a buffer
+    const bool direct = (s->prm.flags & GD_F_DEVICE_PTRS) &&
+                        (fmt == GD_SPINS_I8 || reinterpret_cast<uintptr_t>(out) % 4 == 0) && device_span(s, out, bytes);
+    void *tmp = out;
+    if (!direct) GD_HIP(hipMalloc(&tmp, bytes));
     hipError_t e = launch_discretise(s->psi[s->cur], s->D, nullptr, OP_F32, s->ro, s->prm.q,
                                      fmt == GD_SPINS_I8 ? static_cast<int8_t *>(tmp) : nullptr,
                                      fmt == GD_SPINS_ANGLE_F32 ? static_cast<float *>(tmp) : nullptr,
                                      fmt == GD_SPINS_STATE_I32 ? static_cast<int32_t *>(tmp) : nullptr,
                                      s->flags, s->n, s->R, s->Np, s->Rp, s->P, s->plane(), s->stream);
-    if (e == hipSuccess)
+    if (e == hipSuccess && !direct)
         e = hipMemcpyAsync(out, tmp, bytes,
                            (s->prm.flags & GD_F_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
                            s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
-    (void)hipFree(tmp);
+    if (!direct) (void)hipFree(tmp);
     if (e != hipSuccess) return fail(GD_E_DEVICE, std::string("gd_spins: ") + hipGetErrorString(e));
     return GD_OK;
 }
@@ -1383,6 +1396,7 @@ int gd_get_state(gd_solver *s, float *psi, float *gamma, int64_t *step) {
     int rc;
     if (psi && (rc = download_planes(s, s->psi[s->cur], psi, s->P)) != GD_OK) return rc;
     if (gamma && (rc = download_planes(s, s->gam, gamma, 1)) != GD_OK) return rc;
+    if (psi || gamma) GD_HIP(hipStreamSynchronize(s->stream));
     if (step) *step = s->steps_done;
     return GD_OK;
 }

@@ -1,0 +1,51 @@
+"""State and spins read straight into the caller's device memory (GD_F_DEVICE_PTRS)
+equal the same solver's host read-back bit for bit: rows that are and are not
+16-byte aligned, destinations in the middle of an allocation, real and complex."""
+import ctypes
+
+import numpy as np
+import pytest
+
+from paper_1807_00699_amd import gd
+from paper_1807_00699_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+def _ptr(t, off):
+    return ctypes.c_void_p(t.data_ptr() + t.element_size() * off)
+
+
+@pytest.mark.parametrize("model", [gd.GD_ISING, gd.GD_XY])
+@pytest.mark.parametrize("n,R", [(1, 1), (66, 5), (132, 3), (1100, 2)])
+def test_device_readback_equals_host(n, R, model):
+    import torch
+    cx = model == gd.GD_XY
+    J = I.dense_pm1(n, 5)
+    x0 = I.psi0_complex(n, R, 5) if cx else I.psi0_real(n, R, 5)
+    with gd.Solver(J, model=model, dt=0.02) as S:
+        S.set_init(R, x0)
+        S.run(3)
+        want_p, want_g, _ = S.state()
+        want_s = S.spins()
+    lib = gd.load()
+    Jd, xd = torch.from_numpy(J).cuda(), torch.from_numpy(x0).cuda()
+    torch.cuda.synchronize()
+    h = gd.gd_create(Jd, model=model, params=gd.default_params(dt=0.02, flags=gd.GD_F_DEVICE_PTRS))
+    try:
+        gd.gd_set_init(h, R, xd, device=True)
+        gd.gd_run(h, R, 3)
+        for off in (0, 1, 4):
+            p = torch.full((want_p.size + off + 8,), -7.0, device="cuda")
+            g = torch.full((want_g.size + off + 8,), -7.0, device="cuda")
+            s = torch.full((want_s.size + off + 8,), 9, device="cuda",
+                           dtype=torch.float32 if cx else torch.int8)
+            torch.cuda.synchronize()
+            assert lib.gd_get_state(h, _ptr(p, off), _ptr(g, off), None) == gd.GD_OK
+            assert lib.gd_spins(h, _ptr(s, off), gd.GD_SPINS_ANGLE_F32 if cx else gd.GD_SPINS_I8) == gd.GD_OK
+            for t, want, pad in ((p, want_p, -7), (g, want_g, -7), (s, want_s, 9)):
+                a = t.cpu().numpy()
+                assert np.array_equal(a[off:off + want.size], want.ravel())
+                assert np.all(a[:off] == pad) and np.all(a[off + want.size:] == pad)
+    finally:
+        gd.gd_destroy(h)
