@@ -110,8 +110,8 @@ discretise_k(const float *__restrict__ psi, float *__restrict__ D, void *shadowD
             nan |= __builtin_isnan(x) || __builtin_isnan(y);
         }
         if (nan) flags[r] = 1;
-        *reinterpret_cast<f32x4 *>(D + t) = d0v;
-        if (P == 2) *reinterpret_cast<f32x4 *>(D + ps + t) = d1v;
+        if (D) *reinterpret_cast<f32x4 *>(D + t) = d0v;
+        if (D && P == 2) *reinterpret_cast<f32x4 *>(D + ps + t) = d1v;
         if (shadowD) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -307,7 +307,7 @@ __global__ void make_shadow_k(const float *__restrict__ src, void *dst, long lon
 // running best of the checks.
 __global__ void run_result_k(const int *__restrict__ flags, int R, const double *__restrict__ run_e,
                              const int *__restrict__ run_i, RunResult *out) {
-    __shared__ int s[256];
+    __shared__ int s[1024];
     int c = 0;
     for (int r = threadIdx.x; r < R; r += blockDim.x) c += flags[r] != 0;
     s[threadIdx.x] = c;
@@ -377,7 +377,9 @@ hipError_t launch_discretise(const float *psi, float *D, void *shadowD, int op, 
 hipError_t launch_energy_reduce(const double *partial, int ntiles, int Rp, int R, double *E,
                                 int *best, hipStream_t st, double *run_e, int *run_i, double *trace) {
     if (R < 1) return hipErrorInvalidValue;
-    if (R <= 512 && ntiles >= 32)
+    // one thread per trajectory reads its tiles one after the other: N = 800,
+    // R = 100 (26 tiles) 7.3 us
+    if (R <= 512 && ntiles >= 8)
         energy_sum_wide_k<<<R, 64, 0, st>>>(partial, ntiles, Rp, E);
     else
         energy_sum_k<<<(R + 255) / 256, 256, 0, st>>>(partial, ntiles, Rp, R, E);
@@ -421,7 +423,7 @@ hipError_t launch_make_shadow(const float *src, void *dst, long long count, int 
 
 hipError_t launch_run_result(const int *flags, int R, const double *run_e, const int *run_i, RunResult *out,
                              hipStream_t st) {
-    run_result_k<<<1, 256, 0, st>>>(flags, R, run_e, run_i, out);
+    run_result_k<<<1, 1024, 0, st>>>(flags, R, run_e, run_i, out);
     return hipGetLastError();
 }
 

@@ -257,11 +257,16 @@ __device__ inline bool step_epilogue4(const DenseStepArgs &a, int i0, int r, boo
 
 // Energy terms of Eq. (h) for four consecutive spins of trajectory r:
 // sum_e [ -(D_0 T_0 + w D_1 T_1) + g_i D_0 ] in FP64 (T: raw GEMM sums of
-// J D; w = im_weight).
-template <bool CPLX>
+// J D; w = im_weight).  SIGN: psi_in holds the amplitudes, D_0 is their sign
+// (sign(+-0) = +1).
+template <bool CPLX, bool SIGN = false>
 __device__ inline double energy_terms4(const DenseStepArgs &a, int i0, int r, f32x4 tr, f32x4 ti) {
     const long long idx = (long long)r * a.Np + i0;
-    const f32x4 d0 = *reinterpret_cast<const f32x4 *>(a.psi_in + idx);
+    f32x4 d0 = *reinterpret_cast<const f32x4 *>(a.psi_in + idx);
+    if constexpr (SIGN) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d0[e] = d0[e] < 0.0f ? -1.0f : 1.0f;
+    }
     const f32x4 gg = *reinterpret_cast<const f32x4 *>(a.g + i0);
     f32x4 d1 = {0.f, 0.f, 0.f, 0.f};
     if (CPLX) d1 = *reinterpret_cast<const f32x4 *>(a.psi_in + a.plane_stride + idx);

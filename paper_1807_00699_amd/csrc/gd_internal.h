@@ -84,6 +84,13 @@ hipError_t launch_tile_couplings(const float *J, const void *J8, void *out, int 
 hipError_t launch_split_step(const DenseConfig &cfg, bool complex_mode, int mode, bool j_fp8,
                              const DenseStepArgs &a, hipStream_t st);
 
+// Energies of the signs of the amplitudes psi_in = B (one plane), J in FP8 from
+// launch_tile_couplings: partial[row tile][r], row tiles of
+// sign_energy_row_tile.  The sums are exact when the couplings are integers
+// and every row of |J| sums to less than 2^24.
+int sign_energy_row_tile(int Np, int R);
+hipError_t launch_sign_energy(const DenseStepArgs &a, hipStream_t st);
+
 // Reduced-precision variants (gd_dense_lp.hip): BF16/FP16 operands, FP32
 // accumulation; J either in the operand type or FP8 E4M3 (j_fp8).
 int dense_lp_config_count();
@@ -194,7 +201,7 @@ enum Readout {
 // 3/4 for q = 3 and 6 (the second plane then holds sin / (sqrt(3)/2) in
 // {0, +-1}, exact), 1 otherwise
 float clock_im_weight(int q);
-// Discretised state planes D (and its operand copy), zero outside n x R.
+// Discretised state planes D (null to skip) and their operand copy, zero outside n x R.
 // Optional outputs (null to skip): spins8 [R][n] int8, angle [R][n] float in
 // [0, 2pi) of the discretised state, states [R][n] int32 (RO_CLOCK).
 // flags[r] set on NaN.

@@ -31,8 +31,10 @@
 namespace gd {
 namespace split {
 
-// Storage of J: FP8 (E4M3, exact) or its three BF16 pieces
-enum JKind : int { J_FP8 = 0, J_PIECES = 1 };
+// Storage of J: FP8 (E4M3, exact) or its three BF16 pieces; J_FP8_SIGN: FP8
+// couplings against the signs of the amplitudes (energies of Ising readouts),
+// one product
+enum JKind : int { J_FP8 = 0, J_PIECES = 1, J_FP8_SIGN = 2 };
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -67,6 +69,18 @@ __device__ inline void split8(const f32x4 &lo, const f32x4 &hi, u32x4 &p0, u32x4
         p1[q] = w1;
         p2[q] = __builtin_bit_cast(unsigned int, __builtin_convertvector(f32x2{sa, sb}, bf16x2));
     }
+}
+
+// the signs (+-1 as BF16, sign(+-0) = +1) of eight consecutive values
+__device__ inline u32x4 sign8(const f32x4 &lo, const f32x4 &hi) {
+    u32x4 p;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float a = q < 2 ? lo[2 * q] : hi[2 * q - 4];
+        const float b = q < 2 ? lo[2 * q + 1] : hi[2 * q - 3];
+        p[q] = (a < 0.0f ? 0xBF80u : 0x3F80u) | (b < 0.0f ? 0xBF800000u : 0x3F800000u);
+    }
+    return p;
 }
 
 // eight FP8 (E4M3) values in two dwords -> eight BF16 values (exact)
@@ -117,7 +131,8 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
     constexpr int NWG = WM * WN, NT = 64 * NWG * KS;
     constexpr int TM = BM / WM, TN = BN / WN, MB = TM / 32, NB = TN / 32;
     constexpr int PL = CPLX ? 2 : 1, TRAJ = BN / PL, TRW = TN / PL;   // trajectories per tile / wave column
-    constexpr bool J8 = JK == J_FP8;
+    constexpr bool J8 = JK != J_PIECES, SIGN = JK == J_FP8_SIGN;
+    static_assert(!SIGN || (MODE == MODE_ENERGY && !CPLX), "signs: energies of one plane");
     constexpr int NSL = BK / 16;                                      // 16-wide K slices per chunk
     constexpr int RB = 4 * BK, TILEB = BN * RB, NI = TILEB / 1024;    // bytes per LDS row; 1 KiB copies per chunk
     constexpr int NCW = NI / NWG;                                     // copies per wave and chunk
@@ -212,7 +227,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
 
     // the products of the smaller pieces have accumulators of their own where
     // those fit: the large ones then add to sums of their own size only
-    constexpr bool LOWACC = MB * NB <= (J8 ? 4 : 2);
+    constexpr bool LOWACC = !SIGN && MB * NB <= (J8 ? 4 : 2);
     // split couplings in 32 x 32 tiles: the large products of odd slices too
     constexpr bool ODDACC = !J8 && MB * NB == 1;
     f32x16 acc[MB][NB], low[LOWACC ? MB : 1][LOWACC ? NB : 1], odd;
@@ -279,21 +294,26 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
                 if (sl + 1 < NSL) lread(sl + 1, set ^ 1);
                 u32x4 x0[NB], x1[NB], x2[NB];
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) split8(xr[set][nb][0], xr[set][nb][1], x0[nb], x1[nb], x2[nb]);
+                for (int nb = 0; nb < NB; ++nb) {
+                    if constexpr (SIGN) x0[nb] = sign8(xr[set][nb][0], xr[set][nb][1]);
+                    else split8(xr[set][nb][0], xr[set][nb][1], x0[nb], x1[nb], x2[nb]);
+                }
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb) {
                     if constexpr (J8) {
                         const u32x4 w = jw[JS][mb][sl / 2];
                         const u32x4 j0 = set == 0 ? widen8(w[0], w[1]) : widen8(w[2], w[3]);
+                        if constexpr (!SIGN) {
 #pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) {
-                            f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
-                            lo = mfma(j0, x2[nb], lo);
-                        }
+                            for (int nb = 0; nb < NB; ++nb) {
+                                f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
+                                lo = mfma(j0, x2[nb], lo);
+                            }
 #pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) {
-                            f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
-                            lo = mfma(j0, x1[nb], lo);
+                            for (int nb = 0; nb < NB; ++nb) {
+                                f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
+                                lo = mfma(j0, x1[nb], lo);
+                            }
                         }
 #pragma unroll
                         for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma(j0, x0[nb], acc[mb][nb]);
@@ -388,7 +408,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
                 if constexpr (MODE == MODE_ENERGY) {
                     // rows past the tile's end add nothing; the row groups of
                     // one trajectory are consecutive lanes
-                    double e = inside ? energy_terms4<CPLX>(a, i0, r, cr, ci) : 0.0;
+                    double e = inside ? energy_terms4<CPLX, SIGN>(a, i0, r, cr, ci) : 0.0;
 #pragma unroll
                     for (int m = RG / 2; m >= 1; m >>= 1) e += __shfl_xor(e, m);
                     if (row == 0 && r < a.R) a.partial[(long long)mt * a.Rp + r] = e;
@@ -417,6 +437,15 @@ hipError_t launch_modes(int mode, const DenseStepArgs &a, hipStream_t st) {
     default: return hipErrorInvalidValue;
     }
 #undef GD_LAUNCH
+    return hipGetLastError();
+}
+
+template <int BM, int BN, int BK, int WM, int WN, int KS, int JD, bool CPLX, int JK>
+hipError_t launch_energy(const DenseStepArgs &a, hipStream_t st) {
+    constexpr int TRAJ = CPLX ? BN / 2 : BN;
+    if (a.Np % BK || a.Np % 4 || a.R < 1 || a.R > a.Rp) return hipErrorInvalidValue;
+    const dim3 grid(((a.Np + BM - 1) / BM) * ((a.R + TRAJ - 1) / TRAJ));
+    dense_step_split<BM, BN, BK, WM, WN, KS, JD, CPLX, MODE_ENERGY, JK><<<grid, 64 * WM * WN * KS, 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -460,6 +489,15 @@ hipError_t launch_modes(int mode, const DenseStepArgs &a, hipStream_t st) {
     X(14, 64, 32, 32, 1, 1, 8, 1)     \
     X(15, 64, 64, 32, 1, 2, 4, 1)
 
+// Tiles {BM, BN, BK, WM, WN, KS, JD} of the sign energies.  One product leaves
+// a third of the matrix work of a step: N = R = 4096 is bound by the conversion
+// and the LDS reads around it.
+#define GD_SPLIT_SIGN_VARIANTS(X)     \
+    X(0, 32, 32, 32, 1, 1, 4, 4)      \
+    X(1, 64, 64, 32, 1, 1, 4, 2)      \
+    X(2, 128, 128, 32, 2, 2, 2, 2)    \
+    X(3, 256, 256, 32, 2, 4, 1, 2)
+
 }  // namespace split
 
 // launchers of the FP8-coupling and split-coupling instantiations, real and
@@ -467,6 +505,7 @@ hipError_t launch_modes(int mode, const DenseStepArgs &a, hipStream_t st) {
 hipError_t launch_split_j8_re(int idx, int mode, const DenseStepArgs &a, hipStream_t st);
 hipError_t launch_split_j8_cx(int idx, int mode, const DenseStepArgs &a, hipStream_t st);
 hipError_t launch_split_j3_re(int idx, int mode, const DenseStepArgs &a, hipStream_t st);
+hipError_t launch_split_sign(int idx, const DenseStepArgs &a, hipStream_t st);
 hipError_t launch_split_j3_cx(int idx, int mode, const DenseStepArgs &a, hipStream_t st);
 
 }  // namespace gd

@@ -74,4 +74,17 @@ hipError_t launch_split_step(const DenseConfig &cfg, bool complex_mode, int mode
     return complex_mode ? launch_split_j3_cx(idx, mode, a, st) : launch_split_j3_re(idx, mode, a, st);
 }
 
+int sign_energy_row_tile(int Np, int R) {
+    // the largest tile with a workgroup for every CU
+    constexpr int kTile[3] = {256, 128, 64};
+    for (const int t : kTile)
+        if ((long long)((Np + t - 1) / t) * ((R + t - 1) / t) >= 256) return t;
+    return 32;
+}
+
+hipError_t launch_sign_energy(const DenseStepArgs &a, hipStream_t st) {
+    const int t = sign_energy_row_tile(a.Np, a.R);
+    return launch_split_sign(t == 256 ? 3 : t == 128 ? 2 : t == 64 ? 1 : 0, a, st);
+}
+
 }  // namespace gd

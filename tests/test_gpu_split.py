@@ -54,3 +54,35 @@ def test_every_variant_one_step_at_tile_edges(monkeypatch, n, R, model, coupling
             assert np.array_equal(E, Ed), cid
         else:
             assert np.allclose(E, Ed, rtol=0, atol=2e-5 * np.abs(J64).sum() / n**0.5), cid
+
+
+@pytest.mark.parametrize("model,prec", [(gd.GD_ISING, gd.GD_PREC_FP32), (gd.GD_ISING, gd.GD_PREC_BF16),
+                                        (gd.GD_ISING_COMPLEX, gd.GD_PREC_FP32)])
+@pytest.mark.parametrize("n,R", [(2, 1), (33, 5), (65, 130), (320, 31), (1100, 1200)])
+def test_sign_energies_exact(n, R, model, prec):
+    """Energies from the signs of the amplitudes (FP8-stored couplings), at the
+    edges of the tiles: exactly sum_i -s_i (J s)_i + g_i s_i in integers for
+    integer couplings (up to 448 in magnitude) and fields, +0, -0 and
+    subnormal amplitudes reading as +1, -1 where negative; couplings in halves
+    take the FP64 re-score: 1e-12 of sum |J| there."""
+    rng = np.random.default_rng([n, R, 9])
+    s = np.where(rng.random((R, n)) < 0.5, -1.0, 1.0)
+    amp = (s * rng.choice([1.0, 0.25, 1e-30, 1e-41], (R, n))).astype(np.float32)
+    zero = rng.random((R, n)) < 0.1
+    amp[zero] = np.where(s[zero] < 0, -0.0, 0.0)
+    s = np.where(amp < 0, -1.0, 1.0)
+    psi = amp if model == gd.GD_ISING else np.stack([amp, rng.uniform(-1, 1, amp.shape).astype(np.float32)], -1)
+    for half in (False, True):
+        vals = np.array([-448, -208, -9, -3, -1, 0, 1, 2, 10, 44]) if not half else np.array([-1.5, -1.0, 0.0, 0.5, 2.0])
+        J = I.sym_from_upper(rng.choice(vals, (n, n)))
+        g = rng.integers(-3, 4, n).astype(np.float32)
+        J64 = J.astype(np.float64)
+        want = -np.einsum("ri,ri->r", s, s @ J64) + s @ g.astype(np.float64)
+        with gd.Solver(J, g, model=model, precision=prec) as S:
+            S.set_state(psi, np.zeros((R, n), np.float32))
+            E, b = S.energy()
+            Ed, bd = S.energy(device_path=True)
+        tol = 1e-12 * np.abs(J64).sum()
+        assert np.all(np.abs(E - want) <= (tol if half else 0.0))
+        if not half:
+            assert np.array_equal(Ed, want) and b == bd == int(np.argmin(want))
