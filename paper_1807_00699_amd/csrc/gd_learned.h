@@ -26,15 +26,14 @@ struct MlpTrainArgs {
     float *params, *mom, *vel;     // [kMlpNParam]
     const float *X;                // [M][F]
     const float *labels;           // [M] +-1
-    const int *seg;                // [K+1] instance boundaries
-    const int *spin_inst;          // [M] instance of each row
+    const int *seg;                // [K+1] instance boundaries (pinned host memory)
+    float *target;                 // [M] sigma_k s_i of each row
     int M;
     float *out;                    // [M][2]
-    float *sigma;                  // [K]
     float *partial;                // [nparts][kMlpNParam] gradient partials of the training workgroups
     double *loss_part;             // [nparts] their loss partials
-    float *grad_out;               // [kMlpNParam] (nullable)
-    double *loss;                  // [1]
+    float *grad_out;               // [kMlpNParam] (nullable; may be pinned host memory)
+    double *loss;                  // [1] (pinned host memory)
 };
 
 struct ProposeArgs {

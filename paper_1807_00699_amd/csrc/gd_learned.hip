@@ -482,21 +482,26 @@ __global__ void __launch_bounds__(MFT) mlp_forward_mfma_k(const float *__restric
     }
 }
 
-// per instance: sigma_k (flip alignment) and loss sums
+// per instance: sigma_k (flip alignment), then the targets sigma_k s_i of its
+// rows, so that the training kernel reads one number per row
 __global__ void __launch_bounds__(256) mlp_segment_k(const float *__restrict__ out, const float *__restrict__ lab,
-                                                    const int *__restrict__ seg, float *__restrict__ sigma,
-                                                    double *__restrict__ seg_loss) {
+                                                    const int *__restrict__ seg, float *__restrict__ target) {
     __shared__ double red[4 * 2];
+    __shared__ float sg;
     const int k = blockIdx.x;
+    const int i0 = seg[k], i1 = seg[k + 1];
     double v[2] = {0.0, 0.0};
-    for (int i = seg[k] + threadIdx.x; i < seg[k + 1]; i += 256) {
+    for (int i = i0 + threadIdx.x; i < i1; i += 256) {
         const double m = tanh((double)out[2 * i]);
         const double s = lab[i];
         v[0] += (m - s) * (m - s);
         v[1] += (m + s) * (m + s);
     }
     block_sum<2>(v, red);
-    if (threadIdx.x == 0) sigma[k] = v[0] <= v[1] ? 1.0f : -1.0f;
+    if (threadIdx.x == 0) sg = v[0] <= v[1] ? 1.0f : -1.0f;
+    __syncthreads();
+    const float sigma = sg;
+    for (int i = i0 + threadIdx.x; i < i1; i += 256) target[i] = sigma * lab[i];
 }
 
 // Training step on the matrix cores (v_mfma_f32_32x32x2_f32, FP32 products
@@ -595,7 +600,7 @@ __device__ __forceinline__ void mlp_mfma32(const MlpTrainArgs &a, float *smem) {
         // the spin's target sigma_k s_i, loaded before the products
         float tg = 0.0f;
         if constexpr (TRAIN)
-            if (ok) tg = a.sigma[a.spin_inst[m]] * a.labels[m];
+            if (ok) tg = a.target[m];
         f32x16_t z1[2], z2[2];
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
@@ -904,7 +909,7 @@ hipError_t launch_mlp_train_step(const MlpTrainArgs &a, int K, int nparts, float
     const int ntiles = (a.M + 31) / 32;
     const int gw = (ntiles + TT / 64 - 1) / (TT / 64);
     mlp_forward_mfma32_k<<<std::min(gw, 2048), TT, kFwdLds, st>>>(a);
-    mlp_segment_k<<<K, 256, 0, st>>>(a.out, a.labels, a.seg, a.sigma, nullptr);
+    mlp_segment_k<<<K, 256, 0, st>>>(a.out, a.labels, a.seg, a.target);
     const int np = std::max(1, std::min(nparts, gw));
     mlp_train_mfma_k<<<np, TT, kTrainLds, st>>>(a);
     mlp_adam_k<<<(NPAR + AP - 1) / AP + 1, AT, 0, st>>>(a, np, lr, step);

@@ -26,13 +26,19 @@ struct gd_mlp {
     int step = 0;
     // workspace for M rows
     int cap = 0;
-    float *out = nullptr, *X = nullptr, *labels = nullptr;
-    int *spin_inst = nullptr;
+    float *out = nullptr, *X = nullptr, *labels = nullptr, *target = nullptr;
+    float *partial = nullptr;
+    double *loss_part = nullptr;
+    // what passes between host and kernels in a training step, in pinned
+    // memory that the kernels read and write themselves (a step waits for its
+    // kernels before it returns)
+    struct Pinned {
+        double loss;
+        float grad[kMlpNParam];
+    };
+    Pinned *pin = nullptr;
     int capK = 0;
-    float *sigma = nullptr;
-    int *seg = nullptr;
-    float *partial = nullptr, *grad = nullptr;
-    double *loss_part = nullptr, *loss = nullptr;
+    int *seg = nullptr;            // pinned
 };
 
 namespace {
@@ -56,11 +62,10 @@ hipError_t dm(T **p, size_t n) {
 }
 
 void free_ws(gd_mlp *m) {
-    void *ps[] = {m->out, m->X, m->labels, m->spin_inst};
+    void *ps[] = {m->out, m->X, m->labels, m->target};
     for (void *p : ps)
         if (p) (void)hipFree(p);
-    m->out = m->X = m->labels = nullptr;
-    m->spin_inst = nullptr;
+    m->out = m->X = m->labels = m->target = nullptr;
     m->cap = 0;
 }
 
@@ -68,20 +73,23 @@ int ensure_ws(gd_mlp *m, int M, int K) {
     if (M > m->cap) {
         free_ws(m);
         if (dm(&m->out, (size_t)M * 2) || dm(&m->X, (size_t)M * kMlpF) || dm(&m->labels, M) ||
-            dm(&m->spin_inst, M)) {
+            dm(&m->target, M)) {
             free_ws(m);
             return gd_fail(GD_E_OOM, "MLP workspace allocation failed");
         }
         m->cap = M;
     }
-    if (K + 1 > m->capK) {
-        if (m->sigma) (void)hipFree(m->sigma);
-        if (m->seg) (void)hipFree(m->seg);
-        m->sigma = nullptr;
+    if (K > 0 && K + 1 > m->capK) {
+        if (m->seg) (void)hipHostFree(m->seg);
         m->seg = nullptr;
-        if (dm(&m->sigma, K + 1) || dm(&m->seg, K + 1)) return gd_fail(GD_E_OOM, "MLP workspace allocation failed");
+        m->capK = 0;
+        if (hipHostMalloc(reinterpret_cast<void **>(&m->seg), (size_t)(K + 1) * sizeof(int)) != hipSuccess)
+            return gd_fail(GD_E_OOM, "MLP workspace allocation failed");
         m->capK = K + 1;
     }
+    if (K > 0 && !m->pin &&
+        hipHostMalloc(reinterpret_cast<void **>(&m->pin), sizeof(gd_mlp::Pinned)) != hipSuccess)
+        return gd_fail(GD_E_OOM, "MLP workspace allocation failed");
     return GD_OK;
 }
 
@@ -106,6 +114,22 @@ void init_params(std::vector<float> &p, uint64_t seed) {
         }
 }
 
+// `count` floats at p lie inside an allocation of the current device
+bool device_floats(const float *p, size_t count) {
+    hipPointerAttribute_t at{};
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    int dev = -1;
+    if (reinterpret_cast<uintptr_t>(p) % 4 || hipGetDevice(&dev) != hipSuccess ||
+        hipPointerGetAttributes(&at, p) != hipSuccess || at.type != hipMemoryTypeDevice || at.device != dev ||
+        hipMemGetAddressRange(&base, &size, const_cast<float *>(p)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const uintptr_t b = reinterpret_cast<uintptr_t>(base), q = reinterpret_cast<uintptr_t>(p);
+    return q >= b && q - b <= size && count * 4 <= size - (q - b);
+}
+
 hipMemcpyKind kind_in(const gd_mlp *m) {
     return (m->flags & GD_F_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
 }
@@ -121,8 +145,7 @@ int gd_mlp_create(gd_mlp **out, const float *params, uint64_t seed, uint32_t fla
     if (!m) return gd_fail(GD_E_OOM, "host allocation failed");
     m->flags = flags;
     if (dm(&m->params, kMlpNParam) || dm(&m->mom, kMlpNParam) || dm(&m->vel, kMlpNParam) ||
-        dm(&m->partial, (size_t)kParts * kMlpNParam) || dm(&m->loss_part, kParts) || dm(&m->grad, kMlpNParam) ||
-        dm(&m->loss, 1)) {
+        dm(&m->partial, (size_t)kParts * kMlpNParam) || dm(&m->loss_part, kParts)) {
         gd_mlp_destroy(m);
         return gd_fail(GD_E_OOM, "MLP allocation failed");
     }
@@ -151,9 +174,11 @@ void gd_mlp_destroy(gd_mlp *m) {
     if (!m) return;
     if (m->stream) (void)hipStreamSynchronize(m->stream);
     free_ws(m);
-    void *ps[] = {m->params, m->mom, m->vel, m->partial, m->grad, m->loss_part, m->loss, m->sigma, m->seg};
+    void *ps[] = {m->params, m->mom, m->vel, m->partial, m->loss_part};
     for (void *p : ps)
         if (p) (void)hipFree(p);
+    if (m->seg) (void)hipHostFree(m->seg);
+    if (m->pin) (void)hipHostFree(m->pin);
     if (m->stream) (void)hipStreamDestroy(m->stream);
     delete m;
 }
@@ -207,38 +232,42 @@ int gd_mlp_train_step(gd_mlp *m, int32_t M, const float *X, const float *labels,
     if (!m || !X || !labels || !seg || M < 1 || K < 1 || !(lr >= 0.0f))
         return gd_fail(GD_E_INVALID_ARG, "bad argument");
     if (seg[0] != 0 || seg[K] != M) return gd_fail(GD_E_INVALID_ARG, "seg must run from 0 to M");
-    std::vector<int> inst((size_t)M);
-    for (int k = 0; k < K; ++k) {
+    for (int k = 0; k < K; ++k)
         if (seg[k + 1] <= seg[k]) return gd_fail(GD_E_INVALID_ARG, "empty or decreasing segment");
-        for (int i = seg[k]; i < seg[k + 1]; ++i) inst[i] = k;
-    }
     int rc = ensure_ws(m, M, K);
     if (rc != GD_OK) return rc;
-    GD_TRY(hipMemcpyAsync(m->X, X, (size_t)M * kMlpF * 4, kind_in(m), m->stream));
-    GD_TRY(hipMemcpyAsync(m->labels, labels, (size_t)M * 4, kind_in(m), m->stream));
-    GD_TRY(hipMemcpyAsync(m->seg, seg, (size_t)(K + 1) * 4, hipMemcpyHostToDevice, m->stream));
-    GD_TRY(hipMemcpyAsync(m->spin_inst, inst.data(), (size_t)M * 4, hipMemcpyHostToDevice, m->stream));
+    // rows in device memory are read where they are (anything that does not
+    // check out goes through a copy, which refuses what is not valid)
+    const bool dev = (m->flags & GD_F_DEVICE_PTRS) != 0;
+    const float *Xd = X, *Ld = labels;
+    if (!dev || !device_floats(X, (size_t)M * kMlpF)) {
+        GD_TRY(hipMemcpyAsync(m->X, X, (size_t)M * kMlpF * 4, kind_in(m), m->stream));
+        Xd = m->X;
+    }
+    if (!dev || !device_floats(labels, (size_t)M)) {
+        GD_TRY(hipMemcpyAsync(m->labels, labels, (size_t)M * 4, kind_in(m), m->stream));
+        Ld = m->labels;
+    }
+    std::memcpy(m->seg, seg, (size_t)(K + 1) * sizeof(int));
     if (lr > 0.0f) m->step += 1;
     MlpTrainArgs a{};
     a.params = m->params;
     a.mom = m->mom;
     a.vel = m->vel;
-    a.X = m->X;
-    a.labels = m->labels;
+    a.X = Xd;
+    a.labels = Ld;
     a.seg = m->seg;
-    a.spin_inst = m->spin_inst;
+    a.target = m->target;
     a.M = M;
     a.out = m->out;
-    a.sigma = m->sigma;
     a.partial = m->partial;
     a.loss_part = m->loss_part;
-    a.grad_out = m->grad;
-    a.loss = m->loss;
+    a.grad_out = grad ? m->pin->grad : nullptr;
+    a.loss = &m->pin->loss;
     GD_TRY(launch_mlp_train_step(a, K, kParts, lr, std::max(m->step, 1), m->stream));
-    double L = 0.0;
-    GD_TRY(hipMemcpyAsync(&L, m->loss, 8, hipMemcpyDeviceToHost, m->stream));
-    if (grad) GD_TRY(hipMemcpyAsync(grad, m->grad, kMlpNParam * 4, hipMemcpyDeviceToHost, m->stream));
     GD_TRY(hipStreamSynchronize(m->stream));
+    const double L = m->pin->loss;
+    if (grad) std::memcpy(grad, m->pin->grad, kMlpNParam * sizeof(float));
     if (loss) *loss = L;
     return GD_OK;
 }
