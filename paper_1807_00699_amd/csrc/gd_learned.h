@@ -49,7 +49,11 @@ struct ProposeArgs {
 };
 
 hipError_t launch_features(const FeatArgs &a, int K, hipStream_t st);
-hipError_t launch_mlp_forward(const float *params, const float *X, float *out, int M, bool fp16,
+// FP16 inference reads the network in its operand order: kMlpPackedBytes
+// written from the parameters by launch_mlp_pack
+constexpr size_t kMlpPackedBytes = 4 * 1024 + 8 * 1024 + 256 + 256 + 512 + 16;
+hipError_t launch_mlp_pack(const float *params, void *packed, hipStream_t st);
+hipError_t launch_mlp_forward(const float *params, const void *packed, const float *X, float *out, int M, bool fp16,
                               hipStream_t st);
 hipError_t launch_mlp_train_step(const MlpTrainArgs &a, int K, int nparts, float lr, int step,
                                  hipStream_t st);

@@ -357,29 +357,37 @@ __global__ void __launch_bounds__(MT) mlp_forward_k(const float *__restrict__ p,
 // hidden unit 8 (2 s + j / 4) + 4 h + j mod 4 of the block (every product is
 // still summed once).  The two outputs take the 32 hidden units of each lane
 // on the vector ALUs and add the other lane half.  The weight operands are
-// built once per workgroup in LDS in the lane order of the instruction.
+// packed in the lane order of the instruction and copied to LDS by every
+// workgroup.
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int MFT = 256;   // 4 waves
 
-__global__ void __launch_bounds__(MFT) mlp_forward_mfma_k(const float *__restrict__ p, const float *__restrict__ X,
-                                                         float *__restrict__ out, int M) {
+// The network in the order the inference kernel reads it, formed once per
+// parameter set (mlp_pack_k):
+// A1[rb][s][lane]: W1^T rows 32 rb + l % 32, features 16 s + 8 h + j
+// A2[rb][ib][s][lane]: W2^T rows 32 rb + l % 32, hidden 32 ib + 8 (2 s + j / 4) + 4 h + j % 4
+// B1, B2, W3: [rb][h][4q + e](...)
+struct __attribute__((aligned(16))) MlpPacked {
+    f16x8_t A1[2][2][64], A2[2][2][2][64];
+    float B1[2][2][16], B2[2][2][16], W3[2][2][16][2];
+    float B3[4];
+};
+static_assert(sizeof(MlpPacked) == kMlpPackedBytes && sizeof(MlpPacked) % 16 == 0, "packed network");
+
+__global__ void __launch_bounds__(MFT) mlp_pack_k(const float *__restrict__ p, MlpPacked *__restrict__ o) {
     static_assert(H == 64 && F <= 32 && NO == 2, "layer shapes of the MFMA forward");
-    // A1[rb][s][lane]: W1^T rows 32 rb + l % 32, features 16 s + 8 h + j
-    // A2[rb][ib][s][lane]: W2^T rows 32 rb + l % 32, hidden 32 ib + 8 (2 s + j / 4) + 4 h + j % 4
-    __shared__ f16x8_t A1[2][2][64], A2[2][2][2][64];
-    __shared__ float B1s[2][2][16], B2s[2][2][16], W3s[2][2][16][2];   // [rb][h][4q + e](...)
-    const int tid = threadIdx.x;
-    for (int q = tid; q < 2 * 2 * 64; q += MFT) {
+    const int tid = blockIdx.x * MFT + threadIdx.x, nt = gridDim.x * MFT;
+    for (int q = tid; q < 2 * 2 * 64; q += nt) {
         const int rb = q / 128, st = (q / 64) % 2, l = q % 64, h = l / 32, row = 32 * rb + l % 32;
         f16x8_t v;
         for (int j = 0; j < 8; ++j) {
             const int f = 16 * st + 8 * h + j;
             v[j] = (_Float16)(f < F ? p[OFF_W1 + f * H + row] : 0.0f);
         }
-        A1[rb][st][l] = v;
+        o->A1[rb][st][l] = v;
     }
-    for (int q = tid; q < 2 * 2 * 2 * 64; q += MFT) {
+    for (int q = tid; q < 2 * 2 * 2 * 64; q += nt) {
         const int rb = q / 256, ib = (q / 128) % 2, st = (q / 64) % 2, l = q % 64, h = l / 32;
         const int row = 32 * rb + l % 32;
         f16x8_t v;
@@ -387,24 +395,34 @@ __global__ void __launch_bounds__(MFT) mlp_forward_mfma_k(const float *__restric
             const int hin = 32 * ib + 8 * (2 * st + j / 4) + 4 * h + j % 4;
             v[j] = (_Float16)p[OFF_W2 + hin * H + row];
         }
-        A2[rb][ib][st][l] = v;
+        o->A2[rb][ib][st][l] = v;
     }
-    for (int q = tid; q < 2 * 2 * 16; q += MFT) {
+    for (int q = tid; q < 2 * 2 * 16; q += nt) {
         const int rb = q / 32, h = (q / 16) % 2, k = q % 16;
         const int row = 32 * rb + 8 * (k / 4) + 4 * h + k % 4;
-        B1s[rb][h][k] = p[OFF_B1 + row];
-        B2s[rb][h][k] = p[OFF_B2 + row];
-        W3s[rb][h][k][0] = p[OFF_W3 + row * NO];
-        W3s[rb][h][k][1] = p[OFF_W3 + row * NO + 1];
+        o->B1[rb][h][k] = p[OFF_B1 + row];
+        o->B2[rb][h][k] = p[OFF_B2 + row];
+        o->W3[rb][h][k][0] = p[OFF_W3 + row * NO];
+        o->W3[rb][h][k][1] = p[OFF_W3 + row * NO + 1];
     }
-    __syncthreads();
+    if (tid < 4) o->B3[tid] = tid < NO ? p[OFF_B3 + tid] : 0.0f;
+}
+
+// Two waves per SIMD with the weights in registers.  What bounds it is the
+// features in flight: 324 731 rows 10.9 us (28.6 MB, 2.6 TB/s); 15.2 us with
+// 257 registers, which left one wave per SIMD, one tile ahead, the operands
+// converted by every workgroup.  Four waves with the weights re-read from LDS:
+// 13.1 us.
+__global__ void __launch_bounds__(MFT, 2) mlp_forward_mfma_k(const MlpPacked *__restrict__ p, const float *__restrict__ X,
+                                                            float *__restrict__ out, int M) {
+    __shared__ MlpPacked sw;
+    const int tid = threadIdx.x;
     const int lane = tid & 63, h = lane >> 5, l32 = lane & 31;
-    const float b30 = p[OFF_B3], b31 = p[OFF_B3 + 1];
     const int ntiles = (M + 31) / 32;
     const int stride = gridDim.x * (MFT / 64);
     // the feature words of a tile (rows of F = 20 floats are 16-byte aligned:
-    // four-float loads, zeros past feature 19); the next tile's are loaded
-    // while the current one is multiplied
+    // four-float loads, zeros past feature 19); loaded two tiles ahead, the
+    // first two before the weights
     static_assert(F == 20, "feature row of five 16-byte words");
     const float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f);
     auto load_x = [&](int t, float4 &w0, float4 &w1, float4 &w2) {
@@ -416,13 +434,18 @@ __global__ void __launch_bounds__(MFT) mlp_forward_mfma_k(const float *__restric
         w2 = ok && h == 0 ? xr[4] : z4;
     };
     int t = blockIdx.x * (MFT / 64) + (tid >> 6);
-    float4 c0, c1, c2;
+    float4 c0, c1, c2, d0, d1, d2;
     load_x(t, c0, c1, c2);
+    load_x(t + stride, d0, d1, d2);
+    for (int q = tid; q < int(sizeof(MlpPacked) / 16); q += MFT)
+        reinterpret_cast<float4 *>(&sw)[q] = reinterpret_cast<const float4 *>(p)[q];
+    __syncthreads();
+    const float b30 = sw.B3[0], b31 = sw.B3[1];
     for (; t < ntiles; t += stride) {
         const long long m = (long long)t * 32 + l32;
         const bool ok = m < M;
         float4 n0, n1, n2;
-        load_x(t + stride, n0, n1, n2);
+        load_x(t + 2 * stride, n0, n1, n2);
         // B1: features 16 s + 8 h + j of spin m
         f16x8_t xb[2];
         {
@@ -434,17 +457,21 @@ __global__ void __launch_bounds__(MFT) mlp_forward_mfma_k(const float *__restric
                 xb[1][j] = (_Float16)(j < 4 ? v1[j] : 0.0f);
             }
         }
-        c0 = n0;
-        c1 = n1;
-        c2 = n2;
+        c0 = d0;
+        c1 = d1;
+        c2 = d2;
+        d0 = n0;
+        d1 = n1;
+        d2 = n2;
+        const MlpPacked &n = sw;
         f32x16_t z1[2], z2[2];
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) z1[rb][k] = B1s[rb][h][k];
+            for (int k = 0; k < 16; ++k) z1[rb][k] = n.B1[rb][h][k];
 #pragma unroll
             for (int st = 0; st < 2; ++st)
-                z1[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A1[rb][st][lane], xb[st], z1[rb], 0, 0, 0);
+                z1[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(n.A1[rb][st][lane], xb[st], z1[rb], 0, 0, 0);
         }
         // relu(Z1)^T as the B operand of layer 2, in the permuted K order
         f16x8_t hb[2][2];
@@ -457,12 +484,12 @@ __global__ void __launch_bounds__(MFT) mlp_forward_mfma_k(const float *__restric
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) z2[rb][k] = B2s[rb][h][k];
+            for (int k = 0; k < 16; ++k) z2[rb][k] = n.B2[rb][h][k];
 #pragma unroll
             for (int ib = 0; ib < 2; ++ib)
 #pragma unroll
                 for (int st = 0; st < 2; ++st)
-                    z2[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[rb][ib][st][lane], hb[ib][st], z2[rb], 0, 0, 0);
+                    z2[rb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(n.A2[rb][ib][st][lane], hb[ib][st], z2[rb], 0, 0, 0);
         }
         float o0 = 0.0f, o1 = 0.0f;
 #pragma unroll
@@ -470,8 +497,8 @@ __global__ void __launch_bounds__(MFT) mlp_forward_mfma_k(const float *__restric
 #pragma unroll
             for (int k = 0; k < 16; ++k) {
                 const float r = fmaxf(z2[rb][k], 0.0f);
-                o0 = fmaf(r, W3s[rb][h][k][0], o0);
-                o1 = fmaf(r, W3s[rb][h][k][1], o1);
+                o0 = fmaf(r, n.W3[rb][h][k][0], o0);
+                o1 = fmaf(r, n.W3[rb][h][k][1], o1);
             }
         o0 += __shfl_xor(o0, 32);
         o1 += __shfl_xor(o1, 32);
@@ -882,7 +909,12 @@ hipError_t launch_features(const FeatArgs &a, int K, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_mlp_forward(const float *params, const float *X, float *out, int M, bool fp16,
+hipError_t launch_mlp_pack(const float *params, void *packed, hipStream_t st) {
+    mlp_pack_k<<<4, MFT, 0, st>>>(params, static_cast<MlpPacked *>(packed));
+    return hipGetLastError();
+}
+
+hipError_t launch_mlp_forward(const float *params, const void *packed, const float *X, float *out, int M, bool fp16,
                               hipStream_t st) {
     if (M <= 0) return hipSuccess;
     const int g = (M + MT - 1) / MT;
@@ -890,10 +922,10 @@ hipError_t launch_mlp_forward(const float *params, const float *X, float *out, i
         // the feature rows are read as 16-byte words
         if (reinterpret_cast<uintptr_t>(X) % 16) return hipErrorInvalidValue;
         // one wave per 32 spins at a time; at most the workgroups that are
-        // resident at once (two per CU), so each builds the weight operands once
+        // resident at once (two per CU)
         const int tiles = (M + 31) / 32;
         const int gm = std::min((tiles + MFT / 64 - 1) / (MFT / 64), 512);
-        mlp_forward_mfma_k<<<gm, MFT, 0, st>>>(params, X, out, M);
+        mlp_forward_mfma_k<<<gm, MFT, 0, st>>>(static_cast<const MlpPacked *>(packed), X, out, M);
     } else {
         mlp_forward_k<<<g, MT, 0, st>>>(params, X, out, M);
     }
