@@ -98,6 +98,12 @@ KERNEL_SOURCES = {"dense_step_split": ("gd_split.h", "gd_epilogue.h"),
                   "gemv_step_k": ("gd_gemv.h", "gd_epilogue.h")}
 
 
+def coupling_kernel(config_id, precision):
+    """Kernel of a coupling variant: at reduced precision ids from 14 on are
+    those of gd_split.h."""
+    return "dense_step_split" if precision == "fp32" or config_id >= 14 else "dense_step_lp"
+
+
 def fp8_exact(J):
     """True when every coupling is exactly an OCP FP8 E4M3 value: the library
     then stores J in one byte per coupling for the kernels that stream J
@@ -782,15 +788,15 @@ def headline(args):
         flops_launch = 2.0 * n * n * R
         peak = fp32_matrix_peak(J) if prec == gd.GD_PREC_FP32 else PEAKS_TFLOPS["bf16"]
         achieved = flops_launch / avg_s / 1e12
+        kern = coupling_kernel(st.kernel_config, "fp32" if prec == gd.GD_PREC_FP32 else "bf16")
         legs[name] = {
             "value": n * R * K / el, "ms_per_step": el / K * 1e3, "dtype": dtype,
             "kernel_config": st.kernel_config, "best_energy": float(E[best]),
             "device_check_equals_fp64_rescore": bool(np.array_equal(E, Ed) and best == best_d),
             "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                          "frac": achieved / peak,
-                         "traffic": kernel_traffic(st.kernel_config, "dense_step_split" if prec == gd.GD_PREC_FP32
-                                                    else "dense_step_lp", "ising4096"),
-                         "kernel": "dense_step_split" if prec == gd.GD_PREC_FP32 else "dense_step_lp",
+                         "traffic": kernel_traffic(st.kernel_config, kern, "ising4096"),
+                         "kernel": kern,
                          "launches": int(launches), "avg_launch_us": avg_s * 1e6,
                          "flops_per_launch": flops_launch},
         }
@@ -1082,7 +1088,7 @@ def main():
                       "unit": "TFLOP/s", "frac": achieved / peak,
                       "traffic": (kernel_traffic(st.kernel_config, "dense_step_split")
                                   if args.workload == "xy1024" else None),
-                      "kernel": "dense_step_split" if prec_name == "fp32" else "dense_step_lp",
+                      "kernel": coupling_kernel(st.kernel_config, prec_name),
                       "launches": int(launches),
                       "avg_launch_us": avg_s * 1e6, "flops_per_launch": flops_launch}),
         "best_energy": float(E[best]),

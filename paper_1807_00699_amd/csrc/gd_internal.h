@@ -106,6 +106,11 @@ hipError_t launch_dense_step_lp(const DenseConfig &cfg, bool complex_mode, int m
 // 32, the row tile of its energy partials).
 constexpr int kGemvBase = 100;
 constexpr int kGemvMaxCols = 16;
+// reduced-precision variants of gd_split.h (FP8-stored couplings): ids kLpSplitBase + index
+constexpr int kLpSplitBase = 14;
+int split_lp_config_count();
+DenseConfig split_lp_config(bool complex_mode, int idx);
+hipError_t launch_split_lp(int idx, bool complex_mode, int mode, int op, const DenseStepArgs &a, hipStream_t st);
 // FP32 variants of gd_split.h with 32-column tiles competing there: ids kFewBase + index
 constexpr int kFewBase = 110;
 int gemv_config_count();

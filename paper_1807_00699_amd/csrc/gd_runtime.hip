@@ -170,7 +170,7 @@ struct gd_solver {
     // HBM every step and widen it exactly to FP32, in the FP32 kernels' order
     // (the same results bit for bit); GD_J8_COPY=0 keeps FP32 J only
     void *dJ8 = nullptr;
-    void *dJt = nullptr;       // FP32 solvers: J (FP8, or three BF16 pieces) as the split kernels read it
+    void *dJt = nullptr;       // J (FP8, or three BF16 pieces) as the split kernels read it
     float *dJs = nullptr;      // FP32 solvers with Np <= 128: J as the fused small-problem kernel reads it
     void *shadow[3] = {nullptr, nullptr, nullptr};   // operand copies of psi[k]
     void *shadowD = nullptr;   // operand copy of the discretised state
@@ -288,7 +288,8 @@ int alloc_state(gd_solver *s, int R) {
     // Euler steps at reduced precision multiply the operand copy, so they
     // update the FP32 amplitudes in place (psi[1] is psi[0]); the copies
     // alternate.  At N = R = 4096 that leaves 218 MB touched per step, within
-    // the 256 MiB of the last-level cache: 146 us per step (164 with two planes)
+    // the 256 MiB of the last-level cache: 126 us per step (two planes: 17 us more
+    // with the kernel of that time)
     const bool in_place = s->op != OP_F32 && s->integrator() == GD_EULER;
     for (int k = 0; k < npsi && rc == GD_OK; ++k) {
         if (in_place && k == 1) s->psi[1] = s->psi[0];
@@ -376,6 +377,10 @@ hipError_t launch_coupling(gd_solver *s, const DenseConfig &cfg, int mode, const
     if (s->op == OP_F32) {
         b.J = s->dJt;
         return launch_split_step(cfg, s->complex_mode(), mode, s->dJ8 != nullptr, b, s->stream);
+    }
+    if (cfg.id >= kLpSplitBase) {
+        b.J = s->dJt;
+        return launch_split_lp(cfg.id - kLpSplitBase, s->complex_mode(), mode, s->op, b, s->stream);
     }
     return launch_dense_step_lp(cfg, s->complex_mode(), mode, s->op, s->jfp8, b, s->stream);
 }
@@ -476,7 +481,8 @@ int enqueue_step(gd_solver *s, const DenseConfig &cfg, float dt_override, bool t
 // J in FP8, row-major, if this solver stores it so
 const void *couplings_fp8(const gd_solver *s) { return s->op == OP_F32 ? s->dJ8 : (s->jfp8 ? s->dJlp : nullptr); }
 
-// J in the order the split kernels read it, laid out once per solver
+// J in the order the split kernels read it, laid out once per solver (at
+// reduced precision FP8-stored couplings only)
 int tile_couplings(gd_solver *s) {
     const void *j8 = couplings_fp8(s);
     if (s->dJt || (s->op != OP_F32 && !j8)) return GD_OK;
@@ -523,7 +529,7 @@ int device_energies(gd_solver *s, int *ntiles) {
 int choose_config(gd_solver *s) {
     const bool cx = s->complex_mode();
     const bool lp = s->op != OP_F32;
-    const int nc = lp ? dense_lp_config_count() : split_config_count();
+    const int nc = lp ? kLpSplitBase + (s->jfp8 ? split_lp_config_count() : 0) : split_config_count();
     auto gemv_ok = [&](int k) {
         return !s->mod() && gemv_fits(k, s->Np, s->R, cx, s->op, s->jfp8 || s->dJ8 != nullptr);
     };
@@ -536,6 +542,7 @@ int choose_config(gd_solver *s) {
             return c;
         }
         if (id >= kGemvBase) return gemv_config(id - kGemvBase);
+        if (lp && id >= kLpSplitBase) return split_lp_config(cx, id - kLpSplitBase);
         return lp ? dense_lp_config(cx, id) : split_config(cx, s->dJ8 != nullptr, id);
     };
     auto fits = [&](int id) {
@@ -549,7 +556,7 @@ int choose_config(gd_solver *s) {
         }
         if (id >= kGemvBase) return gemv_ok(id - kGemvBase);
         if (id < 0 || id >= nc) return false;
-        return !lp || dense_lp_config_fits(cfg_of(id), s->Np, s->Rp);
+        return !lp || id >= kLpSplitBase || dense_lp_config_fits(cfg_of(id), s->Np, s->Rp);
     };
     // the fused kernel needs its own form of J; the coupling kernels' form is
     // laid out when they first run (energy checks outside a run, pinned variants)
@@ -559,7 +566,7 @@ int choose_config(gd_solver *s) {
         if (rc != GD_OK) return rc;
         GD_HIP(launch_small_couplings(s->dJ, s->dJs, s->Np, s->stream));
     }
-    if (!fused && !lp) {
+    if (!fused) {
         const int rc = tile_couplings(s);
         if (rc != GD_OK) return rc;
     }

@@ -14,6 +14,9 @@
 // second accumulator) [4.0e-7, 8.1e-7]; U[-10, 10] N = 1000 0.9-4.7e-7
 // [5.7e-7]; N(0, 1/N) N = 4096 0.12-1.0e-6 [1.15e-6].
 //
+// BF16 and FP16 operands (FP8 couplings) take one product; the amplitudes are
+// then the 16-bit copies that the previous step wrote.
+//
 // What bounds it: at N = R = 4096 the matrix cores.  One launch is 3 x 137
 // GFLOP; it takes 329 us (1.25 PFLOP/s; a large BF16 matrix product runs at
 // 1.28 on this card), against 1016 us on the FP32 matrix cores (135 TFLOP/s,
@@ -38,6 +41,7 @@ enum JKind : int { J_FP8 = 0, J_PIECES = 1, J_FP8_SIGN = 2 };
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
@@ -51,8 +55,8 @@ constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4); 
 // consecutive rows read at one logical slot then cover all 64 banks
 template <int ROWB>
 __device__ inline int row_swz(int row) {
-    static_assert(ROWB == 128 || ROWB == 256, "rows of 32 or 64 floats");
-    return ROWB == 128 ? (row >> 1) & 7 : row & 15;
+    static_assert(ROWB == 64 || ROWB == 128 || ROWB == 256, "rows of 4, 8 or 16 slots");
+    return ROWB == 64 ? (row >> 2) & 3 : ROWB == 128 ? (row >> 1) & 7 : row & 15;
 }
 
 // the three BF16 pieces of eight consecutive FP32 values
@@ -83,17 +87,32 @@ __device__ inline u32x4 sign8(const f32x4 &lo, const f32x4 &hi) {
     return p;
 }
 
-// eight FP8 (E4M3) values in two dwords -> eight BF16 values (exact)
+// eight FP8 (E4M3) values in two dwords -> eight BF16 or FP16 values (exact)
+template <int OPT>
 __device__ inline u32x4 widen8(unsigned int w0, unsigned int w1) {
-    return u32x4{__builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false)),
-                 __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, true)),
-                 __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, false)),
-                 __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, true))};
+    u32x4 r;
+    if constexpr (OPT == OP_F16) {
+        r[0] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, 1.0f, false));
+        r[1] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, 1.0f, true));
+        r[2] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, 1.0f, false));
+        r[3] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, 1.0f, true));
+    } else {
+        r[0] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, false));
+        r[1] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w0, 1.0f, true));
+        r[2] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, false));
+        r[3] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w1, 1.0f, true));
+    }
+    return r;
 }
 
+template <int OPT = OP_F32>
 __device__ inline f32x16 mfma(const u32x4 &a, const u32x4 &b, const f32x16 &c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
-                                                   0, 0, 0);
+    if constexpr (OPT == OP_F16)
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
+                                                      0);
+    else
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                       0, 0);
 }
 
 // Workgroup -> (row tile, column tile): one contiguous range of tiles per XCD
@@ -123,18 +142,23 @@ __device__ inline void tile_of(int b, int nblk, int n_mt, int n_ct, int &mt, int
 // is one contiguous KiB); through LDS, as the amplitudes, XY N = R = 1024 took
 // 39 us per stage and N = 800 7.7 us per step:
 //   J_FP8:    [Np / 32][Np / 32][lane][16 bytes], lane l holds row l % 32,
-//             bytes 8 s + e: k = 16 s + 8 (l / 32) + e of the 32-wide block;
+//             k = 16 (l / 32) .. + 15 of the 32-wide block: its first eight
+//             are operands of one slice, the others of the next;
 //   J_PIECES: [Np / 32][Np / 16][piece][lane][8 BF16], k = 8 (l / 32) + e.
-template <int BM, int BN, int BK, int WM, int WN, int KS, int JD, bool CPLX, int MODE, int JK>
+template <int BM, int BN, int BK, int WM, int WN, int KS, int JD, bool CPLX, int MODE, int JK,
+          int OPT = OP_F32>
 __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepArgs a) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the host pass has no buffer resources; it needs the kernel's stub only
     constexpr int NWG = WM * WN, NT = 64 * NWG * KS;
     constexpr int TM = BM / WM, TN = BN / WN, MB = TM / 32, NB = TN / 32;
     constexpr int PL = CPLX ? 2 : 1, TRAJ = BN / PL, TRW = TN / PL;   // trajectories per tile / wave column
-    constexpr bool J8 = JK != J_PIECES, SIGN = JK == J_FP8_SIGN;
-    static_assert(!SIGN || (MODE == MODE_ENERGY && !CPLX), "signs: energies of one plane");
     constexpr int NSL = BK / 16;                                      // 16-wide K slices per chunk
-    constexpr int RB = 4 * BK, TILEB = BN * RB, NI = TILEB / 1024;    // bytes per LDS row; 1 KiB copies per chunk
+    constexpr bool F32 = OPT == OP_F32;
+    constexpr bool J8 = JK != J_PIECES, SIGN = JK == J_FP8_SIGN;
+    static_assert(!SIGN || (MODE == MODE_ENERGY && !CPLX && F32), "signs: energies of one plane");
+    static_assert(F32 || J8, "16-bit operands: FP8 couplings");
+    constexpr int EB = F32 ? 4 : 2;                                   // bytes per amplitude of the operand
+    constexpr int RB = EB * BK, TILEB = BN * RB, NI = TILEB / 1024;   // bytes per LDS row; 1 KiB copies per chunk
     constexpr int NCW = NI / NWG;                                     // copies per wave and chunk
     constexpr int JPC = J8 ? NSL / 2 : 3 * NSL, NJ = MB * JPC;        // coupling loads per row block / wave and chunk
     static_assert(BK % 32 == 0 && NI % NWG == 0 && (NI / NWG) * NWG * 1024 == TILEB, "chunks of whole 32-wide blocks");
@@ -189,14 +213,14 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
 #pragma unroll
     for (int p = 0; p < PL; ++p)
         rsrc[p] = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<unsigned char *>(Bb + (p * a.plane_stride + r0 * Np) * 4), 0, -1, 0x00027000);
+            const_cast<unsigned char *>(Bb + (p * a.plane_stride + r0 * Np) * EB), 0, -1, 0x00027000);
     int voff[NCW];
 #pragma unroll
     for (int u = 0; u < NCW; ++u) {
         const int row = (wave + u * NWG) * RPC + lane / LPR;
         const int ls = (lane % LPR) ^ row_swz<RB>(row);
         const int tr = row / TN * TRW + row % TN % TRW;
-        voff[u] = min(tr, a.Rp - 1 - r0) * (a.Np * 4) + ls * 16;
+        voff[u] = min(tr, a.Rp - 1 - r0) * (a.Np * EB) + ls * 16;
     }
     unsigned char *gl = lds + grp * (JD + 1) * TILEB;
     auto copy_chunk = [&](int k0, int buf) {
@@ -205,7 +229,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
             const int j = wave + u * NWG;
             const bool im = CPLX && j * RPC % TN >= TRW;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(im ? rsrc[PL - 1] : rsrc[0], (lvoid_t *)(gl + buf * TILEB + j * 1024),
-                                                     16, voff[u], k0 * 4, 0, 0);
+                                                     16, voff[u], k0 * EB, 0, 0);
         }
     };
     // the couplings of each of this wave's row blocks (blocks past the matrix
@@ -227,7 +251,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
 
     // the products of the smaller pieces have accumulators of their own where
     // those fit: the large ones then add to sums of their own size only
-    constexpr bool LOWACC = !SIGN && MB * NB <= (J8 ? 4 : 2);
+    constexpr bool LOWACC = F32 && !SIGN && MB * NB <= (J8 ? 4 : 2);
     // split couplings in 32 x 32 tiles: the large products of odd slices too
     constexpr bool ODDACC = !J8 && MB * NB == 1;
     f32x16 acc[MB][NB], low[LOWACC ? MB : 1][LOWACC ? NB : 1], odd;
@@ -275,16 +299,19 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
         __asm__ __volatile__("" ::: "memory");
         if (!LAST || it * KS + grp < nk) {
             const unsigned char *Bt = gl + buf * TILEB;
-            f32x4 xr[2][NB][2];                        // raw amplitudes of one slice
+            // raw amplitudes of one slice: this lane's eight are k = 32 m + 16 h
+            // + 8 s on (FP8 couplings, slice s of block m) or 16 s + 8 h on
+            constexpr int NQ = F32 ? 2 : 1;            // 16-byte words
+            u32x4 xr[2][NB][NQ];
             auto lread = [&](int sl, int set) {
-                const int slot = 4 * sl + 2 * lh;
+                const int slot = NQ * (J8 ? (sl >> 1) * 4 + 2 * lh + (sl & 1) : 2 * sl + lh);
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                    for (int t = 0; t < 2; ++t) {
+                    for (int t = 0; t < NQ; ++t) {
                         const int row = wn * TN + nb * 32 + l32;
                         xr[set][nb][t] =
-                            *reinterpret_cast<const f32x4 *>(Bt + row * RB + (((slot + t) ^ row_swz<RB>(row)) * 16));
+                            *reinterpret_cast<const u32x4 *>(Bt + row * RB + (((slot + t) ^ row_swz<RB>(row)) * 16));
                     }
             };
             lread(0, 0);
@@ -295,15 +322,18 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
                 u32x4 x0[NB], x1[NB], x2[NB];
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
-                    if constexpr (SIGN) x0[nb] = sign8(xr[set][nb][0], xr[set][nb][1]);
-                    else split8(xr[set][nb][0], xr[set][nb][1], x0[nb], x1[nb], x2[nb]);
+                    const f32x4 lo = __builtin_bit_cast(f32x4, xr[set][nb][0]);
+                    const f32x4 hi = __builtin_bit_cast(f32x4, xr[set][nb][NQ - 1]);
+                    if constexpr (!F32) x0[nb] = xr[set][nb][0];
+                    else if constexpr (SIGN) x0[nb] = sign8(lo, hi);
+                    else split8(lo, hi, x0[nb], x1[nb], x2[nb]);
                 }
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb) {
                     if constexpr (J8) {
                         const u32x4 w = jw[JS][mb][sl / 2];
-                        const u32x4 j0 = set == 0 ? widen8(w[0], w[1]) : widen8(w[2], w[3]);
-                        if constexpr (!SIGN) {
+                        const u32x4 j0 = set == 0 ? widen8<OPT>(w[0], w[1]) : widen8<OPT>(w[2], w[3]);
+                        if constexpr (F32 && !SIGN) {
 #pragma unroll
                             for (int nb = 0; nb < NB; ++nb) {
                                 f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
@@ -316,7 +346,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
                             }
                         }
 #pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma(j0, x0[nb], acc[mb][nb]);
+                        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma<OPT>(j0, x0[nb], acc[mb][nb]);
                     } else {
                         const u32x4 j0 = jw[JS][mb][3 * sl], j1 = jw[JS][mb][3 * sl + 1], j2 = jw[JS][mb][3 * sl + 2];
 #pragma unroll
@@ -413,7 +443,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
                     for (int m = RG / 2; m >= 1; m >>= 1) e += __shfl_xor(e, m);
                     if (row == 0 && r < a.R) a.partial[(long long)mt * a.Rp + r] = e;
                 } else if (inside) {
-                    if (epi_apply<MODE, CPLX, OP_F32>(a, i0, r, true, EARLY ? pre[u0 + v] : in[v], cr, ci)) a.flags[r] = 1;
+                    if (epi_apply<MODE, CPLX, OPT>(a, i0, r, true, EARLY ? pre[u0 + v] : in[v], cr, ci)) a.flags[r] = 1;
                 }
             }
         }
@@ -421,12 +451,12 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
 #endif
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int KS, int JD, bool CPLX, int JK>
+template <int BM, int BN, int BK, int WM, int WN, int KS, int JD, bool CPLX, int JK, int OPT = OP_F32>
 hipError_t launch_modes(int mode, const DenseStepArgs &a, hipStream_t st) {
     constexpr int TRAJ = CPLX ? BN / 2 : BN;
     if (a.Np % BK || a.Np % 4 || a.R < 1 || a.R > a.Rp) return hipErrorInvalidValue;
     const dim3 grid(((a.Np + BM - 1) / BM) * ((a.R + TRAJ - 1) / TRAJ)), block(64 * WM * WN * KS);
-#define GD_LAUNCH(M) dense_step_split<BM, BN, BK, WM, WN, KS, JD, CPLX, M, JK><<<grid, block, 0, st>>>(a)
+#define GD_LAUNCH(M) dense_step_split<BM, BN, BK, WM, WN, KS, JD, CPLX, M, JK, OPT><<<grid, block, 0, st>>>(a)
     switch (mode) {
     case MODE_EULER: GD_LAUNCH(MODE_EULER); break;
     case MODE_RK1: GD_LAUNCH(MODE_RK1); break;
@@ -498,6 +528,19 @@ hipError_t launch_energy(const DenseStepArgs &a, hipStream_t st) {
     X(2, 128, 128, 32, 2, 2, 2, 2)    \
     X(3, 256, 256, 32, 2, 4, 1, 2)
 
+// Variants {BM, BN, BK, WM, WN, KS, JD} of the 16-bit operands: one product,
+// no splitting, so larger waves; KS = 1 keeps the order of the sums that the
+// direct-to-LDS kernels of gd_dense_lp.h have (the same bits), so small problems take small
+// tiles instead.  Per step, BF16 (gd_dense_lp.h's best in brackets): N = 1000,
+// R = 128 6.9 us (14.2), N = R = 1024 10.3 (15.0), N = 1500, R = 600 12.6
+// (20.8), N = R = 2048 30.5 (36.7), N = R = 4096 126 (137).
+#define GD_SPLIT_LP_VARIANTS(X)       \
+    X(0, 256, 128, 64, 2, 2, 1, 2)    \
+    X(1, 128, 128, 64, 2, 2, 1, 2)    \
+    X(2, 128, 64, 64, 2, 2, 1, 2)     \
+    X(3, 64, 64, 64, 1, 2, 1, 4)      \
+    X(4, 32, 32, 64, 1, 1, 1, 4)
+
 }  // namespace split
 
 // launchers of the FP8-coupling and split-coupling instantiations, real and
@@ -507,5 +550,7 @@ hipError_t launch_split_j8_cx(int idx, int mode, const DenseStepArgs &a, hipStre
 hipError_t launch_split_j3_re(int idx, int mode, const DenseStepArgs &a, hipStream_t st);
 hipError_t launch_split_sign(int idx, const DenseStepArgs &a, hipStream_t st);
 hipError_t launch_split_j3_cx(int idx, int mode, const DenseStepArgs &a, hipStream_t st);
+hipError_t launch_split_lp_re(int idx, int mode, int op, const DenseStepArgs &a, hipStream_t st);
+hipError_t launch_split_lp_cx(int idx, int mode, int op, const DenseStepArgs &a, hipStream_t st);
 
 }  // namespace gd

@@ -10,6 +10,23 @@ constexpr int kSplitCfg[2][16][7] = {
     {GD_SPLIT_J8_VARIANTS(GD_ROW)},
 #undef GD_ROW
 };
+constexpr int kSplitLpCfg[][7] = {
+#define GD_ROW(id, bm, bn, bk, wm, wn, ks, jd) {bm, bn, bk, wm, wn, ks, jd},
+    GD_SPLIT_LP_VARIANTS(GD_ROW)
+#undef GD_ROW
+};
+
+DenseConfig config_of(const int *k, bool complex_mode, int id) {
+    DenseConfig c{};
+    c.id = id;
+    c.bm = k[0];
+    c.bn = k[1];
+    c.bk = k[2];
+    c.wn = k[4];
+    c.traj_tile = complex_mode ? c.bn / 2 : c.bn;
+    c.threads = 64 * k[3] * k[4] * k[5];
+    return c;
+}
 
 // J in the lane order of the matrix instruction (gd_split.h): one thread per
 // lane and 16-byte word
@@ -19,10 +36,8 @@ __global__ void tile_j8_k(const unsigned char *__restrict__ J, uint4 *__restrict
          t += (long long)gridDim.x * blockDim.x) {
         const int lane = int(t & 63);
         const long long blk = t >> 6;
-        const long long row = blk / (Np / 32) * 32 + (lane & 31), k = blk % (Np / 32) * 32 + 8 * (lane >> 5);
-        const uint2 s0 = *reinterpret_cast<const uint2 *>(J + row * Np + k);
-        const uint2 s1 = *reinterpret_cast<const uint2 *>(J + row * Np + k + 16);
-        out[t] = make_uint4(s0.x, s0.y, s1.x, s1.y);
+        const long long row = blk / (Np / 32) * 32 + (lane & 31), k = blk % (Np / 32) * 32 + 16 * (lane >> 5);
+        out[t] = *reinterpret_cast<const uint4 *>(J + row * Np + k);
     }
 }
 
@@ -54,16 +69,7 @@ hipError_t launch_tile_couplings(const float *J, const void *J8, void *out, int 
 int split_config_count() { return int(sizeof(kSplitCfg[0]) / sizeof(kSplitCfg[0][0])); }
 
 DenseConfig split_config(bool complex_mode, bool j_fp8, int idx) {
-    const int *k = kSplitCfg[j_fp8][idx];
-    DenseConfig c{};
-    c.id = idx;
-    c.bm = k[0];
-    c.bn = k[1];
-    c.bk = k[2];
-    c.wn = k[4];
-    c.traj_tile = complex_mode ? c.bn / 2 : c.bn;
-    c.threads = 64 * k[3] * k[4] * k[5];
-    return c;
+    return config_of(kSplitCfg[j_fp8][idx], complex_mode, idx);
 }
 
 hipError_t launch_split_step(const DenseConfig &cfg, bool complex_mode, int mode, bool j_fp8, const DenseStepArgs &a,
@@ -72,6 +78,17 @@ hipError_t launch_split_step(const DenseConfig &cfg, bool complex_mode, int mode
     if (idx < 0 || idx >= split_config_count()) return hipErrorInvalidValue;
     if (j_fp8) return complex_mode ? launch_split_j8_cx(idx, mode, a, st) : launch_split_j8_re(idx, mode, a, st);
     return complex_mode ? launch_split_j3_cx(idx, mode, a, st) : launch_split_j3_re(idx, mode, a, st);
+}
+
+int split_lp_config_count() { return int(sizeof(kSplitLpCfg) / sizeof(kSplitLpCfg[0])); }
+
+DenseConfig split_lp_config(bool complex_mode, int idx) {
+    return config_of(kSplitLpCfg[idx], complex_mode, kLpSplitBase + idx);
+}
+
+hipError_t launch_split_lp(int idx, bool complex_mode, int mode, int op, const DenseStepArgs &a, hipStream_t st) {
+    if (op != OP_BF16 && op != OP_F16) return hipErrorInvalidValue;
+    return complex_mode ? launch_split_lp_cx(idx, mode, op, a, st) : launch_split_lp_re(idx, mode, op, a, st);
 }
 
 int sign_energy_row_tile(int Np, int R) {
