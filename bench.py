@@ -1040,7 +1040,9 @@ def main():
     # then bracket whole launches and count their coupling evaluations (the
     # J d of an energy check closing a launch is one more)
     small = (-(-n // 64) * 64 <= 128 and prec_name == "fp32")
-    gemv = st.kernel_config >= 100 and not small
+    # ids from 200 on: persistent steps (J in registers; latency of the exchange)
+    persist = st.kernel_config >= 200 and not small
+    gemv = st.kernel_config >= 100 and not small and not persist
     achieved = flops_launch / avg_s / 1e12
     peak = fp32_matrix_peak(J) if prec_name == "fp32" else PEAKS_TFLOPS[prec_name]
     if gemv:
@@ -1084,6 +1086,11 @@ def main():
                       "kernel": "small_step_k", "coupling_evaluations": int(launches),
                       "avg_evaluation_us": avg_s * 1e6, "flops_per_evaluation": flops_launch}
                      if small else
+                     {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+                      "frac": achieved / peak, "traffic": None, "kernel": "persist_step_k" if st.kernel_config < 208
+                      else "persist_few_k", "coupling_evaluations": int(launches),
+                      "avg_evaluation_us": avg_s * 1e6, "flops_per_evaluation": flops_launch}
+                     if persist else
                      {"bound": "mfma", "achieved": achieved, "peak": peak,
                       "unit": "TFLOP/s", "frac": achieved / peak,
                       "traffic": (kernel_traffic(st.kernel_config, "dense_step_split")

@@ -186,7 +186,11 @@ typedef struct gd_run_stats {
                                  pins one instead (the set-up call then fails with
                                  GD_E_INVALID_ARG if that id does not fit).  Problems of
                                  at most 128 padded spins (FP32, no pinned variant) use a
-                                 fused multi-step kernel instead of the variants.  Batches
+                                 fused multi-step kernel instead of the variants; larger
+                                 ones whose couplings fit the registers of the chip (FP32,
+                                 no pinned variant, not GD_F_ASYNC) run all steps of a call
+                                 in persistent kernels (ids from 200 on, once run).
+                                 Batches
                                  of instances: the same with GD_BATCH_CONFIG=<id>; the
                                  variants with per-instance item widths also relabel each
                                  instance's spins at set-up (host threads, deterministic,

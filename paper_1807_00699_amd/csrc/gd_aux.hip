@@ -306,7 +306,7 @@ __global__ void make_shadow_k(const float *__restrict__ src, void *dst, long lon
 // memory: the number of trajectories with flags set and (run_e non-null) the
 // running best of the checks.
 __global__ void run_result_k(const int *__restrict__ flags, int R, const double *__restrict__ run_e,
-                             const int *__restrict__ run_i, RunResult *out) {
+                             const int *__restrict__ run_i, const int *__restrict__ stalled, RunResult *out) {
     __shared__ int s[1024];
     int c = 0;
     for (int r = threadIdx.x; r < R; r += blockDim.x) c += flags[r] != 0;
@@ -318,6 +318,7 @@ __global__ void run_result_k(const int *__restrict__ flags, int R, const double 
     }
     if (threadIdx.x == 0) {
         out->diverged = s[0];
+        out->stalled = stalled ? *stalled : 0;
         if (run_e) {
             out->best_e = run_e[0];
             out->best_i = run_i[0];
@@ -421,9 +422,9 @@ hipError_t launch_make_shadow(const float *src, void *dst, long long count, int 
     return hipGetLastError();
 }
 
-hipError_t launch_run_result(const int *flags, int R, const double *run_e, const int *run_i, RunResult *out,
+hipError_t launch_run_result(const int *flags, int R, const double *run_e, const int *run_i, const int *stalled, RunResult *out,
                              hipStream_t st) {
-    run_result_k<<<1, 1024, 0, st>>>(flags, R, run_e, run_i, out);
+    run_result_k<<<1, 1024, 0, st>>>(flags, R, run_e, run_i, stalled, out);
     return hipGetLastError();
 }
 

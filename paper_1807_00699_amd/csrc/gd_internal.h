@@ -99,6 +99,24 @@ bool dense_lp_config_fits(const DenseConfig &c, int Np, int Rp);
 hipError_t launch_dense_step_lp(const DenseConfig &cfg, bool complex_mode, int mode, int op,
                                 bool j_fp8, const DenseStepArgs &a, hipStream_t st);
 
+// Persistent steps (gd_persist.hip): FP32, Np > 128; ids reported from
+// kPersistBase on
+constexpr int kPersistBase = 200;
+struct PersistArgs {
+    unsigned *x;              // exchange buffers (persist_words), empty before the first launch
+    int *stalled;             // set when a workgroup waited longer than `patience`
+    long long base;           // amplitudes published by earlier launches
+    long long t0;             // index of the first step (noise)
+    unsigned long long seed;  // noise seed
+    long long patience;       // wall-clock ticks (100 MHz)
+    int steps;
+    int groups, pause;        // set by launch_persist
+};
+long long persist_words(int id, bool cplx, int Np, int R);
+int persist_variant(bool cplx, bool rk4, bool j8, int Np, int R);
+hipError_t launch_persist(int id, bool cplx, bool rk4, bool j8, const DenseStepArgs &a, const PersistArgs &p,
+                          hipStream_t st);
+
 // ---- small-R coupling product (gd_gemv.hip): a J-streaming matrix-vector
 // kernel for at most kGemvMaxCols GEMM columns (R real or 2R complex), with
 // the same modes and epilogue as the dense kernels.  Its variants carry ids
@@ -236,9 +254,10 @@ struct RunResult {
     double best_e;   // running best of the checks and its trajectory
     int best_i;
     int diverged;    // trajectories r < R with flags[r] != 0
+    int stalled;     // *stalled, 0 without one
 };
-hipError_t launch_run_result(const int *flags, int R, const double *run_e, const int *run_i, RunResult *out,
-                             hipStream_t st);
+hipError_t launch_run_result(const int *flags, int R, const double *run_e, const int *run_i, const int *stalled,
+                             RunResult *out, hipStream_t st);
 // J in the order the small-problem kernel reads it (Np 64 or 128; Np^2 floats)
 hipError_t launch_small_couplings(const float *J, float *out, int Np, hipStream_t st);
 // `steps` Euler or RK4 steps of a small problem (Np 64 or 128; FP32; a.J from

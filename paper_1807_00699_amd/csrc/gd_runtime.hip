@@ -173,6 +173,12 @@ struct gd_solver {
     void *dJt = nullptr;       // J (FP8, or three BF16 pieces) as the split kernels read it
     float *dJs = nullptr;      // FP32 solvers with Np <= 128: J as the fused small-problem kernel reads it
     void *shadow[3] = {nullptr, nullptr, nullptr};   // operand copies of psi[k]
+    // persistent steps: variant (-1: one launch per step), exchange buffers
+    // and how many amplitude sets went through them
+    int persist = -1;
+    unsigned *xchg = nullptr;
+    int *stalled = nullptr;
+    long long xbase = 0;
     void *shadowD = nullptr;   // operand copy of the discretised state
     // state
     int R = 0, Rp = 0;
@@ -240,6 +246,11 @@ void free_state(gd_solver *s) {
     s->shadowD = nullptr;
     if (s->D64) (void)hipFree(s->D64);
     s->D64 = nullptr;
+    if (s->xchg) (void)hipFree(s->xchg);
+    if (s->stalled) (void)hipFree(s->stalled);
+    s->xchg = nullptr;
+    s->stalled = nullptr;
+    s->persist = -1;
     if (s->partial) (void)hipFree(s->partial);
     if (s->dE) (void)hipFree(s->dE);
     if (s->flags) (void)hipFree(s->flags);
@@ -517,6 +528,28 @@ int device_energies(gd_solver *s, int *ntiles) {
     a.psi_in = s->D;
     GD_HIP(launch_coupling(s, s->cfg, MODE_ENERGY, a));
     *ntiles = (s->Np + s->cfg.bm - 1) / s->cfg.bm;
+    return GD_OK;
+}
+
+// Whether runs of this solver are persistent steps, and their buffers
+int choose_persist(gd_solver *s) {
+    const bool cx = s->complex_mode();
+    s->persist = -1;
+    // (asynchronous runs return before anyone looks whether the launch stalled)
+    if (s->op != OP_F32 || s->mod() || s->Np <= 128 || (s->prm.flags & GD_F_ASYNC) || std::getenv("GD_DENSE_CONFIG"))
+        return GD_OK;
+    const int id = persist_variant(cx, s->integrator() == GD_RK4, s->dJ8 != nullptr, s->Np, s->R);
+    if (id < 0) return GD_OK;
+    if (!s->xchg) {
+        const long long words = persist_words(id, cx, s->Np, s->R);
+        int rc = dalloc(&s->xchg, (size_t)words);
+        if (rc == GD_OK) rc = dalloc(&s->stalled, 1);
+        if (rc != GD_OK) return rc;
+        GD_HIP(hipMemsetAsync(s->xchg, 0xFF, (size_t)words * 4, s->stream));
+        GD_HIP(hipMemsetAsync(s->stalled, 0, 4, s->stream));
+        s->xbase = 0;
+    }
+    s->persist = id;
     return GD_OK;
 }
 
@@ -1082,7 +1115,8 @@ int gd_set_init(gd_solver *s, int32_t batch, const float *psi0, const float *gam
     }
     GD_HIP(refresh_shadow(s, 0));
     if ((rc = reset_mod_couplings(s)) != GD_OK) return rc;
-    return choose_config(s);
+    if ((rc = choose_config(s)) != GD_OK) return rc;
+    return choose_persist(s);
 }
 
 // Replay the captured kGraphSteps steps (capturing them first if the
@@ -1090,6 +1124,10 @@ int gd_set_init(gd_solver *s, int32_t batch, const float *psi0, const float *gam
 // so the Euler buffer ping-pong ends where it started.
 constexpr int kGraphSteps = 32;
 constexpr int kSmallStepsPerLaunch = 4096;
+constexpr int kPersistSteps = 4096;
+// wall-clock ticks (60 s): the exchange takes microseconds, but workgroups may
+// start as late as long kernels of other streams leave their CUs
+constexpr long long kPersistPatience = 6000000000;
 constexpr long long kGraphWork = 1ll << 28;   // Np^2 Rp P below which steps are replayed
 static_assert(kGraphSteps % 2 == 0, "Euler ping-pong parity");
 
@@ -1141,7 +1179,9 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     // (those of its steps, and J d of an energy check that closes it) as
     // launches.  Otherwise small problems replay captured
     // graphs, except with profiling events, noise (its key changes every
-    // step) or GD-mod.
+    // step) or GD-mod.  Problems whose J fits the registers of the chip run
+    // persistent steps, a bounded number per launch, whatever the chunk: a
+    // trajectory does not depend on how a run is cut.
     const bool rk4 = s->integrator() == GD_RK4;
     const bool small_ok = !s->mod() && s->op == OP_F32 && s->Np <= 128 &&
                           std::getenv("GD_DENSE_CONFIG") == nullptr;
@@ -1229,6 +1269,36 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
                 k += m;
             }
         }
+        while (s->persist >= 0 && k < chunk) {
+            const int m = int(std::min<int64_t>(chunk - k, kPersistSteps));
+            DenseStepArgs a = base_args(s);
+            a.J = s->dJ8 ? s->dJ8 : (const void *)s->dJ;
+            a.psi_in = s->psi[s->cur];
+            a.psi_out = s->psi[s->cur ^ 1];
+            a.gam_in = s->gam;
+            a.gam_out = s->gam;
+            if (s->prm.noise_D != 0.0) a.noise_amp = float(s->prm.noise_D * std::sqrt(double(a.dt)));
+            PersistArgs p{};
+            p.x = s->xchg;
+            p.stalled = s->stalled;
+            p.base = s->xbase;
+            p.t0 = s->steps_done + k;
+            p.seed = s->prm.noise_seed;
+            p.patience = kPersistPatience;
+            p.steps = m;
+            if (timed && (rc = ev_begin(s)) != GD_OK) return rc;
+            if (launch_persist(s->persist, s->complex_mode(), rk4, s->dJ8 != nullptr, a, p, s->stream) != hipSuccess) {
+                // cooperative launches are refused while another process on
+                // the device uses them: one launch per step from here on
+                (void)hipGetLastError();
+                s->persist = -1;
+                break;
+            }
+            if (timed && (rc = ev_end(s, m * (rk4 ? 4 : 1))) != GD_OK) return rc;
+            s->xbase += m * (rk4 ? 4 : 1);
+            s->cur ^= 1;
+            k += m;
+        }
         if (graph_ok) {
             for (; chunk - k >= kGraphSteps; k += kGraphSteps) {
                 if (timed && (rc = ev_begin(s)) != GD_OK) return rc;
@@ -1293,7 +1363,8 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     // one wait for the steps and for what the host reads of them, written to
     // pinned memory by the last kernel
     if (!s->hres) GD_HIP(hipHostMalloc(reinterpret_cast<void **>(&s->hres), sizeof(RunResult)));
-    GD_HIP(launch_run_result(s->flags, s->R, deferred ? s->dE + s->Rp + 1 : nullptr, s->dBest + 1, s->hres, s->stream));
+    GD_HIP(launch_run_result(s->flags, s->R, deferred ? s->dE + s->Rp + 1 : nullptr, s->dBest + 1, s->stalled, s->hres,
+                             s->stream));
     GD_HIP(hipStreamSynchronize(s->stream));
     s->run_seconds += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     if (clocked) {
@@ -1310,6 +1381,11 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
         s->launches_timed += s->ev_launches;
         s->ev_used = 0;
         s->ev_launches = 0;
+    }
+    if (s->hres->stalled) {
+        // (the amplitudes of that launch were not written)
+        free_state(s);
+        return fail(GD_E_DEVICE, "persistent step kernel: a workgroup waited too long for the others");
     }
     const int cnt = s->hres->diverged;
     s->diverged = cnt;
@@ -1465,6 +1541,7 @@ int gd_set_state(gd_solver *s, int32_t batch, const float *psi, const float *gam
     if (!s->have_state || batch != s->R) {
         if ((rc = alloc_state(s, batch)) != GD_OK) return rc;
         if ((rc = choose_config(s)) != GD_OK) return rc;
+        if ((rc = choose_persist(s)) != GD_OK) return rc;
     }
     reset_stats(s);
     s->cur = 0;
@@ -1512,7 +1589,8 @@ int gd_stats(gd_solver *s, gd_run_stats *out) {
     out->ttt_steps = s->ttt_steps;
     out->best_energy = s->best_energy;
     out->best_index = s->best_index;
-    out->kernel_config = s->cfg.id;
+    // (until a run: the variant that energy checks use)
+    out->kernel_config = s->persist >= 0 && s->xbase > 0 ? kPersistBase + s->persist : s->cfg.id;
     return GD_OK;
 }
 
