@@ -143,6 +143,14 @@ hipError_t launch_gemv_step(const DenseConfig &cfg, bool complex_mode, int mode,
 // [R][Np][Np] (updated in place); c_hat = dt * eps_hat.  Needs Np % 16 == 0
 // and gdmod_lds_bytes <= 64 KiB.
 size_t gdmod_lds_bytes(bool complex_mode, int Np);
+// packed K (one triangle, gdmod_packed_floats per trajectory) and the partial
+// sums of its step
+long long gdmod_packed_floats(int Np);
+long long gdmod_part_floats(bool cplx, int Np, int R);
+hipError_t launch_gdmod_pack(const float *J, float *K, int Np, int R, hipStream_t st);
+hipError_t launch_gdmod_unpack(const float *K, float *out, int Np, int n, hipStream_t st);
+hipError_t launch_gdmod_sym(bool complex_mode, const DenseStepArgs &a, const float *J, float *K, float *part, float c_hat,
+                            hipStream_t st);
 hipError_t launch_gdmod(bool complex_mode, const DenseStepArgs &a, const float *J, float *K, float c_hat,
                         hipStream_t st);
 

@@ -104,6 +104,7 @@ inline bool f16_exact(float v, uint16_t *out) {
 // that cannot allocate.  In host code `scratch` names a host-side stand-in,
 // not device memory: the device address comes from hipGetSymbolAddress, once
 // per device with that device current, and only that address is used.
+constexpr long long kModPacked = 25000000;   // GD-mod: R Np^2 from which one triangle of each K is kept (gd_mod.hip)
 constexpr size_t kScratchBytes = size_t(16) << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 std::mutex g_scratch_mu;
@@ -187,7 +188,9 @@ struct gd_solver {
     float *psi[3] = {nullptr, nullptr, nullptr};
     float *gam = nullptr, *gam_s = nullptr, *acc_psi = nullptr, *acc_gam = nullptr;
     float *D = nullptr;
-    float *K = nullptr;        // GD-mod couplings [R][Np][Np]
+    float *K = nullptr;        // GD-mod couplings [R][Np][Np], or one triangle of each (K_packed)
+    bool K_packed = false;
+    float *Kpart = nullptr;    // K_packed: partial coupling sums of a step
     double *D64 = nullptr;     // FP64 readout planes of the re-score (allocated on first use)
     double *partial = nullptr, *dE = nullptr;
     int *flags = nullptr, *dBest = nullptr;
@@ -239,7 +242,7 @@ void free_state(gd_solver *s) {
     s->step_graph_cur = -1;
     if (s->psi[1] == s->psi[0]) s->psi[1] = nullptr;
     for (float *&p : s->psi) { if (p) (void)hipFree(p); p = nullptr; }
-    float **fl[] = {&s->gam, &s->gam_s, &s->acc_psi, &s->acc_gam, &s->D, &s->K};
+    float **fl[] = {&s->gam, &s->gam_s, &s->acc_psi, &s->acc_gam, &s->D, &s->K, &s->Kpart};
     for (float **p : fl) { if (*p) (void)hipFree(*p); *p = nullptr; }
     for (void *&p : s->shadow) { if (p) (void)hipFree(p); p = nullptr; }
     if (s->shadowD) (void)hipFree(s->shadowD);
@@ -314,7 +317,9 @@ int alloc_state(gd_solver *s, int R) {
     }
     if (rc == GD_OK && s->mod()) {
         rc = dalloc(&s->gam_s, pl);   // gains ping-pong: every row block reads all gains
-        if (rc == GD_OK) rc = dalloc(&s->K, (size_t)R * s->Np * s->Np);
+        s->K_packed = (long long)R * s->Np * s->Np >= kModPacked;
+        if (rc == GD_OK) rc = dalloc(&s->K, (size_t)R * (s->K_packed ? gdmod_packed_floats(s->Np) : (long long)s->Np * s->Np));
+        if (rc == GD_OK && s->K_packed) rc = dalloc(&s->Kpart, (size_t)gdmod_part_floats(s->complex_mode(), s->Np, R));
     }
     if (rc == GD_OK) rc = dalloc(&s->D, pl * P);
     if (s->op != OP_F32) {
@@ -346,6 +351,10 @@ int alloc_state(gd_solver *s, int R) {
 // GD-mod: K_ij(0) = J_ij for every trajectory
 int reset_mod_couplings(gd_solver *s) {
     if (!s->mod() || !s->K) return GD_OK;
+    if (s->K_packed) {
+        GD_HIP(launch_gdmod_pack(s->dJ, s->K, s->Np, s->R, s->stream));
+        return GD_OK;
+    }
     const size_t m = (size_t)s->Np * s->Np;
     for (int r = 0; r < s->R; ++r)
         GD_HIP(hipMemcpyAsync(s->K + (size_t)r * m, s->dJ, m * sizeof(float), hipMemcpyDeviceToDevice,
@@ -439,8 +448,9 @@ int enqueue_step(gd_solver *s, const DenseConfig &cfg, float dt_override, bool t
         a.gam_in = s->gam;
         a.gam_out = s->gam_s;
         if (timed && (rc = ev_begin(s)) != GD_OK) return rc;
-        GD_HIP(launch_gdmod(s->complex_mode(), a, s->dJ, s->K, float(double(a.dt) * s->prm.eps_hat),
-                            s->stream));
+        const float c_hat = float(double(a.dt) * s->prm.eps_hat);
+        if (s->K_packed) GD_HIP(launch_gdmod_sym(s->complex_mode(), a, s->dJ, s->K, s->Kpart, c_hat, s->stream));
+        else GD_HIP(launch_gdmod(s->complex_mode(), a, s->dJ, s->K, c_hat, s->stream));
         if (timed && (rc = ev_end(s, 1)) != GD_OK) return rc;
         std::swap(s->gam, s->gam_s);
         s->cur ^= 1;
@@ -1566,6 +1576,21 @@ int gd_mod_couplings(gd_solver *s, int32_t traj, float *K) {
     if (traj < 0 || traj >= s->R) return fail(GD_E_INVALID_ARG, "trajectory out of range");
     const hipMemcpyKind kind =
         (s->prm.flags & GD_F_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
+    if (s->K_packed) {
+        const float *src = s->K + (size_t)traj * gdmod_packed_floats(s->Np);
+        const size_t m = (size_t)s->n * s->n;
+        float *full = K;
+        if (kind != hipMemcpyDeviceToDevice) {
+            const int rc = dalloc(&full, m);
+            if (rc != GD_OK) return rc;
+        }
+        hipError_t e = launch_gdmod_unpack(src, full, s->Np, s->n, s->stream);
+        if (e == hipSuccess && full != K) e = hipMemcpyAsync(K, full, m * sizeof(float), kind, s->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+        if (full != K) (void)hipFree(full);
+        GD_HIP(e);
+        return GD_OK;
+    }
     const float *src = s->K + (size_t)traj * s->Np * s->Np;
     GD_HIP(hipMemcpy2DAsync(K, (size_t)s->n * sizeof(float), src, (size_t)s->Np * sizeof(float),
                             (size_t)s->n * sizeof(float), (size_t)s->n, kind, s->stream));
