@@ -1,6 +1,7 @@
 // Auxiliary kernels of libgd.so: layout conversion, readout (discretisation)
 // of the amplitudes onto the spin domains of Eq. (h), deterministic energy
 // reductions and the FP64 re-scoring of Eq. (h).
+#include "gd_check.h"
 #include "gd_epilogue.h"
 #include "gd_readout.h"
 
@@ -32,8 +33,8 @@ __global__ void pack_planes_k(const float *__restrict__ user, float *__restrict_
 // Four spins of one trajectory per thread; `vec`: rows of the user's array are
 // 16-byte aligned (n a multiple of 4).  Bound by HBM.
 template <int P>
-__global__ void __launch_bounds__(256) unpack_planes_k(const float *__restrict__ planes, float *__restrict__ user,
-                                                       int n, int R, int Np, long long ps, bool vec) {
+__device__ inline void unpack_rows(const float *__restrict__ planes, float *__restrict__ user, int n, int R, int Np,
+                                   long long ps, bool vec) {
     const int i = 4 * (blockIdx.x * 256 + threadIdx.x);
     if (i >= n) return;
     for (int r = blockIdx.y; r < R; r += gridDim.y) {
@@ -54,6 +55,20 @@ __global__ void __launch_bounds__(256) unpack_planes_k(const float *__restrict__
                 if (i + e / P < n) dst[e] = o[e / 4][e % 4];
         }
     }
+}
+
+template <int P>
+__global__ void __launch_bounds__(256) unpack_planes_k(const float *__restrict__ planes, float *__restrict__ user,
+                                                       int n, int R, int Np, long long ps, bool vec) {
+    unpack_rows<P>(planes, user, n, R, Np, ps, vec);
+}
+
+template <int P>
+__global__ void __launch_bounds__(256)
+unpack_state_k(const float *__restrict__ psi, float *__restrict__ upsi, const float *__restrict__ gam,
+               float *__restrict__ ugam, int n, int R, int Np, long long ps, bool vec) {
+    if (blockIdx.z == 0) unpack_rows<P>(psi, upsi, n, R, Np, ps, vec);
+    else unpack_rows<1>(gam, ugam, n, R, Np, ps, vec);
 }
 
 __device__ inline void store_shadow(void *dst, long long k, float v, int op) {
@@ -135,56 +150,18 @@ __global__ void energy_sum_k(const double *__restrict__ partial, int ntiles, int
 // The same sums for few trajectories and many row tiles: one wave per
 // trajectory, lane l adds tiles l, l + 64, ... in order, then a butterfly
 // over the wave (a fixed order, so repeated checks give the same sums).
-__global__ void __launch_bounds__(64) energy_sum_wide_k(const double *__restrict__ partial, int ntiles,
-                                                        int Rp, double *__restrict__ E) {
+__global__ void __launch_bounds__(64) energy_sum_wide_k(const double *__restrict__ partial, int ntiles, int Rp,
+                                                        CheckEnd c) {
     const int r = blockIdx.x, lane = threadIdx.x;
     double s = 0.0;
     for (int t = lane; t < ntiles; t += 64) s += partial[(long long)t * Rp + r];
 #pragma unroll
     for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m);
-    if (lane == 0) E[r] = s;
+    if (lane == 0) store_agent(c.E + r, s);
+    if (last_arrival(c.count, c.R)) check_end(c);
 }
 
-// best = argmin_r E[r], ties -> lowest r (one workgroup); best_e = E[best]
-// (one read-back for the host's check).  With run_e: the running best of a
-// run's checks keeps (E[best], best) when E[best] < *run_e.  With trace:
-// E[best] is also written there (the check's entry of the energy trace).
-__global__ void energy_argmin_k(const double *__restrict__ E, int R, int *__restrict__ best,
-                                double *__restrict__ best_e, double *__restrict__ run_e,
-                                int *__restrict__ run_i, double *__restrict__ trace) {
-    __shared__ double sv[256];
-    __shared__ int si[256];
-    double bv = __builtin_inf();
-    int bi = 0x7fffffff;
-    for (int r = threadIdx.x; r < R; r += blockDim.x) {
-        const double s = E[r];
-        if (s < bv || (s == bv && r < bi)) { bv = s; bi = r; }
-    }
-    sv[threadIdx.x] = bv;
-    si[threadIdx.x] = bi;
-    __syncthreads();
-    for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) {
-            const double ov = sv[threadIdx.x + w];
-            const int oi = si[threadIdx.x + w];
-            if (ov < sv[threadIdx.x] || (ov == sv[threadIdx.x] && oi < si[threadIdx.x])) {
-                sv[threadIdx.x] = ov;
-                si[threadIdx.x] = oi;
-            }
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const int b = (si[0] == 0x7fffffff) ? 0 : si[0];
-        if (best) best[0] = b;
-        if (best_e) best_e[0] = E[b];
-        if (trace) trace[0] = E[b];
-        if (run_e && E[b] < run_e[0]) {
-            run_e[0] = E[b];
-            run_i[0] = b;
-        }
-    }
-}
+__global__ void __launch_bounds__(1024) check_end_k(CheckEnd c) { check_end(c); }
 
 // FP64 re-score of Eq. (h) for the discretised state, formed in FP64 from
 // the FP32 amplitudes by the readout of the model.  The readout planes are
@@ -302,45 +279,11 @@ __global__ void make_shadow_k(const float *__restrict__ src, void *dst, long lon
         store_shadow(dst, t, src[t], op);
 }
 
-// What the host reads at the end of a run, written straight to its pinned
-// memory: the number of trajectories with flags set and (run_e non-null) the
-// running best of the checks.
-__global__ void run_result_k(const int *__restrict__ flags, int R, const double *__restrict__ run_e,
-                             const int *__restrict__ run_i, const int *__restrict__ stalled, RunResult *out) {
-    __shared__ int s[1024];
-    int c = 0;
-    for (int r = threadIdx.x; r < R; r += blockDim.x) c += flags[r] != 0;
-    s[threadIdx.x] = c;
-    __syncthreads();
-    for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        out->diverged = s[0];
-        out->stalled = stalled ? *stalled : 0;
-        if (run_e) {
-            out->best_e = run_e[0];
-            out->best_i = run_i[0];
-        }
-    }
-}
-
 inline int grid_for(long long total) {
     long long b = (total + 255) / 256;
     if (b > 65536) b = 65536;
     if (b < 1) b = 1;
     return int(b);
-}
-
-// Running best over the device checks of one run, kept on the device so that
-// a run with no target does not wait for every check: seeded with (e0, i0);
-// energy_argmin_k keeps the first strict minimum of E[best] (the host rule).
-__global__ void best_seed_k(double *__restrict__ run_e, int *__restrict__ run_i, double e0, int i0) {
-    if (threadIdx.x == 0) {
-        run_e[0] = e0;
-        run_i[0] = i0;
-    }
 }
 
 }  // namespace
@@ -361,6 +304,17 @@ hipError_t launch_unpack_planes(const float *planes, float *user, int n, int R, 
     return hipGetLastError();
 }
 
+hipError_t launch_unpack_state(const float *psi, float *upsi, const float *gam, float *ugam, int n, int R, int Np, int Rp,
+                               int nplanes, hipStream_t st) {
+    const dim3 grid(unsigned((n + 1023) / 1024), unsigned(std::min(R, 65535)), 2);
+    const long long ps = (long long)Rp * Np;
+    const bool vec =
+        n % 4 == 0 && (reinterpret_cast<uintptr_t>(upsi) | reinterpret_cast<uintptr_t>(ugam)) % 16 == 0;
+    if (nplanes == 2) unpack_state_k<2><<<grid, 256, 0, st>>>(psi, upsi, gam, ugam, n, R, Np, ps, vec);
+    else unpack_state_k<1><<<grid, 256, 0, st>>>(psi, upsi, gam, ugam, n, R, Np, ps, vec);
+    return hipGetLastError();
+}
+
 float clock_im_weight(int q) { return (q == 3 || q == 6) ? 0.75f : 1.0f; }
 
 hipError_t launch_discretise(const float *psi, float *D, void *shadowD, int op, int readout, int q,
@@ -375,23 +329,21 @@ hipError_t launch_discretise(const float *psi, float *D, void *shadowD, int op, 
     return hipGetLastError();
 }
 
-hipError_t launch_energy_reduce(const double *partial, int ntiles, int Rp, int R, double *E,
-                                int *best, hipStream_t st, double *run_e, int *run_i, double *trace) {
-    if (R < 1) return hipErrorInvalidValue;
+hipError_t launch_energy_reduce(const double *partial, int ntiles, int Rp, const CheckEnd &c, hipStream_t st) {
+    if (c.R < 1 || c.R > Rp || !c.E || !c.count) return hipErrorInvalidValue;
     // one thread per trajectory reads its tiles one after the other: N = 800,
     // R = 100 (26 tiles) 7.3 us
-    if (R <= 512 && ntiles >= 8)
-        energy_sum_wide_k<<<R, 64, 0, st>>>(partial, ntiles, Rp, E);
-    else
-        energy_sum_k<<<(R + 255) / 256, 256, 0, st>>>(partial, ntiles, Rp, R, E);
-    energy_argmin_k<<<1, 256, 0, st>>>(E, R, best, E + Rp, run_e, run_i, trace);
-    return hipGetLastError();
+    if (c.R <= 512 && ntiles >= 8) {
+        energy_sum_wide_k<<<c.R, 64, 0, st>>>(partial, ntiles, Rp, c);
+        return hipGetLastError();
+    }
+    energy_sum_k<<<(c.R + 255) / 256, 256, 0, st>>>(partial, ntiles, Rp, c.R, c.E);
+    return launch_check_end(c, st);
 }
 
-hipError_t launch_energy_argmin(double *E, int R, int Rp, int *best, double *run_e, int *run_i,
-                                hipStream_t st, double *trace) {
-    if (R < 1 || R > Rp) return hipErrorInvalidValue;
-    energy_argmin_k<<<1, 256, 0, st>>>(E, R, best, E + Rp, run_e, run_i, trace);
+hipError_t launch_check_end(const CheckEnd &c, hipStream_t st) {
+    if (c.R < 1 || (c.out && !c.flags)) return hipErrorInvalidValue;
+    check_end_k<<<1, c.R > 512 ? 1024 : c.R > 64 ? 256 : 64, 0, st>>>(c);
     return hipGetLastError();
 }
 
@@ -412,19 +364,8 @@ hipError_t launch_energy_fp64(const float *J, const float *psi, const float *g, 
     return hipGetLastError();
 }
 
-hipError_t launch_best_seed(double *run_e, int *run_i, double e0, int i0, hipStream_t st) {
-    best_seed_k<<<1, 64, 0, st>>>(run_e, run_i, e0, i0);
-    return hipGetLastError();
-}
-
 hipError_t launch_make_shadow(const float *src, void *dst, long long count, int op, hipStream_t st) {
     make_shadow_k<<<grid_for(count), 256, 0, st>>>(src, dst, count, op);
-    return hipGetLastError();
-}
-
-hipError_t launch_run_result(const int *flags, int R, const double *run_e, const int *run_i, const int *stalled, RunResult *out,
-                             hipStream_t st) {
-    run_result_k<<<1, 1024, 0, st>>>(flags, R, run_e, run_i, stalled, out);
     return hipGetLastError();
 }
 

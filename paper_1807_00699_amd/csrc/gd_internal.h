@@ -99,6 +99,31 @@ bool dense_lp_config_fits(const DenseConfig &c, int Np, int Rp);
 hipError_t launch_dense_step_lp(const DenseConfig &cfg, bool complex_mode, int mode, int op,
                                 bool j_fp8, const DenseStepArgs &a, hipStream_t st);
 
+// What the host reads at the end of a run (out: pinned host memory)
+struct RunResult {
+    double best_e;   // running best of the checks and its trajectory
+    int best_i;
+    int diverged;    // trajectories r < R with flags[r] != 0
+    int stalled;     // *stalled, 0 without one
+};
+// The end of an energy check or of a run (gd_check.h)
+struct CheckEnd {
+    double *E = nullptr;        // energies of the check, or null
+    int R = 0;
+    int *best = nullptr;        // argmin and its energy
+    double *best_e = nullptr;
+    double *run_e = nullptr;    // running best of a run's checks; its first check takes (e0, i0) as the best so far
+    int *run_i = nullptr;
+    double e0 = 0.0;
+    int i0 = 0;
+    bool first = false;
+    double *trace = nullptr;    // the check's entry of the energy trace
+    const int *flags = nullptr;
+    const int *stalled = nullptr;
+    RunResult *out = nullptr;   // end of a run: pinned host memory
+    unsigned *count = nullptr;  // workgroups that have arrived, 0 between launches
+};
+
 // Persistent steps (gd_persist.hip): FP32, Np > 128; ids reported from
 // kPersistBase on
 constexpr int kPersistBase = 200;
@@ -113,9 +138,10 @@ struct PersistArgs {
     int groups, pause;        // set by launch_persist
 };
 long long persist_words(int id, bool cplx, int Np, int R);
+bool persist_ends_run(int id);
 int persist_variant(bool cplx, bool rk4, bool j8, int Np, int R);
 hipError_t launch_persist(int id, bool cplx, bool rk4, bool j8, const DenseStepArgs &a, const PersistArgs &p,
-                          hipStream_t st);
+                          const CheckEnd &c, hipStream_t st);
 
 // ---- small-R coupling product (gd_gemv.hip): a J-streaming matrix-vector
 // kernel for at most kGemvMaxCols GEMM columns (R real or 2R complex), with
@@ -218,6 +244,9 @@ hipError_t launch_batch_best(const double *E, int K, int R, double *best_E, int 
 // user [R][n] (or [R][n][2]) -> zero-padded planes [P][Rp][Np]
 hipError_t launch_pack_planes(const float *user, float *planes, int n, int R, int Np, int Rp,
                               int nplanes, hipStream_t st);
+// psi (nplanes) and gains at once
+hipError_t launch_unpack_state(const float *psi, float *upsi, const float *gam, float *ugam, int n, int R, int Np, int Rp,
+                               int nplanes, hipStream_t st);
 hipError_t launch_unpack_planes(const float *planes, float *user, int n, int R, int Np, int Rp,
                                 int nplanes, hipStream_t st);
 // Readout of the amplitudes onto the spin domain of Eq. (h).
@@ -239,16 +268,10 @@ float clock_im_weight(int q);
 hipError_t launch_discretise(const float *psi, float *D, void *shadowD, int op, int readout, int q,
                              int8_t *spins8, float *angle, int32_t *states, int *flags, int n, int R,
                              int Np, int Rp, int nplanes, long long plane_stride, hipStream_t st);
-// E[r] = sum_t partial[t][r] (fixed order), best = argmin (ties -> lowest r),
-// E[Rp] = E[best] (E holds Rp + 1 doubles); with run_e, the running best of a
-// run's checks (*run_e, *run_i) takes (E[best], best) when E[best] < *run_e;
-// with trace, *trace = E[best] as well
-hipError_t launch_energy_reduce(const double *partial, int ntiles, int Rp, int R, double *E,
-                                int *best, hipStream_t st, double *run_e = nullptr, int *run_i = nullptr,
-                                double *trace = nullptr);
-// The argmin and running-best part of launch_energy_reduce for E[r] already formed
-hipError_t launch_energy_argmin(double *E, int R, int Rp, int *best, double *run_e, int *run_i,
-                                hipStream_t st, double *trace = nullptr);
+// c.E[r] = sum_t partial[t][r] (fixed order), then the end of the check
+hipError_t launch_energy_reduce(const double *partial, int ntiles, int Rp, const CheckEnd &c, hipStream_t st);
+// The end of a check or run alone
+hipError_t launch_check_end(const CheckEnd &c, hipStream_t st);
 // FP64 re-score from the FP32 amplitudes (unit phasors / signs formed in FP64):
 // partial[t][r] = sum_{i in tile t} [-Re(conj(d_i) (J d)_i) + g_i Re(d_i)]
 // D64: scratch for the FP64 readout planes, nplanes * Rp * Np doubles
@@ -257,27 +280,16 @@ hipError_t launch_energy_fp64(const float *J, const float *psi, const float *g, 
                               long long plane_stride, int readout, int q, hipStream_t st);
 // shadow copy of FP32 planes in BF16 / FP16
 hipError_t launch_make_shadow(const float *src, void *dst, long long count, int op, hipStream_t st);
-// What the host reads at the end of a run (out: pinned host memory)
-struct RunResult {
-    double best_e;   // running best of the checks and its trajectory
-    int best_i;
-    int diverged;    // trajectories r < R with flags[r] != 0
-    int stalled;     // *stalled, 0 without one
-};
-hipError_t launch_run_result(const int *flags, int R, const double *run_e, const int *run_i, const int *stalled,
-                             RunResult *out, hipStream_t st);
 // J in the order the small-problem kernel reads it (Np 64 or 128; Np^2 floats)
 hipError_t launch_small_couplings(const float *J, float *out, int Np, hipStream_t st);
 // `steps` Euler or RK4 steps of a small problem (Np 64 or 128; FP32; a.J from
 // launch_small_couplings) in one launch: psi_in/gam_in -> psi_out/gam_out (gam_out
 // may alias gam_in), flags[r] set if trajectory r ends non-finite.  Noise
 // (a.noise_amp != 0): step t0 + k uses the key SplitMix64(seed ^
-// SplitMix64(t0 + k)), as the step-by-step path does.  With E: the Eq. (h)
-// energies of the final state's readout (readout, q) into E[r], r < R.
+// SplitMix64(t0 + k)), as the step-by-step path does.  With c.E: the Eq. (h)
+// energies of the final state's readout (readout, q), and the end of the check.
 hipError_t launch_small_steps(bool complex_mode, bool rk4, const DenseStepArgs &a, int steps,
-                              unsigned long long seed, long long t0, int readout, int q, double *E,
+                              unsigned long long seed, long long t0, int readout, int q, const CheckEnd &c,
                               hipStream_t st);
-// Running best of a run's device checks: (*run_e, *run_i) = (e0, i0)
-hipError_t launch_best_seed(double *run_e, int *run_i, double e0, int i0, hipStream_t st);
 
 }  // namespace gd

@@ -33,6 +33,7 @@
 // couplings), 13.3 -> 3.7 (split couplings); N = 300, R = 64 5.4 -> 2.1; N =
 // 800, R = 100 6.3 -> 3.5; N = 2000, R = 64 9.8 -> 6.1; XY RK4 (four
 // evaluations) N = 1000, R = 128 32 -> 17.7; XY N = 1500, R = 48 31 -> 22.
+#include "gd_check.h"
 #include "gd_split.h"
 
 namespace gd {
@@ -82,11 +83,12 @@ __global__ void __launch_bounds__(64 * kWaves)
 persist_step_k(DenseStepArgs a, PersistArgs p) {
     constexpr int TR = CPLX ? 8 : 16;            // trajectories of a group
     constexpr int ROWS = 16 * RB, RS = ROWS + 4;
-    // fragments whose third pieces are kept in LDS (the registers do not hold
-    // them); the waves' sums then have one buffer and a barrier more
-    constexpr int JL = !J8 && FR * RB > 12 ? (RB == 4 ? 3 : FR) : 0;
+    // third pieces of J kept in LDS, as many as fit, where the registers do not
+    // hold them (spilled ones cost XY N = 1000, R = 128 10%); the waves' sums
+    // then have one buffer and a barrier more
+    constexpr int JL = !J8 && FR * RB > 12 ? (RB == 4 ? 15 : FR * RB) : 0;
     __shared__ __attribute__((aligned(16))) float red[JL ? 1 : 2][kWaves][16][RS];
-    __shared__ __attribute__((aligned(16))) u32x4 jlds[JL ? JL * RB * kWaves * 64 : 1];
+    __shared__ __attribute__((aligned(16))) u32x4 jlds[JL ? JL * kWaves * 64 : 1];
     __shared__ int stalled;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, kq = lane >> 4;
@@ -111,7 +113,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
                 const f32x4 *q = reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.J) + at);
                 u32x4 t;
                 split8(q[0], q[1], j[f][rb][0], j[f][rb][1], t);
-                if (f < JL) jlds[((f * RB + rb) * kWaves + wave) * 64 + lane] = t;
+                if (f * RB + rb < JL) jlds[((f * RB + rb) * kWaves + wave) * 64 + lane] = t;
                 else j[f][rb][2] = t;
             }
         }
@@ -211,7 +213,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
                         hi[rb] = mfma16(j0, x0, hi[rb]);
                     } else {
                         const u32x4 &j0 = j[f][rb][0], &j1 = j[f][rb][1];
-                        const u32x4 j2 = f < JL ? jlds[((f * RB + rb) * kWaves + wave) * 64 + lane] : j[f][rb][2];
+                        const u32x4 j2 = f * RB + rb < JL ? jlds[((f * RB + rb) * kWaves + wave) * 64 + lane] : j[f][rb][2];
                         lo[rb] = mfma16(j0, x2, lo[rb]);
                         lo[rb] = mfma16(j2, x0, lo[rb]);
                         lo[rb] = mfma16(j1, x1, lo[rb]);
@@ -303,18 +305,15 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
             if (CPLX) store1(mark + 16, kEmpty);
         }
     }
-    if (stalled) {
-        if (tid == 0) *p.stalled = 1;
-        return;
-    }
+    if (stalled && tid == 0) store_agent(p.stalled, 1);
 #pragma unroll
-    for (int k = 0; k < IT; ++k) {
+    for (int k = 0; k < IT && !stalled; ++k) {
         const int i = m0 + lr + k * LSTEP;
         if (!(item && i < a.n && r < a.R)) continue;
         a.psi_out[(long long)r * a.Np + i] = xr[k];
         if (CPLX) a.psi_out[ps + (long long)r * a.Np + i] = xi[k];
         a.gam_out[(long long)r * a.Np + i] = gm[k];
-        if (!(gd_finite(xr[k]) && gd_finite(gm[k]) && gd_finite(xi[k]))) a.flags[r] = 1;
+        if (!(gd_finite(xr[k]) && gd_finite(gm[k]) && gd_finite(xi[k]))) store_agent(a.flags + r, 1);
     }
 }
 
@@ -326,7 +325,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
 // through LDS within the wave.
 template <int NR, bool J8>
 __global__ void __launch_bounds__(1024)
-persist_few_k(DenseStepArgs a, PersistArgs p) {
+persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
     constexpr int NC = 3 * NR, PB = 528, RS = 20;   // LDS bytes of one piece's 256 values, floats of 16 rows (both padded)
     __shared__ __attribute__((aligned(16))) unsigned char xl[16][NC][PB];
     __shared__ __attribute__((aligned(16))) float red[2][16][NC][RS];
@@ -462,15 +461,13 @@ persist_few_k(DenseStepArgs a, PersistArgs p) {
             if (lane < 16) store1(own + ((p.base + ev + 2) & 3) * bsz, kEmpty);
         }
     }
-    if (stalled) {
-        if (tid == 0) *p.stalled = 1;
-        return;
-    }
-    if (inside && lane < 16) {
+    if (stalled && tid == 0) store_agent(p.stalled, 1);
+    if (inside && lane < 16 && !stalled) {
         a.psi_out[(long long)r * Np + i] = x;
         a.gam_out[(long long)r * Np + i] = gm;
-        if (!(gd_finite(x) && gd_finite(gm))) a.flags[r] = 1;
+        if (!(gd_finite(x) && gd_finite(gm))) store_agent(a.flags + r, 1);
     }
+    if (ce.out && last_arrival(ce.count, gridDim.x)) check_end(ce);   // the end of a run
 }
 
 }  // namespace
@@ -567,13 +564,22 @@ int persist_variant(bool cplx, bool rk4, bool j8, int Np, int R) {
     return -1;
 }
 
-hipError_t launch_persist(int id, bool cplx, bool rk4, bool j8, const DenseStepArgs &a, const PersistArgs &p, hipStream_t st) {
-    if (a.Np % 64 || a.R < 1 || p.steps < 1) return hipErrorInvalidValue;
+// The kernel for few trajectories also ends a run (gd_check.h); in the other one
+// the code for it costs registers: XY N = 1000, R = 128 388 us per 80
+// evaluations, 416 with it
+bool persist_ends_run(int id) { return id >= kFew; }
+
+hipError_t launch_persist(int id, bool cplx, bool rk4, bool j8, const DenseStepArgs &a, const PersistArgs &p,
+                          const CheckEnd &ce, hipStream_t st) {
+    if (a.Np % 64 || a.R < 1 || p.steps < 1 || ce.E ||
+        (ce.out && (!persist_ends_run(id) || ce.R != a.R || !ce.count || !ce.flags)))
+        return hipErrorInvalidValue;
     DenseStepArgs x = a;
     PersistArgs y = p;
     y.groups = persist_groups(id, cplx, a.R);
     y.pause = id < kFew ? kPause : a.Np > 1024 ? kPauseFewLarge : kPauseFew;
-    void *args[] = {&x, &y};
+    CheckEnd z = ce;
+    void *args[] = {&x, &y, &z};   // (the last for few trajectories only)
     if (id >= kFew) {
         const void *k = few_kernel(id, j8);
         if (!k || cplx || rk4 || a.Np > 4096 || a.R > (1 << (id - kFew)) || 256 * (a.R - 1) >= a.Np)

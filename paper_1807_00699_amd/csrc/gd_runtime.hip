@@ -179,6 +179,7 @@ struct gd_solver {
     int persist = -1;
     unsigned *xchg = nullptr;
     int *stalled = nullptr;
+    unsigned *arrivals = nullptr;   // of the last-workgroup ends of checks and runs
     long long xbase = 0;
     void *shadowD = nullptr;   // operand copy of the discretised state
     // state
@@ -251,6 +252,8 @@ void free_state(gd_solver *s) {
     s->D64 = nullptr;
     if (s->xchg) (void)hipFree(s->xchg);
     if (s->stalled) (void)hipFree(s->stalled);
+    if (s->arrivals) (void)hipFree(s->arrivals);
+    s->arrivals = nullptr;
     s->xchg = nullptr;
     s->stalled = nullptr;
     s->persist = -1;
@@ -331,6 +334,7 @@ int alloc_state(gd_solver *s, int R) {
     // + E[best] of the last check, + running best of a run's checks
     if (rc == GD_OK) rc = dalloc(&s->dE, (size_t)s->Rp + 2);
     if (rc == GD_OK) rc = dalloc(&s->flags, (size_t)s->Rp);
+    if (rc == GD_OK) rc = dalloc(&s->arrivals, 1);
     if (rc == GD_OK) rc = dalloc(&s->dBest, 2);   // best of the last check, running best
     if (rc == GD_OK) rc = dalloc(&s->dTrace, (size_t)kTraceChecks);
     if (rc != GD_OK) {
@@ -342,6 +346,7 @@ int alloc_state(gd_solver *s, int R) {
         if (s->shadow[k]) GD_HIP(hipMemsetAsync(s->shadow[k], 0, pl * P * sizeof(uint16_t), s->stream));
     }
     GD_HIP(hipMemsetAsync(s->flags, 0, (size_t)s->Rp * sizeof(int), s->stream));
+    GD_HIP(hipMemsetAsync(s->arrivals, 0, sizeof(unsigned), s->stream));
     if (s->gam_s) GD_HIP(hipMemsetAsync(s->gam_s, 0, pl * sizeof(float), s->stream));
     s->cur = 0;
     s->have_state = true;
@@ -602,16 +607,12 @@ int choose_config(gd_solver *s) {
         return !lp || id >= kLpSplitBase || dense_lp_config_fits(cfg_of(id), s->Np, s->Rp);
     };
     // the fused kernel needs its own form of J; the coupling kernels' form is
-    // laid out when they first run (energy checks outside a run, pinned variants)
+    // laid out when they first run (here, when they are timed)
     const bool fused = !lp && !s->mod() && s->Np <= 128;
     if (fused && !s->dJs) {
         const int rc = dalloc(&s->dJs, (size_t)s->Np * s->Np);
         if (rc != GD_OK) return rc;
         GD_HIP(launch_small_couplings(s->dJ, s->dJs, s->Np, s->stream));
-    }
-    if (!fused) {
-        const int rc = tile_couplings(s);
-        if (rc != GD_OK) return rc;
     }
     if (const char *env = std::getenv("GD_DENSE_CONFIG")) {
         int id = std::atoi(env);
@@ -657,6 +658,8 @@ int choose_config(gd_solver *s) {
     const long long work = (long long)s->Np * s->Np * s->Rp * s->P;
     int best = -1;
     if (work >= (1ll << 26) && !s->mod()) {
+        const int rt = tile_couplings(s);
+        if (rt != GD_OK) return rt;
         hipEvent_t e0, e1;
         GD_HIP(hipEventCreate(&e0));
         GD_HIP(hipEventCreate(&e1));
@@ -1195,7 +1198,7 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     const bool rk4 = s->integrator() == GD_RK4;
     const bool small_ok = !s->mod() && s->op == OP_F32 && s->Np <= 128 &&
                           std::getenv("GD_DENSE_CONFIG") == nullptr;
-    if (!small_ok && !s->mod() && (rc = tile_couplings(s)) != GD_OK) return rc;
+    if (!small_ok && !s->mod() && (s->persist < 0 || ci > 0) && (rc = tile_couplings(s)) != GD_OK) return rc;
     // The matrix-vector kernels of few trajectories run for microseconds, so
     // they are always replayed from graphs (with GD_F_PROFILE one event pair
     // brackets each replay and its launches, in-graph dispatch gaps included).
@@ -1206,7 +1209,41 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     // the checks is kept on the device and read back with the run's end.
     const bool deferred = ci > 0 && !s->prm.has_target && !s->track_target &&
                           !(s->prm.flags & GD_F_ASYNC);
-    if (deferred) GD_HIP(launch_best_seed(s->dE + s->Rp + 1, s->dBest + 1, s->best_energy, s->best_index, s->stream));
+    // What the host reads of the run at its end is written to pinned memory by
+    // the kernel that ends its last check or steps.
+    const bool async = (s->prm.flags & GD_F_ASYNC) != 0;
+    if (!async && !s->hres) GD_HIP(hipHostMalloc(reinterpret_cast<void **>(&s->hres), sizeof(RunResult)));
+    bool first_check = true, ended = false;
+    auto end_of = [&](bool check, bool run_end) {
+        CheckEnd c;
+        c.R = s->R;
+        c.count = s->arrivals;
+        if (deferred) {
+            c.run_e = s->dE + s->Rp + 1;
+            c.run_i = s->dBest + 1;
+            c.first = first_check;
+            c.e0 = s->best_energy;
+            c.i0 = s->best_index;
+        }
+        if (check) {
+            c.E = s->dE;
+            c.best = s->dBest;
+            c.best_e = s->dE + s->Rp;
+            first_check = false;
+        }
+        if (run_end) {
+            c.flags = s->flags;
+            c.stalled = s->stalled;
+            c.out = s->hres;
+            ended = true;
+        }
+        return c;
+    };
+    auto trace_slot = [&](int64_t step) -> double * {
+        if (s->trace_steps.size() >= (size_t)kTraceChecks) return nullptr;
+        s->trace_steps.push_back(step);
+        return s->dTrace + s->trace_steps.size() - 1;
+    };
     // Recording the time to target without stopping: each check is read back
     // one check later (the next chunk is queued meanwhile) and timed by
     // events from the start of the run.
@@ -1257,7 +1294,7 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
             chunk = std::min<int64_t>(chunk, to_check);
         }
         int64_t k = 0;
-        const bool check_due = ci > 0 && (s->steps_done + chunk) % ci == 0;
+        const bool check_due = ci > 0 && (s->steps_done + chunk) % ci == 0, last = !async && done + chunk == steps;
         if (small_ok) {
             // all steps of the chunk in LDS, a bounded number per launch
             while (k < chunk) {
@@ -1271,10 +1308,13 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
                 if (timed && (rc = ev_begin(s)) != GD_OK) return rc;
                 if (s->prm.noise_D != 0.0) a.noise_amp = float(s->prm.noise_D * std::sqrt(double(a.dt)));
                 // the launch that ends at a check also forms its energies
-                double *E = (check_due && k + m == chunk) ? s->dE : nullptr;
+                CheckEnd c;
+                const bool tail = k + m == chunk;
+                if (tail && (check_due || last)) c = end_of(check_due, last);
+                if (tail && check_due) c.trace = trace_slot(s->steps_done + chunk);
                 GD_HIP(launch_small_steps(s->complex_mode(), rk4, a, m, s->prm.noise_seed, s->steps_done + k,
-                                          s->ro, s->prm.q, E, s->stream));
-                if (timed && (rc = ev_end(s, m * (rk4 ? 4 : 1) + (E ? 1 : 0))) != GD_OK) return rc;
+                                          s->ro, s->prm.q, c, s->stream));
+                if (timed && (rc = ev_end(s, m * (rk4 ? 4 : 1) + (c.E ? 1 : 0))) != GD_OK) return rc;
                 s->cur ^= 1;
                 k += m;
             }
@@ -1297,11 +1337,15 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
             p.patience = kPersistPatience;
             p.steps = m;
             if (timed && (rc = ev_begin(s)) != GD_OK) return rc;
-            if (launch_persist(s->persist, s->complex_mode(), rk4, s->dJ8 != nullptr, a, p, s->stream) != hipSuccess) {
+            CheckEnd c;
+            if (last && !check_due && k + m == chunk && persist_ends_run(s->persist)) c = end_of(false, true);
+            if (launch_persist(s->persist, s->complex_mode(), rk4, s->dJ8 != nullptr, a, p, c, s->stream) != hipSuccess) {
                 // cooperative launches are refused while another process on
                 // the device uses them: one launch per step from here on
                 (void)hipGetLastError();
                 s->persist = -1;
+                ended = false;
+                if ((rc = tile_couplings(s)) != GD_OK) return rc;
                 break;
             }
             if (timed && (rc = ev_end(s, m * (rk4 ? 4 : 1))) != GD_OK) return rc;
@@ -1327,21 +1371,13 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
         s->spin_updates += (int64_t)s->n * s->R * chunk;
         if (ci > 0 && s->steps_done % ci == 0) {
             // device check: energy GEMM of the readout, deterministic reduction
-            // (small problems: energies from the last step launch, the argmin)
-            double *run_e = deferred ? s->dE + s->Rp + 1 : nullptr;
-            int *run_i = deferred ? s->dBest + 1 : nullptr;
-            double *trace = nullptr;
-            if (s->trace_steps.size() < (size_t)kTraceChecks) {
-                trace = s->dTrace + s->trace_steps.size();
-                s->trace_steps.push_back(s->steps_done);
-            }
-            if (small_ok) {
-                GD_HIP(launch_energy_argmin(s->dE, s->R, s->Rp, s->dBest, run_e, run_i, s->stream, trace));
-            } else {
+            // (small problems: done by the last step launch)
+            if (!small_ok) {
                 int ntiles = 0;
                 if ((rc = device_energies(s, &ntiles)) != GD_OK) return rc;
-                GD_HIP(launch_energy_reduce(s->partial, ntiles, s->Rp, s->R, s->dE, s->dBest, s->stream, run_e, run_i,
-                                            trace));
+                CheckEnd c = end_of(true, last);
+                c.trace = trace_slot(s->steps_done);
+                GD_HIP(launch_energy_reduce(s->partial, ntiles, s->Rp, c, s->stream));
             }
             if (deferred) continue;
             if (lookahead) {
@@ -1370,11 +1406,8 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     if (s->prm.flags & GD_F_ASYNC) return GD_OK;
     if ((rc = read_pending()) != GD_OK) return rc;
     if (clocked) GD_HIP(hipEventRecord(s->ev_end, s->stream));
-    // one wait for the steps and for what the host reads of them, written to
-    // pinned memory by the last kernel
-    if (!s->hres) GD_HIP(hipHostMalloc(reinterpret_cast<void **>(&s->hres), sizeof(RunResult)));
-    GD_HIP(launch_run_result(s->flags, s->R, deferred ? s->dE + s->Rp + 1 : nullptr, s->dBest + 1, s->stalled, s->hres,
-                             s->stream));
+    // one wait for the steps and for what the host reads of them
+    if (!ended) GD_HIP(launch_check_end(end_of(false, true), s->stream));
     GD_HIP(hipStreamSynchronize(s->stream));
     s->run_seconds += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     if (clocked) {
@@ -1436,7 +1469,13 @@ static int energies(gd_solver *s, double *E, int32_t *best, bool fp64) {
     } else if ((rc = device_energies(s, &ntiles)) != GD_OK) {
         return rc;
     }
-    GD_HIP(launch_energy_reduce(s->partial, ntiles, s->Rp, s->R, s->dE, s->dBest, s->stream));
+    CheckEnd c;
+    c.E = s->dE;
+    c.R = s->R;
+    c.best = s->dBest;
+    c.best_e = s->dE + s->Rp;
+    c.count = s->arrivals;
+    GD_HIP(launch_energy_reduce(s->partial, ntiles, s->Rp, c, s->stream));
     int bi = 0;
     if (s->prm.flags & GD_F_DEVICE_PTRS) {
         GD_HIP(hipMemcpyAsync(E, s->dE, sizeof(double) * s->R, hipMemcpyDeviceToDevice, s->stream));
@@ -1530,8 +1569,16 @@ int gd_get_state(gd_solver *s, float *psi, float *gamma, int64_t *step) {
     if (s->batch) return batch_get_state(s->batch, psi, gamma, step);
     if (!s->have_state) return fail(GD_E_STATE, "no state");
     int rc;
-    if (psi && (rc = download_planes(s, s->psi[s->cur], psi, s->P)) != GD_OK) return rc;
-    if (gamma && (rc = download_planes(s, s->gam, gamma, 1)) != GD_OK) return rc;
+    const bool both = psi && gamma && (s->prm.flags & GD_F_DEVICE_PTRS) != 0 &&
+                      (reinterpret_cast<uintptr_t>(psi) | reinterpret_cast<uintptr_t>(gamma)) % 4 == 0 &&
+                      device_span(s, psi, (size_t)s->R * s->n * s->P * sizeof(float)) &&
+                      device_span(s, gamma, (size_t)s->R * s->n * sizeof(float));
+    if (both) {
+        GD_HIP(launch_unpack_state(s->psi[s->cur], psi, s->gam, gamma, s->n, s->R, s->Np, s->Rp, s->P, s->stream));
+    } else {
+        if (psi && (rc = download_planes(s, s->psi[s->cur], psi, s->P)) != GD_OK) return rc;
+        if (gamma && (rc = download_planes(s, s->gam, gamma, 1)) != GD_OK) return rc;
+    }
     if (psi || gamma) GD_HIP(hipStreamSynchronize(s->stream));
     if (step) *step = s->steps_done;
     return GD_OK;

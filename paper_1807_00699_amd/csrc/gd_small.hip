@@ -13,6 +13,7 @@
 // Np = 128 the waves of a trajectory exchange amplitudes through LDS, with one
 // barrier.  Ising N = 64, R = 100: 0.26 us per step (0.66 with J and the
 // amplitudes read from LDS by 256-thread workgroups).
+#include "gd_check.h"
 #include "gd_epilogue.h"
 #include "gd_readout.h"
 
@@ -71,12 +72,12 @@ __device__ inline float dot64(const float (&w)[64], float x) {
 
 // `steps` Euler or RK4 steps (Eq. (main, gamma), as in gd_epilogue.h) of
 // trajectory blockIdx.x, then the noise increment of step t0 + k after step k
-// (key derived from `seed` as on the host).  With E: the Eq. (h) energy of the
+// (key derived from `seed` as on the host).  With ce.E: the Eq. (h) energy of the
 // final state's readout (ro, clock order q), E_r = sum_i [-(d0_i T0_i + w d1_i
 // T1_i) + g_i d0_i], T = J d in FP32, the terms in FP64 in a fixed tree.
 template <bool CPLX, int NPX, bool RK4>
 __global__ void __launch_bounds__(64 * (NPX / 64) * (CPLX && NPX == 128 ? 2 : 1))
-small_step_k(DenseStepArgs a, int steps, unsigned long long seed, long long t0, int ro, int q, double *E) {
+small_step_k(DenseStepArgs a, int steps, unsigned long long seed, long long t0, int ro, int q, CheckEnd ce) {
     constexpr int NB = NPX / 64;
     constexpr bool SPLIT = CPLX && NPX == 128;   // a wave holds one plane of its spins
     constexpr int NC = CPLX && !SPLIT ? 2 : 1;   // amplitude components held by a lane
@@ -201,8 +202,8 @@ small_step_k(DenseStepArgs a, int steps, unsigned long long seed, long long t0, 
     }
     if (p == 0) a.gam_out[idx] = g;
     // non-finite values persist once they appear, so the final state tells
-    if (bad) a.flags[r] = 1;
-    if (E) {
+    if (bad) store_agent(a.flags + r, 1);
+    if (ce.E) {
         double d0 = 0.0, d1 = 0.0;
         int k;
         const float x = SPLIT && p ? oth : v[0], y = CPLX ? (SPLIT ? (p ? v[0] : oth) : v[NC - 1]) : 0.0f;
@@ -220,7 +221,7 @@ small_step_k(DenseStepArgs a, int steps, unsigned long long seed, long long t0, 
 #pragma unroll
         for (int m = 32; m >= 1; m >>= 1) term += __shfl_xor(term, m);
         if constexpr (W == 1) {
-            if (lane == 0) E[r] = term;
+            if (lane == 0) store_agent(ce.E + r, term);
         } else {
             if (lane == 0) red[wave] = term;
             __syncthreads();
@@ -228,10 +229,12 @@ small_step_k(DenseStepArgs a, int steps, unsigned long long seed, long long t0, 
                 double s = red[0];
 #pragma unroll
                 for (int u = 1; u < W; ++u) s += red[u];
-                E[r] = s;
+                store_agent(ce.E + r, s);
             }
         }
     }
+    // the end of a check or a run: by the last trajectory
+    if ((ce.E || ce.out) && last_arrival(ce.count, gridDim.x)) check_end(ce);
 }
 
 #undef GD_FMAC4
@@ -246,12 +249,13 @@ hipError_t launch_small_couplings(const float *J, float *out, int Np, hipStream_
 }
 
 hipError_t launch_small_steps(bool complex_mode, bool rk4, const DenseStepArgs &a, int steps,
-                              unsigned long long seed, long long t0, int readout, int q, double *E,
+                              unsigned long long seed, long long t0, int readout, int q, const CheckEnd &c,
                               hipStream_t st) {
     if (steps < 1 || (a.Np != 64 && a.Np != 128) || a.R < 1 || a.R > a.Rp) return hipErrorInvalidValue;
-    if (E && readout == RO_CLOCK && (q < 2 || q > 8)) return hipErrorInvalidValue;
+    if (c.E && readout == RO_CLOCK && (q < 2 || q > 8)) return hipErrorInvalidValue;
+    if ((c.E || c.out) && (c.R != a.R || !c.count)) return hipErrorInvalidValue;
     const int waves = a.Np / 64 * (complex_mode && a.Np == 128 ? 2 : 1);
-#define GD_SMALL(C, N, K) small_step_k<C, N, K><<<a.R, 64 * waves, 0, st>>>(a, steps, seed, t0, readout, q, E)
+#define GD_SMALL(C, N, K) small_step_k<C, N, K><<<a.R, 64 * waves, 0, st>>>(a, steps, seed, t0, readout, q, c)
     if (a.Np == 64) {
         if (complex_mode) { if (rk4) GD_SMALL(true, 64, true); else GD_SMALL(true, 64, false); }
         else { if (rk4) GD_SMALL(false, 64, true); else GD_SMALL(false, 64, false); }
