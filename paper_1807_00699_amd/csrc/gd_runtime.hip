@@ -155,7 +155,7 @@ struct gd_solver {
     gd_params prm{};
     double s = 1.0;
     bool j_integer = false, g_integer = true;
-    bool j_sums24 = false;     // every row of |J| sums to less than 2^24
+    bool j_sums24 = false;     // if J is integer and exact in FP8: every row of |J| sums to less than 2^24
     hipStream_t stream = nullptr;
     bool own_stream = false;
     int device = 0;
@@ -944,9 +944,8 @@ int gd_create(gd_solver **out, int32_t n, const float *J, const float *g, int32_
         if (!all_finite(hg)) return bail(fail(GD_E_NONFINITE, "g has non-finite entries"));
     }
     double ss = 0.0;
-    bool integer = true, sums24 = true;
-    for (int i = 0; i < n; ++i) {
-        double row = 0.0;
+    bool integer = true;
+    for (int i = 0; i < n; ++i)
         for (int j = 0; j < n; ++j) {
             if (i == j) continue;
             const float v = hj[(size_t)i * n + j];
@@ -956,13 +955,17 @@ int gd_create(gd_solver **out, int32_t n, const float *J, const float *g, int32_
                 return bail(fail(GD_E_NOT_SYMMETRIC, buf));
             }
             ss += double(v) * double(v);
-            row += std::fabs(double(v));
             integer = integer && (v == std::nearbyint(v));
         }
-        sums24 = sums24 && row < 16777216.0;
-    }
     s->j_integer = integer;
-    s->j_sums24 = sums24;
+    // (FP8 couplings are at most 448 in magnitude)
+    s->j_sums24 = integer;
+    for (int i = 0; i < n && s->j_sums24 && n > 16777216 / 448; ++i) {
+        double row = 0.0;
+        for (int j = 0; j < n; ++j)
+            if (j != i) row += std::fabs(double(hj[(size_t)i * n + j]));
+        s->j_sums24 = row < 16777216.0;
+    }
     for (float v : hg) s->g_integer = s->g_integer && (v == std::nearbyint(v));
     s->s = prm.j_scale > 0 ? prm.j_scale : std::sqrt(ss / n);
     if (!(s->s > 0)) s->s = 1.0;
