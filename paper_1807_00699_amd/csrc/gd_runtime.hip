@@ -528,6 +528,9 @@ bool sign_readout(const gd_solver *s) {
 // Partial energies of the current state into s->partial, `ntiles` row tiles:
 // the device check path
 int device_energies(gd_solver *s, int *ntiles) {
+    // (the matrix-vector kernels read J row-major)
+    const int rc = s->cfg.id < kGemvBase || s->cfg.id >= kFewBase ? tile_couplings(s) : GD_OK;
+    if (rc != GD_OK) return rc;
     DenseStepArgs a = base_args(s);
     if (s->op == OP_F32 && s->cfg.id < kGemvBase && sign_readout(s)) {
         a.J = s->dJt;
@@ -1201,7 +1204,7 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     const bool rk4 = s->integrator() == GD_RK4;
     const bool small_ok = !s->mod() && s->op == OP_F32 && s->Np <= 128 &&
                           std::getenv("GD_DENSE_CONFIG") == nullptr;
-    if (!small_ok && !s->mod() && (s->persist < 0 || ci > 0) && (rc = tile_couplings(s)) != GD_OK) return rc;
+    if (!small_ok && !s->mod() && s->persist < 0 && (rc = tile_couplings(s)) != GD_OK) return rc;
     // The matrix-vector kernels of few trajectories run for microseconds, so
     // they are always replayed from graphs (with GD_F_PROFILE one event pair
     // brackets each replay and its launches, in-graph dispatch gaps included).
@@ -1457,8 +1460,8 @@ static int energies(gd_solver *s, double *E, int32_t *best, bool fp64) {
     // and the terms in FP64, in any order, so the FP8 path gives the FP64
     // re-score's numbers (N = R = 4096: 0.16 ms against 2.4 ms)
     const bool exact = fp64 && sign_readout(s) && s->j_integer && s->j_sums24 && s->g_integer;
-    if ((!fp64 || exact) && (rc = tile_couplings(s)) != GD_OK) return rc;
     if (exact) {
+        if ((rc = tile_couplings(s)) != GD_OK) return rc;
         DenseStepArgs a = base_args(s);
         a.J = s->dJt;
         a.B = a.psi_in = s->psi[s->cur];

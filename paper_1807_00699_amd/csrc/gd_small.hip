@@ -251,7 +251,7 @@ hipError_t launch_small_couplings(const float *J, float *out, int Np, hipStream_
 hipError_t launch_small_steps(bool complex_mode, bool rk4, const DenseStepArgs &a, int steps,
                               unsigned long long seed, long long t0, int readout, int q, const CheckEnd &c,
                               hipStream_t st) {
-    if (steps < 1 || (a.Np != 64 && a.Np != 128) || a.R < 1 || a.R > a.Rp) return hipErrorInvalidValue;
+    if (!a.J || steps < 1 || (a.Np != 64 && a.Np != 128) || a.R < 1 || a.R > a.Rp) return hipErrorInvalidValue;
     if (c.E && readout == RO_CLOCK && (q < 2 || q > 8)) return hipErrorInvalidValue;
     if ((c.E || c.out) && (c.R != a.R || !c.count)) return hipErrorInvalidValue;
     const int waves = a.Np / 64 * (complex_mode && a.Np == 128 ? 2 : 1);

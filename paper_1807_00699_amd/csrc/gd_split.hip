@@ -75,7 +75,7 @@ DenseConfig split_config(bool complex_mode, bool j_fp8, int idx) {
 hipError_t launch_split_step(const DenseConfig &cfg, bool complex_mode, int mode, bool j_fp8, const DenseStepArgs &a,
                              hipStream_t st) {
     const int idx = cfg.id >= kFewBase ? cfg.id - kFewBase : cfg.id;
-    if (idx < 0 || idx >= split_config_count()) return hipErrorInvalidValue;
+    if (!a.J || idx < 0 || idx >= split_config_count()) return hipErrorInvalidValue;
     if (j_fp8) return complex_mode ? launch_split_j8_cx(idx, mode, a, st) : launch_split_j8_re(idx, mode, a, st);
     return complex_mode ? launch_split_j3_cx(idx, mode, a, st) : launch_split_j3_re(idx, mode, a, st);
 }
@@ -87,7 +87,7 @@ DenseConfig split_lp_config(bool complex_mode, int idx) {
 }
 
 hipError_t launch_split_lp(int idx, bool complex_mode, int mode, int op, const DenseStepArgs &a, hipStream_t st) {
-    if (op != OP_BF16 && op != OP_F16) return hipErrorInvalidValue;
+    if (!a.J || (op != OP_BF16 && op != OP_F16)) return hipErrorInvalidValue;
     return complex_mode ? launch_split_lp_cx(idx, mode, op, a, st) : launch_split_lp_re(idx, mode, op, a, st);
 }
 
@@ -100,6 +100,7 @@ int sign_energy_row_tile(int Np, int R) {
 }
 
 hipError_t launch_sign_energy(const DenseStepArgs &a, hipStream_t st) {
+    if (!a.J) return hipErrorInvalidValue;
     const int t = sign_energy_row_tile(a.Np, a.R);
     return launch_split_sign(t == 256 ? 3 : t == 128 ? 2 : t == 64 ? 1 : 0, a, st);
 }
