@@ -341,7 +341,12 @@ def bench_gdmod(args, wl, steps):
     Np = -(-n // 64) * 64
     launches = st.kernel_launches - st0.kernel_launches
     avg_s = (st.kernel_ms - st0.kernel_ms) / 1e3 / max(launches, 1)
-    bytes_launch = R * Np * Np * 8.0 + R * Np * (2 * 2 + 2) * 4.0
+    # K read and written: both triangles, or (from R Np^2 = 2.5e7 on) the 64 x 64
+    # tiles of one and the partial sums of the tile rows
+    nt = Np // 64
+    packed = R * Np * Np >= 25_000_000
+    bytes_launch = R * Np * (2 * 2 + 2) * 4.0 + R * (nt * (nt + 1) / 2 * (4096 * 8.0 + 2 * 64 * 8.0) if packed
+                                                     else Np * Np * 8.0)
     achieved = bytes_launch / avg_s / 1e9
     out = {
         "metric": "spin-updates/s (N*R*steps/s)", "value": n * R * steps / el, "unit": "spin-updates/s",
@@ -351,7 +356,7 @@ def bench_gdmod(args, wl, steps):
         "config": {"workload": wl["desc"], "n": n, "R": R, "integrator": "euler", "dt": wl["dt"],
                    "gamma_c": gc, "energy_check_every": args.check},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                     "frac": achieved / PEAK_HBM_GBS, "traffic": None, "kernel": "gdmod_euler_k",
+                     "frac": achieved / PEAK_HBM_GBS, "traffic": None, "kernel": "gdmod_sym_k" if packed else "gdmod_euler_k",
                      "launches": int(launches), "avg_launch_us": avg_s * 1e6,
                      "bytes_per_launch": bytes_launch},
         "best_energy": float(E[best]),
