@@ -510,25 +510,42 @@ __global__ void __launch_bounds__(MFT, 2) mlp_forward_mfma_k(const MlpPacked *__
 }
 
 // per instance: sigma_k (flip alignment), then the targets sigma_k s_i of its
-// rows, so that the training kernel reads one number per row
-__global__ void __launch_bounds__(256) mlp_segment_k(const float *__restrict__ out, const float *__restrict__ lab,
+// rows, so that the training kernel reads one number per row.  Bound by the
+// FP64 tanh of each thread's rows, one after the other: 64 instances of about
+// 1100 rows 6.7 us (9.1 with 256 threads)
+constexpr int ST = 1024;
+__global__ void __launch_bounds__(ST) mlp_segment_k(const float *__restrict__ out, const float *__restrict__ lab,
                                                     const int *__restrict__ seg, float *__restrict__ target) {
-    __shared__ double red[4 * 2];
+    __shared__ double red[ST / 64][2];
     __shared__ float sg;
     const int k = blockIdx.x;
     const int i0 = seg[k], i1 = seg[k + 1];
     double v[2] = {0.0, 0.0};
-    for (int i = i0 + threadIdx.x; i < i1; i += 256) {
+    for (int i = i0 + threadIdx.x; i < i1; i += ST) {
         const double m = tanh((double)out[2 * i]);
         const double s = lab[i];
         v[0] += (m - s) * (m - s);
         v[1] += (m + s) * (m + s);
     }
-    block_sum<2>(v, red);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        v[0] += __shfl_xor(v[0], o);
+        v[1] += __shfl_xor(v[1], o);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6][0] = v[0];
+        red[threadIdx.x >> 6][1] = v[1];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int w = 1; w < ST / 64; ++w) {
+            v[0] += red[w][0];
+            v[1] += red[w][1];
+        }
     if (threadIdx.x == 0) sg = v[0] <= v[1] ? 1.0f : -1.0f;
     __syncthreads();
     const float sigma = sg;
-    for (int i = i0 + threadIdx.x; i < i1; i += 256) target[i] = sigma * lab[i];
+    for (int i = i0 + threadIdx.x; i < i1; i += ST) target[i] = sigma * lab[i];
 }
 
 // Training step on the matrix cores (v_mfma_f32_32x32x2_f32, FP32 products
@@ -548,8 +565,11 @@ __global__ void __launch_bounds__(256) mlp_segment_k(const float *__restrict__ o
 // is then one conflict-free LDS read per lane, W2 in rows of 65 words so that
 // both its row and its column order read across banks).
 // The accumulators stay in registers over all of the wave's tiles; at the
-// end the four waves of a workgroup add theirs into one partial in a fixed
-// order (partial[block][param], loss_part[block]).  Without TRAIN the kernel
+// end the four waves of a workgroup leave theirs in LDS and the threads add
+// them in a fixed order (partial[block][param], loss_part[block]).  One
+// minibatch of 64 instances (73 k rows): 44.5 us, the forward pass alone 16.2
+// (52.7 and 21.4 with the weights staged load by load and the waves adding
+// their partials in turn).  Without TRAIN the kernel
 // only writes the two outputs of every spin.
 constexpr int TT = 256;           // 4 waves
 constexpr int PS = 65;            // padded row of W2 and of the transposition buffers
@@ -557,7 +577,8 @@ constexpr int PS = 65;            // padded row of W2 and of the transposition b
 // (training) the transposition buffers of the four waves
 constexpr int kWLds = F * H + H * PS + 2 * H + H * NO;
 constexpr size_t kFwdLds = (size_t)kWLds * 4;
-constexpr size_t kTrainLds = (size_t)(kWLds + 4 * 2 * 32 * PS) * 4;
+constexpr size_t kTrainLds =
+    std::max((size_t)(kWLds + 4 * 2 * 32 * PS) * 4, (size_t)4 * NPAR * 4 + 4 * 8);   // or the waves' partials
 
 __device__ inline void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -575,26 +596,6 @@ __device__ __forceinline__ void mlp_mfma32(const MlpTrainArgs &a, float *smem) {
     float *B1s = W2s + H * PS, *B2s = B1s + H, *W3s = B2s + H;
     float *P = smem + kWLds + (size_t)w * 2 * 32 * PS;        // this wave's buffers
     float *Q = P + 32 * PS;
-    for (int q = tid; q < F * H; q += TT) W1s[q] = p[OFF_W1 + q];
-    for (int q = tid; q < H * H; q += TT) W2s[(q / H) * PS + q % H] = p[OFF_W2 + q];
-    for (int q = tid; q < H; q += TT) {
-        B1s[q] = p[OFF_B1 + q];
-        B2s[q] = p[OFF_B2 + q];
-    }
-    for (int q = tid; q < H * NO; q += TT) W3s[q] = p[OFF_W3 + q];
-    __syncthreads();
-    f32x16_t g2[4], g1[2];               // dW2 blocks (j-block, b-block), dW1 blocks (j-block)
-    float gb1 = 0.f, gb2 = 0.f, gw30 = 0.f, gw31 = 0.f, gb30 = 0.f, gb31 = 0.f;
-    double lsum = 0.0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int k = 0; k < 16; ++k) g2[u][k] = 0.f;
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-        for (int k = 0; k < 16; ++k) g1[u][k] = 0.f;
-    const float invM = 1.0f / float(a.M);
     const float b30 = p[OFF_B3], b31 = p[OFF_B3 + 1];
     const int ntiles = (a.M + 31) / 32;
     const int tstride = gridDim.x * (TT / 64);
@@ -610,6 +611,40 @@ __device__ __forceinline__ void mlp_mfma32(const MlpTrainArgs &a, float *smem) {
     float xn[F / 2];
     int t = blockIdx.x * (TT / 64) + w;
     load_x(t, xn);
+    // the weights, all loads in flight together (and the first tile's rows)
+    static_assert(F * H % TT == 0 && H * H % TT == 0 && TT >= H * NO, "whole loads per thread");
+    float w1[F * H / TT], w2[H * H / TT], wb1 = 0.f, wb2 = 0.f, w3 = 0.f;
+#pragma unroll
+    for (int u = 0; u < F * H / TT; ++u) w1[u] = p[OFF_W1 + u * TT + tid];
+#pragma unroll
+    for (int u = 0; u < H * H / TT; ++u) w2[u] = p[OFF_W2 + u * TT + tid];
+    if (tid < H) {
+        wb1 = p[OFF_B1 + tid];
+        wb2 = p[OFF_B2 + tid];
+    }
+    if (tid < H * NO) w3 = p[OFF_W3 + tid];
+#pragma unroll
+    for (int u = 0; u < F * H / TT; ++u) W1s[u * TT + tid] = w1[u];
+#pragma unroll
+    for (int u = 0; u < H * H / TT; ++u) W2s[((u * TT + tid) / H) * PS + tid % H] = w2[u];
+    if (tid < H) {
+        B1s[tid] = wb1;
+        B2s[tid] = wb2;
+    }
+    if (tid < H * NO) W3s[tid] = w3;
+    __syncthreads();
+    f32x16_t g2[4], g1[2];               // dW2 blocks (j-block, b-block), dW1 blocks (j-block)
+    float gb1 = 0.f, gb2 = 0.f, gw30 = 0.f, gw31 = 0.f, gb30 = 0.f, gb31 = 0.f;
+    double lsum = 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) g2[u][k] = 0.f;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) g1[u][k] = 0.f;
+    const float invM = 1.0f / float(a.M);
     for (; t < ntiles; t += tstride) {
         const int m = t * 32 + c;
         const bool ok = m < a.M;
@@ -767,42 +802,42 @@ __device__ __forceinline__ void mlp_mfma32(const MlpTrainArgs &a, float *smem) {
         }
     }
     if constexpr (TRAIN) {
-        // the workgroup's partial: the waves add theirs in order (wave 0 writes)
+        // the workgroup's partial: every wave leaves its sums in LDS (over the
+        // weights and the transposition buffers), then each thread adds the
+        // four of its parameters in wave order
         for (int q = 1; q < 64; q <<= 1) lsum += __shfl_xor(lsum, q);
         __syncthreads();
-        float *R = smem + kWLds;                        // NPAR floats, then 4 doubles
-        double *RL = reinterpret_cast<double *>(R + ((NPAR + 1) & ~1));
-        for (int v = 0; v < TT / 64; ++v) {
-            if (w == v) {
-                auto put = [&](int q, float val) { R[q] = v == 0 ? val : R[q] + val; };
+        float *R = smem + w * NPAR;
+        double *RL = reinterpret_cast<double *>(smem + 4 * NPAR);
+        static_assert(TT == 256 && NPAR % 2 == 0, "four waves; the losses are aligned");
+        auto put = [&](int q, float val) { R[q] = val; };
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-                    for (int k = 0; k < 16; ++k) {
-                        const int j = 32 * (u >> 1) + 8 * (k / 4) + 4 * h + k % 4, b = 32 * (u & 1) + c;
-                        put(OFF_W2 + j * H + b, g2[u][k]);
-                    }
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int k = 0; k < 16; ++k) {
-                        const int f = 8 * (k / 4) + 4 * h + k % 4, j = 32 * u + c;
-                        if (f < F) put(OFF_W1 + f * H + j, g1[u][k]);
-                    }
-                put(OFF_B1 + lane, gb1);
-                put(OFF_B2 + lane, gb2);
-                put(OFF_W3 + lane * NO, gw30);
-                put(OFF_W3 + lane * NO + 1, gw31);
-                if (lane == 0) {
-                    put(OFF_B3, gb30);
-                    put(OFF_B3 + 1, gb31);
-                    RL[v] = lsum;
-                }
+            for (int k = 0; k < 16; ++k) {
+                const int j = 32 * (u >> 1) + 8 * (k / 4) + 4 * h + k % 4, b = 32 * (u & 1) + c;
+                put(OFF_W2 + j * H + b, g2[u][k]);
             }
-            __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int f = 8 * (k / 4) + 4 * h + k % 4, j = 32 * u + c;
+                if (f < F) put(OFF_W1 + f * H + j, g1[u][k]);
+            }
+        put(OFF_B1 + lane, gb1);
+        put(OFF_B2 + lane, gb2);
+        put(OFF_W3 + lane * NO, gw30);
+        put(OFF_W3 + lane * NO + 1, gw31);
+        if (lane == 0) {
+            put(OFF_B3, gb30);
+            put(OFF_B3 + 1, gb31);
+            RL[w] = lsum;
         }
+        __syncthreads();
         float *part = a.partial + (long long)blockIdx.x * NPAR;
-        for (int q = tid; q < NPAR; q += TT) part[q] = R[q];
+        for (int q = tid; q < NPAR; q += TT)
+            part[q] = ((smem[q] + smem[NPAR + q]) + smem[2 * NPAR + q]) + smem[3 * NPAR + q];
         if (tid == 0) a.loss_part[blockIdx.x] = ((RL[0] + RL[1]) + RL[2]) + RL[3];
     }
 }
@@ -941,7 +976,7 @@ hipError_t launch_mlp_train_step(const MlpTrainArgs &a, int K, int nparts, float
     const int ntiles = (a.M + 31) / 32;
     const int gw = (ntiles + TT / 64 - 1) / (TT / 64);
     mlp_forward_mfma32_k<<<std::min(gw, 2048), TT, kFwdLds, st>>>(a);
-    mlp_segment_k<<<K, 256, 0, st>>>(a.out, a.labels, a.seg, a.target);
+    mlp_segment_k<<<K, ST, 0, st>>>(a.out, a.labels, a.seg, a.target);
     const int np = std::max(1, std::min(nparts, gw));
     mlp_train_mfma_k<<<np, TT, kTrainLds, st>>>(a);
     mlp_adam_k<<<(NPAR + AP - 1) / AP + 1, AT, 0, st>>>(a, np, lr, step);
