@@ -137,6 +137,37 @@ discretise_k(const float *__restrict__ psi, float *__restrict__ D, void *shadowD
     }
 }
 
+// int8 spins of real amplitudes alone, n a multiple of 4: four spins per load
+// and store, four of those in flight per thread.  Bound by HBM: N = R = 4096
+// 14 us (discretise_k 36, one load per thread).
+__global__ void __launch_bounds__(256)
+sign_spins_k(const float *__restrict__ psi, unsigned *__restrict__ spins, int *__restrict__ flags, int n, int R, int Np) {
+    const unsigned nq = n / 4, total = nq * (unsigned)R;   // (the launcher's limit: below 2^31)
+    constexpr int U = 4;
+    const unsigned q0 = blockIdx.x * (256u * U) + threadIdx.x;
+    f32x4 x[U];
+    unsigned r[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const unsigned q = min(q0 + u * 256u, total - 1);
+        r[u] = q / nq;
+        x[u] = *reinterpret_cast<const f32x4 *>(psi + (long long)r[u] * Np + 4 * (q - r[u] * nq));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (q0 + u * 256u >= total) break;
+        unsigned w = 0;
+        bool nan = false;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            w |= (x[u][e] < 0.0f ? 0xFFu : 1u) << 8 * e;
+            nan |= __builtin_isnan(x[u][e]);
+        }
+        spins[q0 + u * 256u] = w;
+        if (nan) flags[r[u]] = 1;
+    }
+}
+
 // E[r] = sum over row tiles in fixed order (one thread per trajectory).
 __global__ void energy_sum_k(const double *__restrict__ partial, int ntiles, int Rp, int R,
                              double *__restrict__ E) {
@@ -322,6 +353,13 @@ hipError_t launch_discretise(const float *psi, float *D, void *shadowD, int op, 
                              int Np, int Rp, int nplanes, long long plane_stride, hipStream_t st) {
     if (readout == RO_CLOCK && (q < 2 || q > 8)) return hipErrorInvalidValue;
     if (Np % 4) return hipErrorInvalidValue;
+    const long long quads = (long long)(n / 4) * R;
+    if (spins8 && !D && !shadowD && !angle && !states && readout == RO_SIGN && nplanes == 1 && n % 4 == 0 &&
+        reinterpret_cast<uintptr_t>(spins8) % 4 == 0 && quads < (1ll << 31)) {
+        sign_spins_k<<<unsigned((quads + 1023) / 1024), 256, 0, st>>>(psi, reinterpret_cast<unsigned *>(spins8), flags, n, R,
+                                                                     Np);
+        return hipGetLastError();
+    }
     const dim3 grid(unsigned(std::min(64, (Np / 4 + 255) / 256)), unsigned(std::min(Rp, 65535)));
     discretise_k<<<grid, 256, 0, st>>>(psi, D, shadowD, op, readout, q, spins8,
                                                               angle, states, flags, n, R, Np, Rp,

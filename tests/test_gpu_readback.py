@@ -49,3 +49,15 @@ def test_device_readback_equals_host(n, R, model):
                 assert np.all(a[:off] == pad) and np.all(a[off + want.size:] == pad)
     finally:
         gd.gd_destroy(h)
+
+
+@pytest.mark.parametrize("n,R", [(4, 1), (60, 3), (64, 100), (66, 5), (256, 33), (1100, 257)])
+def test_int8_spins_are_the_signs(n, R):
+    """Whole words of spins (n a multiple of 4) and single bytes; +-0 reads as
+    +1, subnormal amplitudes by their sign."""
+    rng = np.random.default_rng([n, R])
+    x = (np.where(rng.random((R, n)) < 0.5, -1.0, 1.0) * rng.choice([1.0, 0.25, 1e-41, 0.0], (R, n))).astype(np.float32)
+    with gd.Solver(I.dense_pm1(n, 2)) as S:
+        S.set_state(x, np.zeros((R, n), np.float32))
+        sp = S.spins()
+    assert np.array_equal(sp, np.where(x < 0, -1, 1).astype(np.int8))
