@@ -189,10 +189,10 @@ __global__ void __launch_bounds__(64) energy_sum_wide_k(const double *__restrict
 #pragma unroll
     for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m);
     if (lane == 0) store_agent(c.E + r, s);
-    if (last_arrival(c.count, c.R)) check_end(c);
+    if (c.count && last_arrival(c.count, c.R)) check_end(c);
 }
 
-__global__ void __launch_bounds__(1024) check_end_k(CheckEnd c) { check_end(c); }
+__global__ void __launch_bounds__(1024) check_end_k(CheckEnd c) { check_end<4>(c); }
 
 // FP64 re-score of Eq. (h) for the discretised state, formed in FP64 from
 // the FP32 amplitudes by the readout of the model.  The readout planes are
@@ -372,8 +372,11 @@ hipError_t launch_energy_reduce(const double *partial, int ntiles, int Rp, const
     // one thread per trajectory reads its tiles one after the other: N = 800,
     // R = 100 (26 tiles) 7.3 us
     if (c.R <= 512 && ntiles >= 8) {
-        energy_sum_wide_k<<<c.R, 64, 0, st>>>(partial, ntiles, Rp, c);
-        return hipGetLastError();
+        CheckEnd z = c;
+        if (c.R > kEndRows) z.count = nullptr;
+        energy_sum_wide_k<<<c.R, 64, 0, st>>>(partial, ntiles, Rp, z);
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess && !z.count ? launch_check_end(c, st) : e;
     }
     energy_sum_k<<<(c.R + 255) / 256, 256, 0, st>>>(partial, ntiles, Rp, c.R, c.E);
     return launch_check_end(c, st);

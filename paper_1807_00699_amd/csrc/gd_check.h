@@ -1,11 +1,17 @@
 // The end of an energy check or of a run, done by the last workgroup to finish
 // of the kernel that formed its inputs, instead of a kernel of its own
 // (3-5 us each with its launch; Ising N = 64, R = 100, 100 steps and two checks:
-// 66 us with four such kernels).
+// 66 us with four such kernels).  Up to kEndRows trajectories: every arrival is
+// an atomic on one word (14 ns each), and one wave reads the trajectories'
+// results.  Ising N = 64, 20 steps, a check every two: R = 64 75 us so, 86 with a
+// launch for every end; R = 200 88-92 and 77-100 (the host's time to launch);
+// R = 400 114-122 and 76-102; R = 4000 628 and 120.
 #pragma once
 #include "gd_internal.h"
 
 namespace gd {
+
+constexpr int kEndRows = 256;
 
 // stores that the last workgroup reads (any CU, in the same launch)
 __device__ inline void store_agent(double *p, double v) {
@@ -32,21 +38,33 @@ __device__ inline bool last_arrival(unsigned *count, unsigned total) {
 
 // By one workgroup of whole waves (at most 16): with c.E, b = argmin_r E[r]
 // (ties: the lowest r) into best, E[b] into best_e and trace, and the running
-// best; with c.out, what the host reads at the end of a run.
+// best; with c.out, what the host reads at the end of a run.  A thread has the
+// loads of U trajectories in flight.
+template <int U = 1>
 __device__ inline void check_end(const CheckEnd &c) {
     __shared__ double se[16];
     __shared__ int si[16], sc[16];
     double bv = __builtin_inf();
     int bi = 0x7fffffff, bad = 0;
-    for (int r = threadIdx.x; r < c.R; r += blockDim.x) {
-        if (c.E) {
-            const double s = __hip_atomic_load(c.E + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (s < bv || (s == bv && r < bi)) {
-                bv = s;
+    for (int r0 = threadIdx.x; r0 < c.R; r0 += U * blockDim.x) {
+        double s[U];
+        int f[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = min(r0 + u * int(blockDim.x), c.R - 1);
+            s[u] = c.E ? __hip_atomic_load(c.E + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : bv;
+            f[u] = c.out ? __hip_atomic_load(c.flags + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int r = r0 + u * int(blockDim.x);
+            if (r >= c.R) break;
+            if (c.E && (s[u] < bv || (s[u] == bv && r < bi))) {
+                bv = s[u];
                 bi = r;
             }
+            bad += f[u] != 0;
         }
-        if (c.out) bad += __hip_atomic_load(c.flags + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
     }
     auto merge = [&](double ov, int oi, int ob) {
         if (ov < bv || (ov == bv && oi < bi)) {

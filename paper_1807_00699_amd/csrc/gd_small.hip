@@ -233,8 +233,8 @@ small_step_k(DenseStepArgs a, int steps, unsigned long long seed, long long t0, 
             }
         }
     }
-    // the end of a check or a run: by the last trajectory
-    if ((ce.E || ce.out) && last_arrival(ce.count, gridDim.x)) check_end(ce);
+    // the end of a check or a run: by the last trajectory, unless a launch follows for it
+    if (ce.count && last_arrival(ce.count, gridDim.x)) check_end(ce);
 }
 
 #undef GD_FMAC4
@@ -255,7 +255,10 @@ hipError_t launch_small_steps(bool complex_mode, bool rk4, const DenseStepArgs &
     if (c.E && readout == RO_CLOCK && (q < 2 || q > 8)) return hipErrorInvalidValue;
     if ((c.E || c.out) && (c.R != a.R || !c.count)) return hipErrorInvalidValue;
     const int waves = a.Np / 64 * (complex_mode && a.Np == 128 ? 2 : 1);
-#define GD_SMALL(C, N, K) small_step_k<C, N, K><<<a.R, 64 * waves, 0, st>>>(a, steps, seed, t0, readout, q, c)
+    CheckEnd z = c;
+    const bool own_end = (c.E || c.out) && a.R > kEndRows;
+    if (own_end || !(c.E || c.out)) z.count = nullptr;
+#define GD_SMALL(C, N, K) small_step_k<C, N, K><<<a.R, 64 * waves, 0, st>>>(a, steps, seed, t0, readout, q, z)
     if (a.Np == 64) {
         if (complex_mode) { if (rk4) GD_SMALL(true, 64, true); else GD_SMALL(true, 64, false); }
         else { if (rk4) GD_SMALL(false, 64, true); else GD_SMALL(false, 64, false); }
@@ -264,7 +267,8 @@ hipError_t launch_small_steps(bool complex_mode, bool rk4, const DenseStepArgs &
         else { if (rk4) GD_SMALL(false, 128, true); else GD_SMALL(false, 128, false); }
     }
 #undef GD_SMALL
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    return e == hipSuccess && own_end ? launch_check_end(c, st) : e;
 }
 
 }  // namespace gd
