@@ -189,8 +189,15 @@ typedef struct gd_run_stats {
                                  fused multi-step kernel instead of the variants; larger
                                  ones whose couplings fit the registers of the chip (FP32,
                                  no pinned variant, not GD_F_ASYNC) run all steps of a call
-                                 in persistent kernels (ids from 200 on, once run).
-                                 Batches
+                                 in persistent kernels (ids from 200 on, once run).  Their
+                                 workgroups wait for each other: where the runtime refuses
+                                 such a launch (another process has one), or a kernel of
+                                 another stream keeps a compute unit for more than 2 s
+                                 (GD_PERSIST_WAIT=<microseconds>), the run goes on from the
+                                 last state with one launch per step, in the summation
+                                 order of those kernels, until the next set-up.
+                                 GD_PERSIST=<k> allows k persistent launches after a set-up
+                                 (0: none).  Batches
                                  of instances: the same with GD_BATCH_CONFIG=<id>; the
                                  variants with per-instance item widths also relabel each
                                  instance's spins at set-up (host threads, deterministic,

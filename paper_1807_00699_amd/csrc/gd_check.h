@@ -17,6 +17,9 @@ constexpr int kEndRows = 256;
 __device__ inline void store_agent(double *p, double v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ inline void store_agent(long long *p, long long v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ inline void store_agent(int *p, int v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -38,7 +41,8 @@ __device__ inline bool last_arrival(unsigned *count, unsigned total) {
 
 // By one workgroup of whole waves (at most 16): with c.E, b = argmin_r E[r]
 // (ties: the lowest r) into best, E[b] into best_e and trace, and the running
-// best; with c.out, what the host reads at the end of a run.  A thread has the
+// best; with c.out, what the host reads at the end of a run.  Energies of steps
+// that were not taken (*c.stalled) read as NaN, below no target and no best.  A thread has the
 // loads of U trajectories in flight.
 template <int U = 1>
 __device__ inline void check_end(const CheckEnd &c) {
@@ -83,6 +87,7 @@ __device__ inline void check_end(const CheckEnd &c) {
     __syncthreads();
     if (threadIdx.x != 0) return;
     for (unsigned w = 1; w < blockDim.x / 64; ++w) merge(se[w], si[w], sc[w]);
+    const long long stalled = c.stalled ? __hip_atomic_load(c.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     double run = c.first ? c.e0 : 0.0;
     int run_i = c.i0;
     if (c.run_e && !c.first) {
@@ -91,7 +96,7 @@ __device__ inline void check_end(const CheckEnd &c) {
     }
     if (c.E) {
         const int b = bi == 0x7fffffff ? 0 : bi;
-        const double eb = bi == 0x7fffffff ? __hip_atomic_load(c.E, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : bv;
+        const double eb = stalled ? __builtin_nan("") : bi == 0x7fffffff ? __hip_atomic_load(c.E, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : bv;
         if (c.best) *c.best = b;
         if (c.best_e) *c.best_e = eb;
         if (c.trace) *c.trace = eb;
@@ -106,7 +111,7 @@ __device__ inline void check_end(const CheckEnd &c) {
     }
     if (c.out) {
         c.out->diverged = bad;
-        c.out->stalled = c.stalled ? __hip_atomic_load(c.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        c.out->stalled = stalled;
         if (c.run_e) {
             c.out->best_e = run;
             c.out->best_i = run_i;

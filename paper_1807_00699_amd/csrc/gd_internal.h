@@ -104,7 +104,7 @@ struct RunResult {
     double best_e;   // running best of the checks and its trajectory
     int best_i;
     int diverged;    // trajectories r < R with flags[r] != 0
-    int stalled;     // *stalled, 0 without one
+    long long stalled;   // *stalled, 0 without one
 };
 // The end of an energy check or of a run (gd_check.h)
 struct CheckEnd {
@@ -119,7 +119,7 @@ struct CheckEnd {
     bool first = false;
     double *trace = nullptr;    // the check's entry of the energy trace
     const int *flags = nullptr;
-    const int *stalled = nullptr;
+    const long long *stalled = nullptr;   // PersistArgs::stalled: set, the check's energies are of no state and not taken
     RunResult *out = nullptr;   // end of a run: pinned host memory
     unsigned *count = nullptr;  // workgroups that have arrived, 0 between launches
 };
@@ -129,7 +129,9 @@ struct CheckEnd {
 constexpr int kPersistBase = 200;
 struct PersistArgs {
     unsigned *x;              // exchange buffers (persist_words), empty before the first launch
-    int *stalled;             // set when a workgroup waited longer than `patience`
+    long long *stalled;       // 0; `tag` from the first launch on in which a workgroup waited longer than
+                              // `patience`: it and later ones write no state that a later step reads
+    long long tag;            // of this launch, not 0
     long long base;           // amplitudes published by earlier launches
     long long t0;             // index of the first step (noise)
     unsigned long long seed;  // noise seed

@@ -27,7 +27,10 @@
 //
 // All workgroups have to be resident at once: at most one per CU, launched
 // cooperatively.  A wait longer than `patience` ends the kernel in every
-// workgroup with *stalled set and no state written.
+// workgroup that waits for the others, and sets *stalled; launches that find it
+// set end at their first missing amplitude.  No launch writes the state it
+// reads, so the state at the start of the first of them is there for the host
+// to go on from.
 //
 // Per step, before -> after: Ising Euler N = 4096, R = 1 5.7 -> 2.35 us (FP8
 // couplings), 13.3 -> 3.7 (split couplings); N = 300, R = 64 5.4 -> 2.1; N =
@@ -95,7 +98,8 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
     const int g = blockIdx.x % p.groups, m0 = blockIdx.x / p.groups * ROWS;
     const int nf = a.Np / 32;
     const long long ps = a.plane_stride;
-    if (tid == 0) stalled = 0;
+    const bool gone = tid == 0 && __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    if (tid == 0) stalled = gone;
 
     // this wave's couplings: fragments w, w + 8, ... of 32 columns, RB blocks of 16 rows
     u32x4 j[J8 ? 1 : FR][J8 ? 1 : RB][3];
@@ -305,7 +309,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
             if (CPLX) store1(mark + 16, kEmpty);
         }
     }
-    if (stalled && tid == 0) store_agent(p.stalled, 1);
+    if (stalled && tid == 0 && !gone) store_agent(p.stalled, p.tag);
 #pragma unroll
     for (int k = 0; k < IT && !stalled; ++k) {
         const int i = m0 + lr + k * LSTEP;
@@ -334,7 +338,8 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
     const int nw = blockDim.x / 64;
     const int col = lane & 15, kq = lane >> 4;
     const int m0 = blockIdx.x * 16, Np = a.Np, R = a.R;
-    if (tid == 0) stalled = 0;
+    const bool gone = tid == 0 && __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    if (tid == 0) stalled = gone;
 
     uint2 j8[8];
     u32x4 j[J8 ? 1 : 8][3];
@@ -461,7 +466,7 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
             if (lane < 16) store1(own + ((p.base + ev + 2) & 3) * bsz, kEmpty);
         }
     }
-    if (stalled && tid == 0) store_agent(p.stalled, 1);
+    if (stalled && tid == 0 && !gone) store_agent(p.stalled, p.tag);
     if (inside && lane < 16 && !stalled) {
         a.psi_out[(long long)r * Np + i] = x;
         a.gam_out[(long long)r * Np + i] = gm;
@@ -571,7 +576,7 @@ bool persist_ends_run(int id) { return id >= kFew; }
 
 hipError_t launch_persist(int id, bool cplx, bool rk4, bool j8, const DenseStepArgs &a, const PersistArgs &p,
                           const CheckEnd &ce, hipStream_t st) {
-    if (a.Np % 64 || a.R < 1 || p.steps < 1 || ce.E ||
+    if (a.Np % 64 || a.R < 1 || p.steps < 1 || !p.tag || a.psi_out == a.psi_in || a.gam_out == a.gam_in || ce.E ||
         (ce.out && (!persist_ends_run(id) || ce.R != a.R || !ce.count || !ce.flags)))
         return hipErrorInvalidValue;
     DenseStepArgs x = a;

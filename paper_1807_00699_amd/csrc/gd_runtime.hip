@@ -45,6 +45,11 @@ inline long long round_up(long long x, long long m) { return (x + m - 1) / m * m
 
 constexpr int kTrajAlign = 128;  // Rp granularity: every dense variant tiles it
 constexpr int kProfileEvery = 8;  // GD_F_PROFILE samples the launches of every 8th step
+// Wall-clock ticks (2 s) that a workgroup of a persistent launch waits for the
+// others: the exchange takes microseconds, but workgroups start when the
+// kernels of other streams leave their CUs.  A run that waits longer goes on
+// with one launch per step.
+constexpr long long kPersistPatience = 200000000;
 constexpr int kTraceChecks = 1 << 16;  // device checks kept in the energy trace (512 KiB)
 
 // SplitMix64 (Steele, Lea, Flood 2014) -> uniform double in [0, 1).
@@ -175,10 +180,12 @@ struct gd_solver {
     float *dJs = nullptr;      // FP32 solvers with Np <= 128: J as the fused small-problem kernel reads it
     void *shadow[3] = {nullptr, nullptr, nullptr};   // operand copies of psi[k]
     // persistent steps: variant (-1: one launch per step), exchange buffers
-    // and how many amplitude sets went through them
+    // and how many amplitude sets went through them; launches left before one
+    // launch per step (< 0: no limit), and the wait that ends a launch
     int persist = -1;
     unsigned *xchg = nullptr;
-    int *stalled = nullptr;
+    long long *stalled = nullptr;
+    int64_t persist_left = -1, patience = 0;
     unsigned *arrivals = nullptr;   // of the last-workgroup ends of checks and runs
     long long xbase = 0;
     void *shadowD = nullptr;   // operand copy of the discretised state
@@ -556,15 +563,24 @@ int choose_persist(gd_solver *s) {
     // (asynchronous runs return before anyone looks whether the launch stalled)
     if (s->op != OP_F32 || s->mod() || s->Np <= 128 || (s->prm.flags & GD_F_ASYNC) || std::getenv("GD_DENSE_CONFIG"))
         return GD_OK;
+    const char *launches = std::getenv("GD_PERSIST"), *wait = std::getenv("GD_PERSIST_WAIT");
+    s->persist_left = launches ? std::atoll(launches) : -1;
+    s->patience = wait ? 100 * std::max(0ll, std::atoll(wait)) : kPersistPatience;
+    if (s->persist_left == 0) return GD_OK;
     const int id = persist_variant(cx, s->integrator() == GD_RK4, s->dJ8 != nullptr, s->Np, s->R);
     if (id < 0) return GD_OK;
     if (!s->xchg) {
         const long long words = persist_words(id, cx, s->Np, s->R);
         int rc = dalloc(&s->xchg, (size_t)words);
         if (rc == GD_OK) rc = dalloc(&s->stalled, 1);
+        // (a launch keeps the state it starts from: gains in two buffers)
+        if (rc == GD_OK && !s->gam_s) {
+            rc = dalloc(&s->gam_s, (size_t)s->plane());
+            if (rc == GD_OK) GD_HIP(hipMemsetAsync(s->gam_s, 0, (size_t)s->plane() * sizeof(float), s->stream));
+        }
         if (rc != GD_OK) return rc;
         GD_HIP(hipMemsetAsync(s->xchg, 0xFF, (size_t)words * 4, s->stream));
-        GD_HIP(hipMemsetAsync(s->stalled, 0, 4, s->stream));
+        GD_HIP(hipMemsetAsync(s->stalled, 0, sizeof(long long), s->stream));
         s->xbase = 0;
     }
     s->persist = id;
@@ -1144,9 +1160,6 @@ int gd_set_init(gd_solver *s, int32_t batch, const float *psi0, const float *gam
 constexpr int kGraphSteps = 32;
 constexpr int kSmallStepsPerLaunch = 4096;
 constexpr int kPersistSteps = 4096;
-// wall-clock ticks (60 s): the exchange takes microseconds, but workgroups may
-// start as late as long kernels of other streams leave their CUs
-constexpr long long kPersistPatience = 6000000000;
 constexpr long long kGraphWork = 1ll << 28;   // Np^2 Rp P below which steps are replayed
 static_assert(kGraphSteps % 2 == 0, "Euler ping-pong parity");
 
@@ -1200,7 +1213,9 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     // graphs, except with profiling events, noise (its key changes every
     // step) or GD-mod.  Problems whose J fits the registers of the chip run
     // persistent steps, a bounded number per launch, whatever the chunk: a
-    // trajectory does not depend on how a run is cut.
+    // trajectory does not depend on how a run is cut (but for launches that the
+    // runtime refuses or that give up: the steps from there on are the coupling
+    // kernels', which add in another order).
     const bool rk4 = s->integrator() == GD_RK4;
     const bool small_ok = !s->mod() && s->op == OP_F32 && s->Np <= 128 &&
                           std::getenv("GD_DENSE_CONFIG") == nullptr;
@@ -1237,9 +1252,9 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
             c.best_e = s->dE + s->Rp;
             first_check = false;
         }
+        if (s->persist >= 0) c.stalled = s->stalled;
         if (run_end) {
             c.flags = s->flags;
-            c.stalled = s->stalled;
             c.out = s->hres;
             ended = true;
         }
@@ -1293,6 +1308,22 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
         return GD_OK;
     };
     int64_t done = 0;
+    // A persistent launch gave up (`tag`: the steps of this call done before it
+    // and the amplitude buffer it read): back to the state it started from, and
+    // one launch per step from there on.
+    auto step_by_launch = [&](long long tag) {
+        const int64_t back = done - ((tag - 1) >> 1);
+        const int cur = int((tag - 1) & 1);
+        if (s->cur != cur) std::swap(s->gam, s->gam_s);   // (a persistent launch swaps both)
+        s->cur = cur;
+        done -= back;
+        s->steps_done -= back;
+        s->spin_updates -= (int64_t)s->n * s->R * back;
+        while (!s->trace_steps.empty() && s->trace_steps.back() > s->steps_done) s->trace_steps.pop_back();
+        s->persist = -1;
+        ended = false;
+    };
+take_steps:
     while (done < steps) {
         int64_t chunk = steps - done;
         if (ci > 0) {
@@ -1325,6 +1356,7 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
                 k += m;
             }
         }
+        bool behind = false;
         while (s->persist >= 0 && k < chunk) {
             const int m = int(std::min<int64_t>(chunk - k, kPersistSteps));
             DenseStepArgs a = base_args(s);
@@ -1332,33 +1364,48 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
             a.psi_in = s->psi[s->cur];
             a.psi_out = s->psi[s->cur ^ 1];
             a.gam_in = s->gam;
-            a.gam_out = s->gam;
+            a.gam_out = s->gam_s;
             if (s->prm.noise_D != 0.0) a.noise_amp = float(s->prm.noise_D * std::sqrt(double(a.dt)));
             PersistArgs p{};
             p.x = s->xchg;
             p.stalled = s->stalled;
+            p.tag = 2 * (done + k) + s->cur + 1;
             p.base = s->xbase;
             p.t0 = s->steps_done + k;
             p.seed = s->prm.noise_seed;
-            p.patience = kPersistPatience;
+            p.patience = s->patience;
             p.steps = m;
             if (timed && (rc = ev_begin(s)) != GD_OK) return rc;
             CheckEnd c;
             if (last && !check_due && k + m == chunk && persist_ends_run(s->persist)) c = end_of(false, true);
-            if (launch_persist(s->persist, s->complex_mode(), rk4, s->dJ8 != nullptr, a, p, c, s->stream) != hipSuccess) {
-                // cooperative launches are refused while another process on
-                // the device uses them: one launch per step from here on
+            const hipError_t pe = s->persist_left == 0 ? hipErrorCooperativeLaunchTooLarge
+                                                       : launch_persist(s->persist, s->complex_mode(), rk4,
+                                                                        s->dJ8 != nullptr, a, p, c, s->stream);
+            if (pe != hipSuccess) {
                 (void)hipGetLastError();
-                s->persist = -1;
+                // refused (hipErrorIllegalState: cooperative launches of another
+                // process on the device): one launch per step from here on, or
+                // from an earlier launch of this call that gave up
+                if (pe != hipErrorIllegalState && pe != hipErrorCooperativeLaunchTooLarge &&
+                    pe != hipErrorLaunchOutOfResources)
+                    return fail(GD_E_DEVICE, std::string("persistent steps: ") + hipGetErrorString(pe));
                 ended = false;
+                long long tag = 0;
+                GD_HIP(hipMemcpyAsync(&tag, s->stalled, sizeof tag, hipMemcpyDeviceToHost, s->stream));
+                GD_HIP(hipStreamSynchronize(s->stream));
+                if ((behind = tag != 0)) step_by_launch(tag);
+                s->persist = -1;
                 if ((rc = tile_couplings(s)) != GD_OK) return rc;
                 break;
             }
+            if (s->persist_left > 0) --s->persist_left;
             if (timed && (rc = ev_end(s, m * (rk4 ? 4 : 1))) != GD_OK) return rc;
             s->xbase += m * (rk4 ? 4 : 1);
             s->cur ^= 1;
+            std::swap(s->gam, s->gam_s);
             k += m;
         }
+        if (behind) continue;
         if (graph_ok) {
             for (; chunk - k >= kGraphSteps; k += kGraphSteps) {
                 if (timed && (rc = ev_begin(s)) != GD_OK) return rc;
@@ -1415,6 +1462,11 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     // one wait for the steps and for what the host reads of them
     if (!ended) GD_HIP(launch_check_end(end_of(false, true), s->stream));
     GD_HIP(hipStreamSynchronize(s->stream));
+    if (const long long tag = s->hres->stalled) {
+        step_by_launch(tag);
+        if ((rc = tile_couplings(s)) != GD_OK) return rc;
+        goto take_steps;
+    }
     s->run_seconds += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     if (clocked) {
         float ms = 0.0f;
@@ -1430,11 +1482,6 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
         s->launches_timed += s->ev_launches;
         s->ev_used = 0;
         s->ev_launches = 0;
-    }
-    if (s->hres->stalled) {
-        // (the amplitudes of that launch were not written)
-        free_state(s);
-        return fail(GD_E_DEVICE, "persistent step kernel: a workgroup waited too long for the others");
     }
     const int cnt = s->hres->diverged;
     s->diverged = cnt;
