@@ -197,7 +197,9 @@ typedef struct gd_run_stats {
                                  last state with one launch per step, in the summation
                                  order of those kernels, until the next set-up.
                                  GD_PERSIST=<k> allows k persistent launches after a set-up
-                                 (0: none).  Batches
+                                 (0: none).  Runs with fewer than 4 coupling evaluations
+                                 between two energy checks (one per Euler, four per RK4
+                                 step) step by launch unless it is set.  Batches
                                  of instances: the same with GD_BATCH_CONFIG=<id>; the
                                  variants with per-instance item widths also relabel each
                                  instance's spins at set-up (host threads, deterministic,

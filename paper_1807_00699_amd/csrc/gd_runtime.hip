@@ -50,6 +50,7 @@ constexpr int kProfileEvery = 8;  // GD_F_PROFILE samples the launches of every 
 // kernels of other streams leave their CUs.  A run that waits longer goes on
 // with one launch per step.
 constexpr long long kPersistPatience = 200000000;
+constexpr int kPersistCheckEvals = 4;   // coupling evaluations between two checks from which steps are persistent
 constexpr int kTraceChecks = 1 << 16;  // device checks kept in the energy trace (512 KiB)
 
 // SplitMix64 (Steele, Lea, Flood 2014) -> uniform double in [0, 1).
@@ -567,6 +568,16 @@ int choose_persist(gd_solver *s) {
     s->persist_left = launches ? std::atoll(launches) : -1;
     s->patience = wait ? 100 * std::max(0ll, std::atoll(wait)) : kPersistPatience;
     if (s->persist_left == 0) return GD_OK;
+    // A cooperative launch between two checks costs about 20 us more than a
+    // step's launch.  us per check interval of 1, 2, 5, 10 steps, one launch per
+    // step and persistent: N = 1000, R = 1 17, 23, 35, 59 and 35, 37, 43, 52; N
+    // = 300, R = 64 15, 21, 37, 65 and 34, 36, 42, 51; N = 800, R = 100 17, 25,
+    // 45, 77 and 39, 42, 52, 68; XY RK4 N = 1000, R = 128, 1 and 2 steps, 52, 83
+    // and 66, 83.  The lines are at 1 to 2 RK4 and 6 to 8 Euler steps; below 4
+    // evaluations persistent steps lose by half.
+    if (s->persist_left < 0 && s->prm.check_interval > 0 &&
+        (long long)s->prm.check_interval * (s->integrator() == GD_RK4 ? 4 : 1) < kPersistCheckEvals)
+        return GD_OK;
     const int id = persist_variant(cx, s->integrator() == GD_RK4, s->dJ8 != nullptr, s->Np, s->R);
     if (id < 0) return GD_OK;
     if (!s->xchg) {
