@@ -29,6 +29,8 @@ thread_local std::string g_last_error;
 
 int fail(int code, const std::string &msg) {
     g_last_error = msg;
+    // the runtime keeps an error for the next launch check, also of other solvers
+    if (code == GD_E_OOM || code == GD_E_DEVICE) (void)hipGetLastError();
     return code;
 }
 
