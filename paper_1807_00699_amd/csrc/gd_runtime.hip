@@ -1691,16 +1691,20 @@ int gd_mod_couplings(gd_solver *s, int32_t traj, float *K) {
         (s->prm.flags & GD_F_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
     if (s->K_packed) {
         const float *src = s->K + (size_t)traj * gdmod_packed_floats(s->Np);
+        // straight into the caller's device memory, else through a buffer
         const size_t m = (size_t)s->n * s->n;
+        const bool direct = (s->prm.flags & GD_F_DEVICE_PTRS) && reinterpret_cast<uintptr_t>(K) % 4 == 0 &&
+                            device_span(s, K, m * sizeof(float));
         float *full = K;
-        if (kind != hipMemcpyDeviceToDevice) {
+        if (!direct) {
             const int rc = dalloc(&full, m);
             if (rc != GD_OK) return rc;
         }
         hipError_t e = launch_gdmod_unpack(src, full, s->Np, s->n, s->stream);
-        if (e == hipSuccess && full != K) e = hipMemcpyAsync(K, full, m * sizeof(float), kind, s->stream);
+        const size_t row = (size_t)s->n * sizeof(float);
+        if (e == hipSuccess && !direct) e = hipMemcpy2DAsync(K, row, full, row, row, (size_t)s->n, kind, s->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
-        if (full != K) (void)hipFree(full);
+        if (!direct) (void)hipFree(full);
         GD_HIP(e);
         return GD_OK;
     }

@@ -1,4 +1,4 @@
-"""gd_mod_couplings with GD_F_DEVICE_PTRS: into device memory
+"""gd_mod_couplings of packed and full K with GD_F_DEVICE_PTRS: into device memory
 (whole words in the middle of an allocation, an unaligned address), into pinned
 host memory; pageable host memory is refused with an error code, which no later
 call reports again.  Nothing but an allocation of the solver's device may be
@@ -14,7 +14,7 @@ from paper_1807_00699_amd import inputs as I
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,R", [(130, 4)])
+@pytest.mark.parametrize("n,R", [(130, 4), (130, 700), (577, 62)])
 def test_destinations(n, R):
     import torch
     lib = gd.load()
