@@ -24,6 +24,7 @@ struct FeatArgs {
 
 struct MlpTrainArgs {
     float *params, *mom, *vel;     // [kMlpNParam]
+    void *packed;                  // params for FP16 inference, updated with them
     const float *X;                // [M][F]
     const float *labels;           // [M] +-1
     const int *seg;                // [K+1] instance boundaries (pinned host memory)
@@ -49,8 +50,8 @@ struct ProposeArgs {
 };
 
 hipError_t launch_features(const FeatArgs &a, int K, hipStream_t st);
-// FP16 inference reads the network in its operand order: kMlpPackedBytes
-// written from the parameters by launch_mlp_pack
+// FP16 inference reads the network in its operand order: kMlpPackedBytes, zero at
+// first, written from the parameters by launch_mlp_pack and the training step
 constexpr size_t kMlpPackedBytes = 4 * 1024 + 8 * 1024 + 256 + 256 + 512 + 16;
 hipError_t launch_mlp_pack(const float *params, void *packed, hipStream_t st);
 hipError_t launch_mlp_forward(const float *params, const void *packed, const float *X, float *out, int M, bool fp16,

@@ -363,8 +363,10 @@ typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int MFT = 256;   // 4 waves
 
-// The network in the order the inference kernel reads it, formed once per
-// parameter set (mlp_pack_k):
+// The network in the order the inference kernel reads it, written with the
+// parameters (mlp_pack_k when they are set, mlp_adam_k with its updates), so
+// that it is complete whenever a call that changes them has returned, for every
+// stream:
 // A1[rb][s][lane]: W1^T rows 32 rb + l % 32, features 16 s + 8 h + j
 // A2[rb][ib][s][lane]: W2^T rows 32 rb + l % 32, hidden 32 ib + 8 (2 s + j / 4) + 4 h + j % 4
 // B1, B2, W3: [rb][h][4q + e](...)
@@ -375,37 +377,29 @@ struct __attribute__((aligned(16))) MlpPacked {
 };
 static_assert(sizeof(MlpPacked) == kMlpPackedBytes && sizeof(MlpPacked) % 16 == 0, "packed network");
 
-__global__ void __launch_bounds__(MFT) mlp_pack_k(const float *__restrict__ p, MlpPacked *__restrict__ o) {
+// Parameter q, value v, in its place there
+__device__ inline void pack_param(MlpPacked *o, int q, float v) {
     static_assert(H == 64 && F <= 32 && NO == 2, "layer shapes of the MFMA forward");
-    const int tid = blockIdx.x * MFT + threadIdx.x, nt = gridDim.x * MFT;
-    for (int q = tid; q < 2 * 2 * 64; q += nt) {
-        const int rb = q / 128, st = (q / 64) % 2, l = q % 64, h = l / 32, row = 32 * rb + l % 32;
-        f16x8_t v;
-        for (int j = 0; j < 8; ++j) {
-            const int f = 16 * st + 8 * h + j;
-            v[j] = (_Float16)(f < F ? p[OFF_W1 + f * H + row] : 0.0f);
-        }
-        o->A1[rb][st][l] = v;
+    if (q < OFF_B1) {
+        const int f = q / H, row = q % H;
+        o->A1[row / 32][f / 16][f / 8 % 2 * 32 + row % 32][f % 8] = (_Float16)v;
+    } else if (q >= OFF_W2 && q < OFF_B2) {
+        const int in = (q - OFF_W2) / H, row = (q - OFF_W2) % H;
+        o->A2[row / 32][in / 32][in / 16 % 2][in / 4 % 2 * 32 + row % 32][in / 8 % 2 * 4 + in % 4] = (_Float16)v;
+    } else if (q < OFF_B3) {   // b1, b2 or W3
+        const int u = q < OFF_W2 ? q - OFF_B1 : q < OFF_W3 ? q - OFF_B2 : (q - OFF_W3) / NO;
+        const int rb = u / 32, h = u / 4 % 2, k = u / 8 % 4 * 4 + u % 4;
+        if (q < OFF_W2) o->B1[rb][h][k] = v;
+        else if (q < OFF_W3) o->B2[rb][h][k] = v;
+        else o->W3[rb][h][k][(q - OFF_W3) % NO] = v;
+    } else {
+        o->B3[q - OFF_B3] = v;
     }
-    for (int q = tid; q < 2 * 2 * 2 * 64; q += nt) {
-        const int rb = q / 256, ib = (q / 128) % 2, st = (q / 64) % 2, l = q % 64, h = l / 32;
-        const int row = 32 * rb + l % 32;
-        f16x8_t v;
-        for (int j = 0; j < 8; ++j) {
-            const int hin = 32 * ib + 8 * (2 * st + j / 4) + 4 * h + j % 4;
-            v[j] = (_Float16)p[OFF_W2 + hin * H + row];
-        }
-        o->A2[rb][ib][st][l] = v;
-    }
-    for (int q = tid; q < 2 * 2 * 16; q += nt) {
-        const int rb = q / 32, h = (q / 16) % 2, k = q % 16;
-        const int row = 32 * rb + 8 * (k / 4) + 4 * h + k % 4;
-        o->B1[rb][h][k] = p[OFF_B1 + row];
-        o->B2[rb][h][k] = p[OFF_B2 + row];
-        o->W3[rb][h][k][0] = p[OFF_W3 + row * NO];
-        o->W3[rb][h][k][1] = p[OFF_W3 + row * NO + 1];
-    }
-    if (tid < 4) o->B3[tid] = tid < NO ? p[OFF_B3 + tid] : 0.0f;
+}
+
+// All of them, over words that are zero (features past the last, words past b3)
+__global__ void __launch_bounds__(MFT) mlp_pack_k(const float *__restrict__ p, MlpPacked *__restrict__ o) {
+    for (int q = blockIdx.x * MFT + threadIdx.x; q < NPAR; q += gridDim.x * MFT) pack_param(o, q, p[q]);
 }
 
 // Two waves per SIMD with the weights in registers.  What bounds it is the
@@ -902,7 +896,9 @@ __global__ void __launch_bounds__(AT) mlp_adam_k(MlpTrainArgs a, int nparts, flo
             a.vel[q] = ve;
             const float mh = mo / (1.0f - powf(b1, float(step)));
             const float vh = ve / (1.0f - powf(b2, float(step)));
-            a.params[q] -= lr * mh / (sqrtf(vh) + 1e-8f);
+            const float next = a.params[q] - lr * mh / (sqrtf(vh) + 1e-8f);
+            a.params[q] = next;
+            pack_param(static_cast<MlpPacked *>(a.packed), q, next);
         }
     }
 }
@@ -945,7 +941,7 @@ hipError_t launch_features(const FeatArgs &a, int K, hipStream_t st) {
 }
 
 hipError_t launch_mlp_pack(const float *params, void *packed, hipStream_t st) {
-    mlp_pack_k<<<4, MFT, 0, st>>>(params, static_cast<MlpPacked *>(packed));
+    mlp_pack_k<<<8, MFT, 0, st>>>(params, static_cast<MlpPacked *>(packed));
     return hipGetLastError();
 }
 

@@ -24,7 +24,6 @@ struct gd_mlp {
     hipStream_t stream = nullptr;
     float *params = nullptr, *mom = nullptr, *vel = nullptr;
     void *packed = nullptr;        // params as FP16 inference reads them
-    bool pack_ok = false;          // ... and up to date
     int step = 0;
     // workspace for M rows
     int cap = 0;
@@ -132,15 +131,6 @@ bool device_floats(const float *p, size_t count) {
     return q >= b && q - b <= size && count * 4 <= size - (q - b);
 }
 
-// FP16 operands of the current parameters, on the stream that will use them
-// (every call that uses them waits for that stream before it returns)
-hipError_t ensure_packed(gd_mlp *m, hipStream_t st) {
-    if (m->pack_ok) return hipSuccess;
-    const hipError_t e = launch_mlp_pack(m->params, m->packed, st);
-    m->pack_ok = e == hipSuccess;
-    return e;
-}
-
 hipMemcpyKind kind_in(const gd_mlp *m) {
     return (m->flags & GD_F_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
 }
@@ -163,6 +153,10 @@ int gd_mlp_create(gd_mlp **out, const float *params, uint64_t seed, uint32_t fla
     if (hipStreamCreateWithFlags(&m->stream, hipStreamNonBlocking) != hipSuccess) {
         gd_mlp_destroy(m);
         return gd_fail(GD_E_DEVICE, "hipStreamCreate failed");
+    }
+    if (hipMemsetAsync(m->packed, 0, kMlpPackedBytes, m->stream) != hipSuccess) {
+        gd_mlp_destroy(m);
+        return gd_fail(GD_E_DEVICE, "hipMemset failed");
     }
     int rc = gd_mlp_set_params(m, params);
     if (params == nullptr) {
@@ -203,7 +197,8 @@ int gd_mlp_set_params(gd_mlp *m, const float *params) {
         for (float v : h)
             if (!std::isfinite(v)) return gd_fail(GD_E_NONFINITE, "parameters are not finite");
         GD_TRY(hipMemcpy(m->params, h.data(), kMlpNParam * 4, hipMemcpyHostToDevice));
-        m->pack_ok = false;
+        GD_TRY(launch_mlp_pack(m->params, m->packed, m->stream));
+        GD_TRY(hipStreamSynchronize(m->stream));
     }
     GD_TRY(hipMemset(m->mom, 0, kMlpNParam * 4));
     GD_TRY(hipMemset(m->vel, 0, kMlpNParam * 4));
@@ -232,7 +227,6 @@ int gd_mlp_forward(gd_mlp *m, int32_t M, const float *X, float *out, int32_t fp1
         Xd = m->X;
     }
     float *od = (m->flags & GD_F_DEVICE_PTRS) ? out : m->out;
-    if (fp16) GD_TRY(ensure_packed(m, m->stream));
     GD_TRY(launch_mlp_forward(m->params, m->packed, Xd, od, M, fp16 != 0, m->stream));
     if (!(m->flags & GD_F_DEVICE_PTRS))
         GD_TRY(hipMemcpyAsync(out, m->out, (size_t)M * 2 * 4, hipMemcpyDeviceToHost, m->stream));
@@ -262,14 +256,12 @@ int gd_mlp_train_step(gd_mlp *m, int32_t M, const float *X, const float *labels,
         Ld = m->labels;
     }
     std::memcpy(m->seg, seg, (size_t)(K + 1) * sizeof(int));
-    if (lr > 0.0f) {
-        m->step += 1;
-        m->pack_ok = false;
-    }
+    if (lr > 0.0f) m->step += 1;
     MlpTrainArgs a{};
     a.params = m->params;
     a.mom = m->mom;
     a.vel = m->vel;
+    a.packed = m->packed;
     a.X = Xd;
     a.labels = Ld;
     a.seg = m->seg;
@@ -350,7 +342,6 @@ int gd_propose(gd_solver *s, gd_mlp *m, int32_t R, int32_t feat_iters, double al
     a.feats = df;
     if (e == hipSuccess) e = launch_features(a, v.K, v.stream);
     if (e == hipSuccess) e = hipStreamSynchronize(v.stream);
-    if (e == hipSuccess) e = ensure_packed(m, v.stream);
     if (e == hipSuccess) e = launch_mlp_forward(m->params, m->packed, df, dout, int(v.total), true, v.stream);
     ProposeArgs p{};
     p.inst_n = v.d_n;
