@@ -193,7 +193,7 @@ typedef struct gd_run_stats {
                                  workgroups wait for each other: where the runtime refuses
                                  such a launch (another process has one), or a kernel of
                                  another stream keeps a compute unit for more than 2 s
-                                 (GD_PERSIST_WAIT=<microseconds>), the run goes on from the
+                                 (GD_PERSIST_WAIT=<microseconds>; 0: none), the run goes on from the
                                  last state with one launch per step, in the summation
                                  order of those kernels, until the next set-up.
                                  GD_PERSIST=<k> allows k persistent launches after a set-up

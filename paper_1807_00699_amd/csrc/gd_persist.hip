@@ -99,7 +99,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
     const int nf = a.Np / 32;
     const long long ps = a.plane_stride;
     const bool gone = tid == 0 && __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-    if (tid == 0) stalled = gone;
+    if (tid == 0) stalled = gone || p.patience < 0;
 
     // this wave's couplings: fragments w, w + 8, ... of 32 columns, RB blocks of 16 rows
     u32x4 j[J8 ? 1 : FR][J8 ? 1 : RB][3];
@@ -339,7 +339,7 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
     const int col = lane & 15, kq = lane >> 4;
     const int m0 = blockIdx.x * 16, Np = a.Np, R = a.R;
     const bool gone = tid == 0 && __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-    if (tid == 0) stalled = gone;
+    if (tid == 0) stalled = gone || p.patience < 0;
 
     uint2 j8[8];
     u32x4 j[J8 ? 1 : 8][3];

@@ -568,7 +568,7 @@ int choose_persist(gd_solver *s) {
         return GD_OK;
     const char *launches = std::getenv("GD_PERSIST"), *wait = std::getenv("GD_PERSIST_WAIT");
     s->persist_left = launches ? std::atoll(launches) : -1;
-    s->patience = wait ? 100 * std::max(0ll, std::atoll(wait)) : kPersistPatience;
+    s->patience = wait ? 100 * std::atoll(wait) - 1 : kPersistPatience;
     if (s->persist_left == 0) return GD_OK;
     // A cooperative launch between two checks costs about 20 us more than a
     // step's launch.  us per check interval of 1, 2, 5, 10 steps, one launch per
