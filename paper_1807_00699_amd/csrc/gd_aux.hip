@@ -16,7 +16,7 @@ namespace {
 
 // user [R][n] or [R][n][2] <-> planes [P][Rp][Np] (zero padded)
 __global__ void pack_planes_k(const float *__restrict__ user, float *__restrict__ planes, int n,
-                              int R, int Np, int Rp, int P) {
+                              int R, int Np, int Rp, int P, int *tiny) {
     const long long total = (long long)Rp * Np;
     for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < total;
          t += (long long)gridDim.x * blockDim.x) {
@@ -26,6 +26,7 @@ __global__ void pack_planes_k(const float *__restrict__ user, float *__restrict_
             float v = 0.0f;
             if (in) v = (P == 1) ? user[(long long)r * n + i] : user[((long long)r * n + i) * 2 + p];
             planes[p * total + t] = v;
+            if (tiny && tiny_number(v)) *tiny = 1;
         }
     }
 }
@@ -320,8 +321,8 @@ inline int grid_for(long long total) {
 }  // namespace
 
 hipError_t launch_pack_planes(const float *user, float *planes, int n, int R, int Np, int Rp,
-                              int nplanes, hipStream_t st) {
-    pack_planes_k<<<grid_for((long long)Rp * Np), 256, 0, st>>>(user, planes, n, R, Np, Rp, nplanes);
+                              int nplanes, int *tiny, hipStream_t st) {
+    pack_planes_k<<<grid_for((long long)Rp * Np), 256, 0, st>>>(user, planes, n, R, Np, Rp, nplanes, tiny);
     return hipGetLastError();
 }
 

@@ -64,6 +64,9 @@ __device__ inline void store_shadow4(void *base, long long idx, f32x4 v) {
     }
 }
 
+// whether v is a number other than zero below 2^-100 (gd_split.h)
+__device__ inline bool tiny_number(float v) { return 2 * __float_as_uint(v) - 1 < 2 * 0x0D800000u - 1; }
+
 // Operands of the pointwise update of four consecutive spins of one
 // trajectory, loaded ahead of the update (the dense kernel issues these loads
 // during its last GEMM iterations so their latency overlaps the matrix work).
@@ -236,6 +239,12 @@ __device__ inline bool epi_apply(const DenseStepArgs &a, int i0, int r, bool rva
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) bad |= !(gd_finite(nr[e]) && gd_finite(ng[e]) && gd_finite(ni[e]));
+    }
+    if constexpr (OPT == OP_F32) {
+        bool tiny = false;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tiny |= tiny_number(nr[e]) || (CPLX && tiny_number(ni[e]));
+        if (tiny) *a.tiny = 1;
     }
     *reinterpret_cast<f32x4 *>(a.psi_out + idx) = nr;
     if (CPLX) *reinterpret_cast<f32x4 *>(a.psi_out + ps + idx) = ni;

@@ -56,6 +56,11 @@ struct DenseStepArgs {
     // noise_key = SplitMix64 key of this step
     float noise_amp;
     unsigned long long noise_key;
+    // split kernels and persistent steps: J is split as J / 2^j_exp; 2^sum_exp
+    // times the sums of the products of its pieces are those of J Psi, or (0,
+    // modes that step) inv_s carries that factor
+    int j_exp, sum_exp;
+    int *tiny;             // FP32: set when an amplitude other than zero below 2^-100 is written
     // energy mode: weight of the second plane's product (3/4 for the q = 3, 6
     // clock states, whose second plane holds sin(theta) / (sqrt(3)/2))
     float im_weight;
@@ -79,8 +84,9 @@ struct DenseConfig {
 int split_config_count();
 DenseConfig split_config(bool complex_mode, bool j_fp8, int idx);
 // out: J in the order those kernels read it (Np^2 bytes from the row-major
-// FP8 copy J8, or, J8 null, 6 Np^2 bytes from the FP32 J)
-hipError_t launch_tile_couplings(const float *J, const void *J8, void *out, int Np, hipStream_t st);
+// FP8 copy J8, or, J8 null, 6 Np^2 bytes from the FP32 J / 2^j_exp)
+constexpr int kAmpExp = 24;   // small amplitudes are split as 2^kAmpExp Psi
+hipError_t launch_tile_couplings(const float *J, const void *J8, void *out, int Np, int j_exp, hipStream_t st);
 hipError_t launch_split_step(const DenseConfig &cfg, bool complex_mode, int mode, bool j_fp8,
                              const DenseStepArgs &a, hipStream_t st);
 
@@ -135,7 +141,7 @@ struct PersistArgs {
     long long base;           // amplitudes published by earlier launches
     long long t0;             // index of the first step (noise)
     unsigned long long seed;  // noise seed
-    long long patience;       // wall-clock ticks (100 MHz)
+    long long patience;       // wall-clock ticks (100 MHz); < 0: every workgroup gives up at once
     int steps;
     int groups, pause;        // set by launch_persist
 };
@@ -243,9 +249,10 @@ hipError_t launch_batch(const BatchConfig &c, int nwg, const BatchArgs &a, hipSt
 hipError_t launch_batch_best(const double *E, int K, int R, double *best_E, int *best_r, hipStream_t st);
 
 // ---- auxiliary kernels (gd_aux.hip)
-// user [R][n] (or [R][n][2]) -> zero-padded planes [P][Rp][Np]
+// user [R][n] (or [R][n][2]) -> zero-padded planes [P][Rp][Np]; tiny (or null):
+// as DenseStepArgs::tiny
 hipError_t launch_pack_planes(const float *user, float *planes, int n, int R, int Np, int Rp,
-                              int nplanes, hipStream_t st);
+                              int nplanes, int *tiny, hipStream_t st);
 // psi (nplanes) and gains at once
 hipError_t launch_unpack_state(const float *psi, float *upsi, const float *gam, float *ugam, int n, int R, int Np, int Rp,
                                int nplanes, hipStream_t st);

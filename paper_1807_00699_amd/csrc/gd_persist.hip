@@ -7,7 +7,7 @@
 // three BF16 pieces of gd_split.h) and its spins' state, and a step is: wait
 // for the amplitudes of its trajectories, split and multiply (as gd_split.h:
 // the same exact products, sums in FP32), add the waves' sums in LDS, update,
-// publish.  Trajectories are independent, so only the workgroups of one group
+// publish (2^24 Psi, gd_split.h).  Trajectories are independent, so only the workgroups of one group
 // of trajectories wait for each other.
 //
 // Exchange: an amplitude is its own arrival mark.  Slots hold kEmpty (a NaN
@@ -44,6 +44,8 @@ namespace gd {
 namespace {
 
 using split::bf16x8;
+using split::kAmpScale;
+using split::ldexp4;
 using split::split8;
 using split::u32x4;
 using split::widen8;
@@ -116,7 +118,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
             } else {
                 const f32x4 *q = reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.J) + at);
                 u32x4 t;
-                split8(q[0], q[1], j[f][rb][0], j[f][rb][1], t);
+                split8(ldexp4(q[0], -a.j_exp), ldexp4(q[1], -a.j_exp), j[f][rb][0], j[f][rb][1], t);
                 if (f * RB + rb < JL) jlds[((f * RB + rb) * kWaves + wave) * 64 + lane] = t;
                 else j[f][rb][2] = t;
             }
@@ -156,7 +158,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
         for (int k = 0; k < IT; ++k) {
             if (!(item && m0 + lr + k * LSTEP < a.Np)) continue;
             unsigned *out = slot(set, k);
-            const unsigned ur = __float_as_uint(xr[k]), ui = __float_as_uint(xi[k]);
+            const unsigned ur = __float_as_uint(xr[k] * kAmpScale), ui = __float_as_uint(xi[k] * kAmpScale);
             store1(out, ur == kEmpty ? 0x7FC00000u : ur);
             if (CPLX) store1(out + 16, ui == kEmpty ? 0x7FC00000u : ui);
         }
@@ -247,6 +249,13 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
                 }
             }
         }
+        if (a.sum_exp != 0) {
+#pragma unroll
+            for (int k = 0; k < IT; ++k) {
+                cr[k] = __builtin_ldexpf(cr[k], a.sum_exp);
+                ci[k] = __builtin_ldexpf(ci[k], a.sum_exp);
+            }
+        }
         if constexpr (JL != 0) __syncthreads();
         const int stage = RK4 ? (ev - 1) & 3 : 0;
 #pragma unroll
@@ -315,6 +324,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
         const int i = m0 + lr + k * LSTEP;
         if (!(item && i < a.n && r < a.R)) continue;
         a.psi_out[(long long)r * a.Np + i] = xr[k];
+        if (tiny_number(xr[k]) || (CPLX && tiny_number(xi[k]))) store_agent(a.tiny, 1);
         if (CPLX) a.psi_out[ps + (long long)r * a.Np + i] = xi[k];
         a.gam_out[(long long)r * a.Np + i] = gm[k];
         if (!(gd_finite(xr[k]) && gd_finite(gm[k]) && gd_finite(xi[k]))) store_agent(a.flags + r, 1);
@@ -356,7 +366,7 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
                 q[0] = reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.J) + at)[0];
                 q[1] = reinterpret_cast<const f32x4 *>(static_cast<const float *>(a.J) + at)[1];
             }
-            split8(q[0], q[1], j[f][0], j[f][1], j[f][2]);
+            split8(ldexp4(q[0], -a.j_exp), ldexp4(q[1], -a.j_exp), j[f][0], j[f][1], j[f][2]);
         }
     }
 
@@ -374,7 +384,7 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
     unsigned *const own = p.x + (long long)r * Np + i;
     auto publish = [&](long long set) {   // (a NaN of the empty pattern becomes another NaN)
         if (!updates || lane >= 16) return;
-        const unsigned u = __float_as_uint(x);
+        const unsigned u = __float_as_uint(x * kAmpScale);
         store1(own + (set & 3) * bsz, u == kEmpty ? 0x7FC00000u : u);
     };
     publish(p.base);
@@ -452,7 +462,9 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
             lo += __shfl_xor(lo, 16);
             hi += __shfl_xor(hi, 32);
             lo += __shfl_xor(lo, 32);
-            const float c = hi + lo, rho = x * x;
+            float c = hi + lo;
+            if (a.sum_exp != 0) c = __builtin_ldexpf(c, a.sum_exp);
+            const float rho = x * x;
             const float f = x * (gm - a.gamma_c - rho) + c * a.inv_s + hh;
             gm += a.dt * (ep * (a.rho_th - rho));
             x += a.dt * f;
@@ -469,6 +481,7 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
     if (stalled && tid == 0 && !gone) store_agent(p.stalled, p.tag);
     if (inside && lane < 16 && !stalled) {
         a.psi_out[(long long)r * Np + i] = x;
+        if (tiny_number(x)) store_agent(a.tiny, 1);
         a.gam_out[(long long)r * Np + i] = gm;
         if (!(gd_finite(x) && gd_finite(gm))) store_agent(a.flags + r, 1);
     }

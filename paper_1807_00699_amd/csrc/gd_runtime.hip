@@ -163,6 +163,7 @@ struct gd_solver {
     gd_params prm{};
     double s = 1.0;
     bool j_integer = false, g_integer = true;
+    int j_exp = 0;             // largest |J_ij| in [2^(j_exp - 1), 2^j_exp)
     bool j_sums24 = false;     // if J is integer and exact in FP8: every row of |J| sums to less than 2^24
     hipStream_t stream = nullptr;
     bool own_stream = false;
@@ -205,6 +206,7 @@ struct gd_solver {
     double *D64 = nullptr;     // FP64 readout planes of the re-score (allocated on first use)
     double *partial = nullptr, *dE = nullptr;
     int *flags = nullptr, *dBest = nullptr;
+    int *tiny = nullptr;       // DenseStepArgs::tiny of the current state
     // minimum energy of each device check since gd_set_init / gd_set_state
     // (the first kTraceChecks checks) and the step of each
     double *dTrace = nullptr;
@@ -270,6 +272,8 @@ void free_state(gd_solver *s) {
     if (s->partial) (void)hipFree(s->partial);
     if (s->dE) (void)hipFree(s->dE);
     if (s->flags) (void)hipFree(s->flags);
+    if (s->tiny) (void)hipFree(s->tiny);
+    s->tiny = nullptr;
     if (s->dBest) (void)hipFree(s->dBest);
     if (s->dTrace) (void)hipFree(s->dTrace);
     s->dTrace = nullptr;
@@ -344,6 +348,7 @@ int alloc_state(gd_solver *s, int R) {
     // + E[best] of the last check, + running best of a run's checks
     if (rc == GD_OK) rc = dalloc(&s->dE, (size_t)s->Rp + 2);
     if (rc == GD_OK) rc = dalloc(&s->flags, (size_t)s->Rp);
+    if (rc == GD_OK) rc = dalloc(&s->tiny, 1);
     if (rc == GD_OK) rc = dalloc(&s->arrivals, 1);
     if (rc == GD_OK) rc = dalloc(&s->dBest, 2);   // best of the last check, running best
     if (rc == GD_OK) rc = dalloc(&s->dTrace, (size_t)kTraceChecks);
@@ -356,6 +361,7 @@ int alloc_state(gd_solver *s, int R) {
         if (s->shadow[k]) GD_HIP(hipMemsetAsync(s->shadow[k], 0, pl * P * sizeof(uint16_t), s->stream));
     }
     GD_HIP(hipMemsetAsync(s->flags, 0, (size_t)s->Rp * sizeof(int), s->stream));
+    GD_HIP(hipMemsetAsync(s->tiny, 0, sizeof(int), s->stream));
     GD_HIP(hipMemsetAsync(s->arrivals, 0, sizeof(unsigned), s->stream));
     if (s->gam_s) GD_HIP(hipMemsetAsync(s->gam_s, 0, pl * sizeof(float), s->stream));
     s->cur = 0;
@@ -398,8 +404,22 @@ DenseStepArgs base_args(gd_solver *s) {
     a.hq = float(s->hq);
     a.noise_amp = 0.0f;
     a.noise_key = 0;
+    a.tiny = s->tiny;
     a.im_weight = s->ro == RO_CLOCK ? clock_im_weight(s->prm.q) : 1.0f;
     return a;
+}
+
+// The powers of two of the split operands (gd_split.h): folded into 1/s for the
+// modes that step, unless it leaves the normal numbers (couplings and a scale s
+// of the caller's in very different units)
+// (`amp_exp`: amplitudes are split as 2^amp_exp Psi)
+void set_scales(const gd_solver *s, int mode, int amp_exp, DenseStepArgs &a) {
+    a.j_exp = s->dJ8 ? 0 : s->j_exp;
+    a.sum_exp = a.j_exp - amp_exp;
+    const float both = float(std::ldexp(1.0 / s->s, a.sum_exp));
+    if (mode == MODE_ENERGY || !std::isnormal(both) || !std::isnormal(a.inv_s)) return;
+    a.inv_s = both;
+    a.sum_exp = 0;
 }
 
 hipError_t launch_coupling(gd_solver *s, const DenseConfig &cfg, int mode, const DenseStepArgs &a) {
@@ -411,6 +431,7 @@ hipError_t launch_coupling(gd_solver *s, const DenseConfig &cfg, int mode, const
     }
     if (s->op == OP_F32) {
         b.J = s->dJt;
+        set_scales(s, mode, 0, b);
         return launch_split_step(cfg, s->complex_mode(), mode, s->dJ8 != nullptr, b, s->stream);
     }
     if (cfg.id >= kLpSplitBase) {
@@ -525,7 +546,7 @@ int tile_couplings(gd_solver *s) {
     const size_t m = (size_t)s->Np * s->Np;
     const int rc = dalloc(reinterpret_cast<uint8_t **>(&s->dJt), j8 ? m : 6 * m);
     if (rc != GD_OK) return rc;
-    GD_HIP(launch_tile_couplings(s->dJ, j8, s->dJt, s->Np, s->stream));
+    GD_HIP(launch_tile_couplings(s->dJ, j8, s->dJt, s->Np, s->j_exp, s->stream));
     return GD_OK;
 }
 
@@ -797,7 +818,8 @@ int upload_planes(gd_solver *s, const float *user, float *planes, int R) {
         e = hipMemcpyAsync(tmp, user, cnt * sizeof(float), hipMemcpyDeviceToDevice, s->stream);
     else
         e = hipMemcpyAsync(tmp, user, cnt * sizeof(float), hipMemcpyHostToDevice, s->stream);
-    if (e == hipSuccess) e = launch_pack_planes(tmp, planes, s->n, R, s->Np, s->Rp, s->P, s->stream);
+    if (e == hipSuccess)
+        e = launch_pack_planes(tmp, planes, s->n, R, s->Np, s->Rp, s->P, planes == s->psi[0] ? s->tiny : nullptr, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     (void)hipFree(tmp);
     if (e != hipSuccess) return fail(GD_E_DEVICE, std::string("upload: ") + hipGetErrorString(e));
@@ -976,6 +998,7 @@ int gd_create(gd_solver **out, int32_t n, const float *J, const float *g, int32_
         if (!all_finite(hg)) return bail(fail(GD_E_NONFINITE, "g has non-finite entries"));
     }
     double ss = 0.0;
+    float jmax = 0.0f;
     bool integer = true;
     for (int i = 0; i < n; ++i)
         for (int j = 0; j < n; ++j) {
@@ -987,9 +1010,11 @@ int gd_create(gd_solver **out, int32_t n, const float *J, const float *g, int32_
                 return bail(fail(GD_E_NOT_SYMMETRIC, buf));
             }
             ss += double(v) * double(v);
+            jmax = std::max(jmax, std::fabs(v));
             integer = integer && (v == std::nearbyint(v));
         }
     s->j_integer = integer;
+    if (jmax > 0.0f) (void)std::frexp(jmax, &s->j_exp);
     // (FP8 couplings are at most 448 in magnitude)
     s->j_sums24 = integer;
     for (int i = 0; i < n && s->j_sums24 && n > 16777216 / 448; ++i) {
@@ -1374,6 +1399,7 @@ take_steps:
             const int m = int(std::min<int64_t>(chunk - k, kPersistSteps));
             DenseStepArgs a = base_args(s);
             a.J = s->dJ8 ? s->dJ8 : (const void *)s->dJ;
+            set_scales(s, rk4 ? MODE_RK1 : MODE_EULER, kAmpExp, a);
             a.psi_in = s->psi[s->cur];
             a.psi_out = s->psi[s->cur ^ 1];
             a.gam_in = s->gam;
@@ -1668,6 +1694,7 @@ int gd_set_state(gd_solver *s, int32_t batch, const float *psi, const float *gam
     }
     reset_stats(s);
     s->cur = 0;
+    GD_HIP(hipMemsetAsync(s->tiny, 0, sizeof(int), s->stream));
     if ((rc = upload_planes(s, psi, s->psi[0], batch)) != GD_OK) return rc;
     const int savedP = s->P;
     s->P = 1;

@@ -198,6 +198,7 @@ small_step_k(DenseStepArgs a, int steps, unsigned long long seed, long long t0, 
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         a.psi_out[(p + c) * ps + idx] = v[c];
+        if (tiny_number(v[c])) store_agent(a.tiny, 1);
         bad |= !__builtin_isfinite(v[c]);
     }
     if (p == 0) a.gam_out[idx] = g;

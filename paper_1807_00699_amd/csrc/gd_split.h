@@ -3,7 +3,14 @@
 //   x = x0 + x1 + x2   (x0 = bf16(x), x1 = bf16(x - x0), x2 = x - x0 - x1),
 // exactly: 3 x 8 significant bits hold the 24 of an FP32 number, both
 // differences are exact, and so is each product of two pieces in the FP32
-// accumulators of v_mfma_f32_32x32x16_bf16.  Couplings that are exact in FP8
+// accumulators of v_mfma_f32_32x32x16_bf16.  The pieces of small numbers would
+// leave BF16's range (the last bit of 2^-110 is 2^-133), so J is split in units
+// of a power of two next to its largest magnitude, and amplitudes times 2^24
+// once a step has written one below 2^-100 (*a.tiny): the last bit of any FP32
+// number is a normal BF16 then.  The sums are scaled back.  That is a simple
+// loop of its own before the pipelined one: a multiplication before every split
+// cost 2% (N = R = 4096) to 12% (N = 3001, R = 1500), one of each chunk in LDS,
+// where it is not even executed, 4% (the compiler's schedule).  Couplings that are exact in FP8
 // (E4M3) are one BF16 piece and take three products per amplitude; any other
 // J is split the same way and takes six (j0 x0, j0 x1, j1 x0, j1 x1, j0 x2,
 // j2 x0; the three left out are below 2^-24 of j x).
@@ -62,6 +69,15 @@ __device__ inline int row_swz(int row) {
     static_assert(ROWB == 64 || ROWB == 128 || ROWB == 256, "rows of 4, 8 or 16 slots");
     return ROWB == 64 ? (row >> 2) & 3 : ROWB == 128 ? (row >> 1) & 7 : row & 15;
 }
+
+// 2^e v
+__device__ inline f32x4 ldexp4(f32x4 v, int e) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = __builtin_ldexpf(v[q], e);
+    return v;
+}
+
+constexpr float kAmpScale = float(1 << kAmpExp);
 
 // the three BF16 pieces of eight consecutive FP32 values
 __device__ inline void split8(const f32x4 &lo, const f32x4 &hi, u32x4 &p0, u32x4 &p1, u32x4 &p2) {
@@ -271,10 +287,155 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
         if constexpr (ODDACC) odd[v] = 0.0f;
     }
 
+    // the products of slice sl: jword(mb, q) is word q of the chunk's couplings
+    auto products = [&](int sl, const u32x4 (&x0)[NB], const u32x4 (&x1)[NB], const u32x4 (&x2)[NB],
+                        auto jword) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) {
+            if constexpr (J8) {
+                const u32x4 w = jword(mb, sl / 2);
+                const u32x4 j0 = (sl & 1) == 0 ? widen8<OPT>(w[0], w[1]) : widen8<OPT>(w[2], w[3]);
+                if constexpr (F32 && !SIGN) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
+                        lo = mfma(j0, x2[nb], lo);
+                    }
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
+                        lo = mfma(j0, x1[nb], lo);
+                    }
+                }
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma<OPT>(j0, x0[nb], acc[mb][nb]);
+            } else {
+                const u32x4 j0 = jword(mb, 3 * sl), j1 = jword(mb, 3 * sl + 1), j2 = jword(mb, 3 * sl + 2);
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
+                    lo = mfma(j0, x2[nb], lo);
+                    lo = mfma(j2, x0[nb], lo);
+                    lo = mfma(j1, x1[nb], lo);
+                    lo = mfma(j0, x1[nb], lo);
+                    lo = mfma(j1, x0[nb], lo);
+                    f32x16 &hi = ODDACC && (sl & 1) ? odd : acc[mb][nb];
+                    hi = mfma(j0, x0[nb], hi);
+                }
+            }
+        }
+    };
+
+    // the sums (of 2^amp_exp times the amplitudes) and the update
+    auto finish = [&](int amp_exp) __attribute__((always_inline)) {
+        if constexpr (ODDACC) acc[0][0] += odd;
+        if constexpr (LOWACC) {
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) acc[mb][nb] += low[mb][nb];
+        }
+
+        // ---------------------------------------------------------------- epilogue
+        // acc[mb][nb][4q + e]: row wm TM + mb 32 + 8q + 4 lh + e, column l32 of
+        // block nb.  The sums are staged in LDS as [group][plane][trajectory][row];
+        // then every thread adds the groups' sums of its (trajectory, 4 rows)
+        // groups and updates them: consecutive lanes on consecutive spins.
+        float *st = reinterpret_cast<float *>(lds);
+#pragma unroll
+        for (int p = 0; p < NPASS; ++p) {
+            __syncthreads();
+            if (NPASS == 1 || wn == p) {
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    const int c = nb * 32 + l32, plane = CPLX ? c / TRW : 0;
+                    const int tr = (NPASS == 1 ? wn * TRW : 0) + (CPLX ? c % TRW : c);
+                    float *o = st + ((grp * PL + plane) * TRP + tr) * TP;
+#pragma unroll
+                    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            *reinterpret_cast<f32x4 *>(o + wm * TM + mb * 32 + 8 * q + 4 * lh) =
+                                f32x4{acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2],
+                                      acc[mb][nb][4 * q + 3]};
+                }
+            }
+            __syncthreads();
+            // UB groups at a time, their state loads in flight together (indices
+            // clamped to the planes; groups outside the problem are not written)
+            constexpr int UB = EARLY ? NU : (NU < 4 ? NU : 4);
+#pragma unroll
+            for (int u0 = 0; u0 < NU; u0 += UB) {
+                EpiIn in[UB];
+                if constexpr (!EARLY && MODE != MODE_ENERGY) {
+#pragma unroll
+                    for (int v = 0; v < UB; ++v) {
+                        const int g = tid + (u0 + v) * NT;
+                        epi_load<MODE, CPLX>(a, min(m0 + (g % RG) * 4, a.Np - 4), min(r0 + p * TRP + g / RG, a.R - 1), in[v]);
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < UB && u0 + v < NU; ++v) {
+                    const int g = tid + (u0 + v) * NT;
+                    if (NGRP % NT != 0 && g >= NGRP) break;
+                    const int tr = g / RG, row = (g % RG) * 4;
+                    const int r = r0 + p * TRP + tr, i0 = m0 + row;
+                    f32x4 cr = *reinterpret_cast<const f32x4 *>(st + tr * TP + row);
+                    f32x4 ci = CPLX ? *reinterpret_cast<const f32x4 *>(st + (TRP + tr) * TP + row) : cr;
+#pragma unroll
+                    for (int q = 1; q < KS; ++q) {
+                        cr += *reinterpret_cast<const f32x4 *>(st + (q * PL * TRP + tr) * TP + row);
+                        if (CPLX) ci += *reinterpret_cast<const f32x4 *>(st + ((q * PL + 1) * TRP + tr) * TP + row);
+                    }
+                    if (F32 && !SIGN && a.sum_exp - amp_exp != 0) {
+                        cr = ldexp4(cr, a.sum_exp - amp_exp);
+                        if (CPLX) ci = ldexp4(ci, a.sum_exp - amp_exp);
+                    }
+                    const bool inside = i0 < a.Np && r < a.R;
+                    if constexpr (MODE == MODE_ENERGY) {
+                        // rows past the tile's end add nothing; the row groups of
+                        // one trajectory are consecutive lanes
+                        double e = inside ? energy_terms4<CPLX, SIGN>(a, i0, r, cr, ci) : 0.0;
+#pragma unroll
+                        for (int m = RG / 2; m >= 1; m >>= 1) e += __shfl_xor(e, m);
+                        if (row == 0 && r < a.R) a.partial[(long long)mt * a.Rp + r] = e;
+                    } else if (inside) {
+                        if (epi_apply<MODE, CPLX, OPT>(a, i0, r, true, EARLY ? pre[u0 + v] : in[v], cr, ci)) a.flags[r] = 1;
+                    }
+                }
+            }
+        }
+    };
+
+    const int nk = a.Np / BK;
+    if constexpr (F32 && MODE != MODE_ENERGY) {
+        // small amplitudes: the same products in the same order of 2^kAmpExp
+        // times the amplitudes, straight from memory
+        if (*(const __attribute__((address_space(4))) int *)a.tiny != 0) {
+            for (int kc = grp; kc < nk; kc += KS)
+#pragma unroll
+                for (int sl = 0; sl < NSL; ++sl) {
+                    const int k = kc * BK + (J8 ? (sl >> 1) * 32 + 16 * lh + 8 * (sl & 1) : 16 * sl + 8 * lh);
+                    u32x4 x0[NB], x1[NB], x2[NB];
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const int c = nb * 32 + l32, plane = CPLX ? c / TRW : 0;
+                        const int tr = min(wn * TRW + c % TRW, a.Rp - 1 - r0);
+                        const f32x4 *x = reinterpret_cast<const f32x4 *>(
+                            static_cast<const float *>(a.B) + plane * a.plane_stride + (r0 + tr) * Np + k);
+                        split8(x[0] * kAmpScale, x[1] * kAmpScale, x0[nb], x1[nb], x2[nb]);
+                    }
+                    products(sl, x0, x1, x2,
+                             [&](int mb, int q) { return (jsrc[mb] + (long long)(kc * JPC + q) * 64)[lane]; });
+                }
+            finish(kAmpExp);
+            return;
+        }
+    }
+
     // Every group runs nit iterations, a multiple of JD; chunks past the last
     // load the last one and multiply nothing.  The last JD iterations issue no
     // loads, so the number of operations in flight is known at every wait.
-    const int nk = a.Np / BK;
     const int nit = ((nk + KS - 1) / KS + JD - 1) / JD * JD;
     auto chunk_of = [&](int it) { return min(it * KS + grp, nk - 1); };
 #pragma unroll
@@ -332,40 +493,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
                     else if constexpr (SIGN) x0[nb] = sign8(lo, hi);
                     else split8(lo, hi, x0[nb], x1[nb], x2[nb]);
                 }
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    if constexpr (J8) {
-                        const u32x4 w = jw[JS][mb][sl / 2];
-                        const u32x4 j0 = set == 0 ? widen8<OPT>(w[0], w[1]) : widen8<OPT>(w[2], w[3]);
-                        if constexpr (F32 && !SIGN) {
-#pragma unroll
-                            for (int nb = 0; nb < NB; ++nb) {
-                                f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
-                                lo = mfma(j0, x2[nb], lo);
-                            }
-#pragma unroll
-                            for (int nb = 0; nb < NB; ++nb) {
-                                f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
-                                lo = mfma(j0, x1[nb], lo);
-                            }
-                        }
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma<OPT>(j0, x0[nb], acc[mb][nb]);
-                    } else {
-                        const u32x4 j0 = jw[JS][mb][3 * sl], j1 = jw[JS][mb][3 * sl + 1], j2 = jw[JS][mb][3 * sl + 2];
-#pragma unroll
-                        for (int nb = 0; nb < NB; ++nb) {
-                            f32x16 &lo = LOWACC ? low[LOWACC ? mb : 0][LOWACC ? nb : 0] : acc[mb][nb];
-                            lo = mfma(j0, x2[nb], lo);
-                            lo = mfma(j2, x0[nb], lo);
-                            lo = mfma(j1, x1[nb], lo);
-                            lo = mfma(j0, x1[nb], lo);
-                            lo = mfma(j1, x0[nb], lo);
-                            f32x16 &hi = ODDACC && set ? odd : acc[mb][nb];
-                            hi = mfma(j0, x0[nb], hi);
-                        }
-                    }
-                }
+                products(sl, x0, x1, x2, [&](int mb, int q) { return jw[JS][mb][q]; });
                 // the couplings just used make room for those JD chunks ahead
                 if constexpr (!LAST)
                     if (!J8 || set == 1) load_j(chunk_of(it + JD), JS, sl);
@@ -379,79 +507,7 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
                   std::make_integer_sequence<int, JD>{});
     seq_apply([&](auto p) { iteration(it + decltype(p)::value, p, std::true_type{}); },
               std::make_integer_sequence<int, JD>{});
-    if constexpr (ODDACC) acc[0][0] += odd;
-    if constexpr (LOWACC) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[mb][nb] += low[mb][nb];
-    }
-
-    // ---------------------------------------------------------------- epilogue
-    // acc[mb][nb][4q + e]: row wm TM + mb 32 + 8q + 4 lh + e, column l32 of
-    // block nb.  The sums are staged in LDS as [group][plane][trajectory][row];
-    // then every thread adds the groups' sums of its (trajectory, 4 rows)
-    // groups and updates them: consecutive lanes on consecutive spins.
-    float *st = reinterpret_cast<float *>(lds);
-#pragma unroll
-    for (int p = 0; p < NPASS; ++p) {
-        __syncthreads();
-        if (NPASS == 1 || wn == p) {
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int c = nb * 32 + l32, plane = CPLX ? c / TRW : 0;
-                const int tr = (NPASS == 1 ? wn * TRW : 0) + (CPLX ? c % TRW : c);
-                float *o = st + ((grp * PL + plane) * TRP + tr) * TP;
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<f32x4 *>(o + wm * TM + mb * 32 + 8 * q + 4 * lh) =
-                            f32x4{acc[mb][nb][4 * q], acc[mb][nb][4 * q + 1], acc[mb][nb][4 * q + 2],
-                                  acc[mb][nb][4 * q + 3]};
-            }
-        }
-        __syncthreads();
-        // UB groups at a time, their state loads in flight together (indices
-        // clamped to the planes; groups outside the problem are not written)
-        constexpr int UB = EARLY ? NU : (NU < 4 ? NU : 4);
-#pragma unroll
-        for (int u0 = 0; u0 < NU; u0 += UB) {
-            EpiIn in[UB];
-            if constexpr (!EARLY && MODE != MODE_ENERGY) {
-#pragma unroll
-                for (int v = 0; v < UB; ++v) {
-                    const int g = tid + (u0 + v) * NT;
-                    epi_load<MODE, CPLX>(a, min(m0 + (g % RG) * 4, a.Np - 4), min(r0 + p * TRP + g / RG, a.R - 1), in[v]);
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < UB && u0 + v < NU; ++v) {
-                const int g = tid + (u0 + v) * NT;
-                if (NGRP % NT != 0 && g >= NGRP) break;
-                const int tr = g / RG, row = (g % RG) * 4;
-                const int r = r0 + p * TRP + tr, i0 = m0 + row;
-                f32x4 cr = *reinterpret_cast<const f32x4 *>(st + tr * TP + row);
-                f32x4 ci = CPLX ? *reinterpret_cast<const f32x4 *>(st + (TRP + tr) * TP + row) : cr;
-#pragma unroll
-                for (int q = 1; q < KS; ++q) {
-                    cr += *reinterpret_cast<const f32x4 *>(st + (q * PL * TRP + tr) * TP + row);
-                    if (CPLX) ci += *reinterpret_cast<const f32x4 *>(st + ((q * PL + 1) * TRP + tr) * TP + row);
-                }
-                const bool inside = i0 < a.Np && r < a.R;
-                if constexpr (MODE == MODE_ENERGY) {
-                    // rows past the tile's end add nothing; the row groups of
-                    // one trajectory are consecutive lanes
-                    double e = inside ? energy_terms4<CPLX, SIGN>(a, i0, r, cr, ci) : 0.0;
-#pragma unroll
-                    for (int m = RG / 2; m >= 1; m >>= 1) e += __shfl_xor(e, m);
-                    if (row == 0 && r < a.R) a.partial[(long long)mt * a.Rp + r] = e;
-                } else if (inside) {
-                    if (epi_apply<MODE, CPLX, OPT>(a, i0, r, true, EARLY ? pre[u0 + v] : in[v], cr, ci)) a.flags[r] = 1;
-                }
-            }
-        }
-    }
+    finish(0);
 #endif
 }
 

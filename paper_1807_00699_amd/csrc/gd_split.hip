@@ -41,7 +41,7 @@ __global__ void tile_j8_k(const unsigned char *__restrict__ J, uint4 *__restrict
     }
 }
 
-__global__ void tile_j3_k(const float *__restrict__ J, uint4 *__restrict__ out, int Np) {
+__global__ void tile_j3_k(const float *__restrict__ J, uint4 *__restrict__ out, int Np, int j_exp) {
     const long long words = (long long)Np * Np / 8;   // lanes; three words each
     for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < words;
          t += (long long)gridDim.x * blockDim.x) {
@@ -50,19 +50,19 @@ __global__ void tile_j3_k(const float *__restrict__ J, uint4 *__restrict__ out, 
         const long long row = blk / (Np / 16) * 32 + (lane & 31), k = blk % (Np / 16) * 16 + 8 * (lane >> 5);
         const f32x4 *p = reinterpret_cast<const f32x4 *>(J + row * Np + k);
         split::u32x4 w[3];
-        split::split8(p[0], p[1], w[0], w[1], w[2]);
+        split::split8(split::ldexp4(p[0], -j_exp), split::ldexp4(p[1], -j_exp), w[0], w[1], w[2]);
         for (int q = 0; q < 3; ++q) out[(blk * 3 + q) * 64 + lane] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
     }
 }
 
 }  // namespace
 
-hipError_t launch_tile_couplings(const float *J, const void *J8, void *out, int Np, hipStream_t st) {
+hipError_t launch_tile_couplings(const float *J, const void *J8, void *out, int Np, int j_exp, hipStream_t st) {
     if (Np % 64) return hipErrorInvalidValue;
     const long long words = (long long)Np * Np / (J8 ? 16 : 8);
     const int grid = int(words / 256 < 65536 ? words / 256 : 65536);
     if (J8) tile_j8_k<<<grid, 256, 0, st>>>(static_cast<const unsigned char *>(J8), static_cast<uint4 *>(out), Np);
-    else tile_j3_k<<<grid, 256, 0, st>>>(J, static_cast<uint4 *>(out), Np);
+    else tile_j3_k<<<grid, 256, 0, st>>>(J, static_cast<uint4 *>(out), Np, j_exp);
     return hipGetLastError();
 }
 
