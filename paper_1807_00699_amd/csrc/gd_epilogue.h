@@ -242,7 +242,8 @@ __device__ inline bool epi_apply(const DenseStepArgs &a, int i0, int r, bool rva
 #pragma unroll
         for (int e = 0; e < 4; ++e) bad |= !(gd_finite(nr[e]) && gd_finite(ng[e]) && gd_finite(ni[e]));
     }
-    if constexpr (OPT == OP_F32) {
+    // (stages of a step lie next to its start and end, 2^10 above the first lost bit)
+    if constexpr (OPT == OP_F32 && (MODE == MODE_EULER || MODE == MODE_RK4)) {
         bool tiny = false;
 #pragma unroll
         for (int e = 0; e < 4; ++e) tiny |= tiny_number(nr[e]) || (CPLX && tiny_number(ni[e]));

@@ -200,6 +200,8 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
     const int wm = wave % WM, wn = wave / WM;
     const int l32 = lane & 31, lh = lane >> 5;
     const int n_mt = (a.Np + BM - 1) / BM, n_ct = (a.R + TRAJ - 1) / TRAJ;
+    int tiny = 0;
+    if constexpr (F32 && MODE != MODE_ENERGY) tiny = *(const __attribute__((address_space(4))) int *)a.tiny;
     int mt, ct;
     tile_of(blockIdx.x, gridDim.x, n_mt, n_ct, mt, ct);
     const int m0 = mt * BM, r0 = ct * TRAJ;
@@ -407,11 +409,24 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
         }
     };
 
+    // Every group runs nit iterations, a multiple of JD; chunks past the last
+    // load the last one and multiply nothing.  The last JD iterations issue no
+    // loads, so the number of operations in flight is known at every wait.
     const int nk = a.Np / BK;
+    const int nit = ((nk + KS - 1) / KS + JD - 1) / JD * JD;
+    auto chunk_of = [&](int it) { return min(it * KS + grp, nk - 1); };
+#pragma unroll
+    for (int p = 0; p < JD; ++p) copy_chunk(chunk_of(p) * BK, p);
+    __asm__ __volatile__("" ::: "memory");
+#pragma unroll
+    for (int p = 0; p < JD; ++p)
+#pragma unroll
+        for (int sl = J8 ? 1 : 0; sl < NSL; sl += J8 ? 2 : 1) load_j(chunk_of(p), p, sl);
     if constexpr (F32 && MODE != MODE_ENERGY) {
         // small amplitudes: the same products in the same order of 2^kAmpExp
-        // times the amplitudes, straight from memory
-        if (*(const __attribute__((address_space(4))) int *)a.tiny != 0) {
+        // times the amplitudes, straight from memory (looked at here, where the
+        // flag's own load has had the time of the first chunks')
+        if (tiny != 0) {
             for (int kc = grp; kc < nk; kc += KS)
 #pragma unroll
                 for (int sl = 0; sl < NSL; ++sl) {
@@ -428,23 +443,11 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
                     products(sl, x0, x1, x2,
                              [&](int mb, int q) { return (jsrc[mb] + (long long)(kc * JPC + q) * 64)[lane]; });
                 }
+            __builtin_amdgcn_s_waitcnt(0);   // (the copies above, before others use their LDS)
             finish(kAmpExp);
             return;
         }
     }
-
-    // Every group runs nit iterations, a multiple of JD; chunks past the last
-    // load the last one and multiply nothing.  The last JD iterations issue no
-    // loads, so the number of operations in flight is known at every wait.
-    const int nit = ((nk + KS - 1) / KS + JD - 1) / JD * JD;
-    auto chunk_of = [&](int it) { return min(it * KS + grp, nk - 1); };
-#pragma unroll
-    for (int p = 0; p < JD; ++p) copy_chunk(chunk_of(p) * BK, p);
-    __asm__ __volatile__("" ::: "memory");
-#pragma unroll
-    for (int p = 0; p < JD; ++p)
-#pragma unroll
-        for (int sl = J8 ? 1 : 0; sl < NSL; sl += J8 ? 2 : 1) load_j(chunk_of(p), p, sl);
     int buf = 0;
     // iteration `it` with the couplings of set JS; LAST: one of the last JD
     auto iteration = [&](int it, auto js, auto last) {
