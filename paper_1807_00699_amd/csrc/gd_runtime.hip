@@ -544,9 +544,13 @@ int tile_couplings(gd_solver *s) {
     const void *j8 = couplings_fp8(s);
     if (s->dJt || (s->op != OP_F32 && !j8)) return GD_OK;
     const size_t m = (size_t)s->Np * s->Np;
-    const int rc = dalloc(reinterpret_cast<uint8_t **>(&s->dJt), j8 ? m : 6 * m);
+    void *t = nullptr;
+    const int rc = dalloc(reinterpret_cast<uint8_t **>(&t), j8 ? m : 6 * m);
     if (rc != GD_OK) return rc;
-    GD_HIP(launch_tile_couplings(s->dJ, j8, s->dJt, s->Np, s->j_exp, s->stream));
+    const hipError_t e = launch_tile_couplings(s->dJ, j8, t, s->Np, s->j_exp, s->stream);
+    if (e != hipSuccess) (void)hipFree(t);
+    GD_HIP(e);
+    s->dJt = t;
     return GD_OK;
 }
 
@@ -663,9 +667,13 @@ int choose_config(gd_solver *s) {
     // laid out when they first run (here, when they are timed)
     const bool fused = !lp && !s->mod() && s->Np <= 128;
     if (fused && !s->dJs) {
-        const int rc = dalloc(&s->dJs, (size_t)s->Np * s->Np);
+        float *t = nullptr;
+        const int rc = dalloc(&t, (size_t)s->Np * s->Np);
         if (rc != GD_OK) return rc;
-        GD_HIP(launch_small_couplings(s->dJ, s->dJs, s->Np, s->stream));
+        const hipError_t e = launch_small_couplings(s->dJ, t, s->Np, s->stream);
+        if (e != hipSuccess) (void)hipFree(t);
+        GD_HIP(e);
+        s->dJs = t;
     }
     if (const char *env = std::getenv("GD_DENSE_CONFIG")) {
         int id = std::atoi(env);
@@ -770,6 +778,15 @@ int choose_config(gd_solver *s) {
     g_tune_cache[key] = best;
     tune_cache_store("dense", fkey, best);
     return GD_OK;
+}
+
+// The kernel variant and persistent steps' buffers of a state just set up;
+// without them there is no state
+int prepare_steps(gd_solver *s) {
+    int rc = choose_config(s);
+    if (rc == GD_OK) rc = choose_persist(s);
+    if (rc != GD_OK) free_state(s);
+    return rc;
 }
 
 int check_params(const gd_params *p) {
@@ -902,6 +919,32 @@ int default_init(gd_solver *s, int R, const float *gamma0) {
     if (rc == GD_OK && gamma0) rc = upload_planes(s, gamma0, s->gam, R);
     s->P = savedP;
     return rc;
+}
+
+// The state of gd_set_init
+int fill_state(gd_solver *s, int32_t batch, const float *psi0, const float *gamma0) {
+    int rc;
+    if (psi0) {
+        if ((rc = upload_planes(s, psi0, s->psi[0], batch)) != GD_OK) return rc;
+        const int savedP = s->P;
+        s->P = 1;
+        if (gamma0) {
+            rc = upload_planes(s, gamma0, s->gam, batch);
+        } else {
+            std::vector<float> g((size_t)batch * s->n, float(s->prm.gamma0));
+            const uint32_t saved = s->prm.flags;
+            s->prm.flags &= ~GD_F_DEVICE_PTRS;
+            rc = upload_planes(s, g.data(), s->gam, batch);
+            s->prm.flags = saved;
+        }
+        s->P = savedP;
+        if (rc != GD_OK) return rc;
+    } else {
+        if ((rc = default_init(s, batch, gamma0)) != GD_OK) return rc;
+    }
+    GD_HIP(refresh_shadow(s, 0));
+    if ((rc = reset_mod_couplings(s)) != GD_OK) return rc;
+    return GD_OK;
 }
 
 }  // namespace
@@ -1168,28 +1211,12 @@ int gd_set_init(gd_solver *s, int32_t batch, const float *psi0, const float *gam
     }
     if ((rc = alloc_state(s, batch)) != GD_OK) return rc;
     reset_stats(s);
-    if (psi0) {
-        if ((rc = upload_planes(s, psi0, s->psi[0], batch)) != GD_OK) return rc;
-        const int savedP = s->P;
-        s->P = 1;
-        if (gamma0) {
-            rc = upload_planes(s, gamma0, s->gam, batch);
-        } else {
-            std::vector<float> g((size_t)batch * s->n, float(s->prm.gamma0));
-            const uint32_t saved = s->prm.flags;
-            s->prm.flags &= ~GD_F_DEVICE_PTRS;
-            rc = upload_planes(s, g.data(), s->gam, batch);
-            s->prm.flags = saved;
-        }
-        s->P = savedP;
-        if (rc != GD_OK) return rc;
-    } else {
-        if ((rc = default_init(s, batch, gamma0)) != GD_OK) return rc;
+    rc = fill_state(s, batch, psi0, gamma0);
+    if (rc != GD_OK) {
+        free_state(s);
+        return rc;
     }
-    GD_HIP(refresh_shadow(s, 0));
-    if ((rc = reset_mod_couplings(s)) != GD_OK) return rc;
-    if ((rc = choose_config(s)) != GD_OK) return rc;
-    return choose_persist(s);
+    return prepare_steps(s);
 }
 
 // Replay the captured kGraphSteps steps (capturing them first if the
@@ -1689,8 +1716,7 @@ int gd_set_state(gd_solver *s, int32_t batch, const float *psi, const float *gam
     if (!all_finite(chk)) return fail(GD_E_NONFINITE, "gamma has non-finite entries");
     if (!s->have_state || batch != s->R) {
         if ((rc = alloc_state(s, batch)) != GD_OK) return rc;
-        if ((rc = choose_config(s)) != GD_OK) return rc;
-        if ((rc = choose_persist(s)) != GD_OK) return rc;
+        if ((rc = prepare_steps(s)) != GD_OK) return rc;
     }
     reset_stats(s);
     s->cur = 0;
