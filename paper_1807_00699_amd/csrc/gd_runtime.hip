@@ -554,6 +554,13 @@ int tile_couplings(gd_solver *s) {
     return GD_OK;
 }
 
+// Whether the solver's steps read that form
+bool steps_read_tiles(const gd_solver *s) {
+    if (s->mod() || s->persist >= 0) return false;
+    if (s->op != OP_F32) return s->cfg.id >= kLpSplitBase && s->cfg.id < kGemvBase;
+    return (s->Np > 128 || std::getenv("GD_DENSE_CONFIG")) && (s->cfg.id < kGemvBase || s->cfg.id >= kFewBase);
+}
+
 // Ising readouts with FP8-stored couplings: energies from the signs of the
 // amplitudes in one kernel, without readout planes
 bool sign_readout(const gd_solver *s) {
@@ -780,11 +787,20 @@ int choose_config(gd_solver *s) {
     return GD_OK;
 }
 
-// The kernel variant and persistent steps' buffers of a state just set up;
-// without them there is no state
+// What the steps of a state just set up need: the kernel variant, persistent
+// steps' buffers, J as the kernels read it (gd_run allocates nothing for its
+// steps, so that asynchronous runs can be captured from the first on).  Without
+// it there is no state.
 int prepare_steps(gd_solver *s) {
     int rc = choose_config(s);
     if (rc == GD_OK) rc = choose_persist(s);
+    if (rc == GD_OK && steps_read_tiles(s)) rc = tile_couplings(s);
+    // the three pieces of J (6 N^2 bytes) were laid out to time the variants only
+    if (rc == GD_OK && s->dJt && !couplings_fp8(s) && !s->mod() && s->cfg.id >= kGemvBase && s->cfg.id < kFewBase) {
+        const hipError_t e = hipFree(s->dJt);   // (waits for the device)
+        s->dJt = nullptr;
+        if (e != hipSuccess) rc = fail(GD_E_DEVICE, std::string("hipFree: ") + hipGetErrorString(e));
+    }
     if (rc != GD_OK) free_state(s);
     return rc;
 }
@@ -1284,7 +1300,7 @@ int gd_run(gd_solver *s, int32_t batch, int64_t steps) {
     const bool rk4 = s->integrator() == GD_RK4;
     const bool small_ok = !s->mod() && s->op == OP_F32 && s->Np <= 128 &&
                           std::getenv("GD_DENSE_CONFIG") == nullptr;
-    if (!small_ok && !s->mod() && s->persist < 0 && (rc = tile_couplings(s)) != GD_OK) return rc;
+    if (steps_read_tiles(s) && (rc = tile_couplings(s)) != GD_OK) return rc;   // (at set-up, unless GD_DENSE_CONFIG changed)
     // The matrix-vector kernels of few trajectories run for microseconds, so
     // they are always replayed from graphs (with GD_F_PROFILE one event pair
     // brackets each replay and its launches, in-graph dispatch gaps included).
@@ -1461,7 +1477,7 @@ take_steps:
                 GD_HIP(hipStreamSynchronize(s->stream));
                 if ((behind = tag != 0)) step_by_launch(tag);
                 s->persist = -1;
-                if ((rc = tile_couplings(s)) != GD_OK) return rc;
+                if (steps_read_tiles(s) && (rc = tile_couplings(s)) != GD_OK) return rc;
                 break;
             }
             if (s->persist_left > 0) --s->persist_left;
@@ -1530,7 +1546,7 @@ take_steps:
     GD_HIP(hipStreamSynchronize(s->stream));
     if (const long long tag = s->hres->stalled) {
         step_by_launch(tag);
-        if ((rc = tile_couplings(s)) != GD_OK) return rc;
+        if (steps_read_tiles(s) && (rc = tile_couplings(s)) != GD_OK) return rc;
         goto take_steps;
     }
     s->run_seconds += std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
