@@ -657,6 +657,11 @@ int choose_config(gd_solver *s) {
         if (lp && id >= kLpSplitBase) return split_lp_config(cx, id - kLpSplitBase);
         return lp ? dense_lp_config(cx, id) : split_config(cx, s->dJ8 != nullptr, id);
     };
+    // a launch holds fewer than 2^32 threads (32 x 32 tiles of 512: n R < 8.6e9)
+    auto grid_fits = [&](const DenseConfig &c) {
+        const long long nwg = (long long)((s->Np + c.bm - 1) / c.bm) * ((s->R + c.traj_tile - 1) / c.traj_tile);
+        return nwg * c.threads < 1ll << 32;
+    };
     auto fits = [&](int id) {
         if (id >= kFewBase) {
             // 32 x 32 tiles; with split couplings the eight-group ones only,
@@ -668,7 +673,7 @@ int choose_config(gd_solver *s) {
         }
         if (id >= kGemvBase) return gemv_ok(id - kGemvBase);
         if (id < 0 || id >= nc) return false;
-        return !lp || id >= kLpSplitBase || dense_lp_config_fits(cfg_of(id), s->Np, s->Rp);
+        return lp && id < kLpSplitBase ? dense_lp_config_fits(cfg_of(id), s->Np, s->Rp) : grid_fits(cfg_of(id));
     };
     // the fused kernel needs its own form of J; the coupling kernels' form is
     // laid out when they first run (here, when they are timed)
