@@ -82,9 +82,11 @@ typedef enum gd_integrator { GD_EULER = 0, GD_RK4 = 1 } gd_integrator;
 typedef enum gd_precision {
     GD_PREC_FP32 = 0,  /* J and Psi in FP32 (the coupling product of many trajectories multiplies
                           exact BF16 pieces of them on the matrix cores, FP32 sums: closer to
-                          64 bits than FP32 matrix instructions; when every coupling is exact in FP8 E4M3 the
-                          few-trajectory kernels stream a one-byte copy of J, widened exactly
-                          and summed in the FP32 order: the same results bit for bit;
+                          64 bits than FP32 matrix instructions; when every coupling is exact in FP8 E4M3 a
+                          one-byte copy of J is read instead, widened exactly; the matrix-vector
+                          kernels (ids 100 to 109) and the persistent steps of up to four real
+                          trajectories sum it in the FP32 order: the same results bit for bit; the
+                          tiles of the other kernels differ, and with them the order of the sums;
                           the environment variable GD_J8_COPY=0 turns the copy off) */
     GD_PREC_BF16 = 1,  /* Psi operand rounded to BF16; J in BF16 (FP8 storage when exact) */
     GD_PREC_FP16 = 2   /* Psi operand rounded to FP16; J in FP16 (FP8 storage when exact) */

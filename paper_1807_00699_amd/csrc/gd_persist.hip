@@ -431,23 +431,25 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        f32x4 c0 = {0.0f, 0.0f, 0.0f, 0.0f}, c1 = c0;
+        // (the same order of the sums for both forms of J: the smaller pieces of
+        // couplings that are exact in FP8 are zero)
+        f32x4 c0 = {0.0f, 0.0f, 0.0f, 0.0f}, c1 = c0, c2 = c0;
         const bool has = col < 3 * R;
         const unsigned char *xp = xl[wave][has ? col : 0] + 16 * kq;
 #pragma unroll
         for (int f = 0; f < 8; ++f) {
             u32x4 b = *reinterpret_cast<const u32x4 *>(xp + 64 * f);
             if (!has) b = u32x4{0u, 0u, 0u, 0u};
+            f32x4 &c = f & 1 ? c1 : c0;
             if constexpr (J8) {
-                f32x4 &c = f & 1 ? c1 : c0;
                 c = mfma16(widen8<OP_F32>(j8[f].x, j8[f].y), b, c);
             } else {
-                c1 = mfma16(j[f][2], b, c1);
-                c1 = mfma16(j[f][1], b, c1);
-                c0 = mfma16(j[f][0], b, c0);
+                c2 = mfma16(j[f][2], b, c2);
+                c2 = mfma16(j[f][1], b, c2);
+                c = mfma16(j[f][0], b, c);
             }
         }
-        if (has) *reinterpret_cast<f32x4 *>(&red[ev & 1][wave][has ? col : 0][4 * kq]) = c0 + c1;
+        if (has) *reinterpret_cast<f32x4 *>(&red[ev & 1][wave][has ? col : 0][4 * kq]) = J8 ? c0 + c1 : (c0 + c1) + c2;
         // (also: the empty marks this wave stored in the last step have arrived)
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();

@@ -4,7 +4,8 @@
 // the diagonal, compute the coupling scale s, map the external field g of
 // Eq. (h) onto the q = 1 term h_1 = -g sqrt(rho_th)/s of Eq. (main), pad to
 // the row tile and upload.  Run: one dense coupling launch per Euler step or
-// per RK4 stage, with the amplitude/gain update fused in (gd_dense.hip).
+// per RK4 stage, with the amplitude/gain update fused in (gd_split.h, gd_gemv.h), or
+// all steps in one launch (gd_small.hip, gd_persist.hip).
 #include "gd_batch_rt.h"
 #include "gd_internal.h"
 #include "../../include/gd.h"
@@ -175,10 +176,9 @@ struct gd_solver {
     int op = OP_F32;           // operand precision of the coupling GEMM
     bool jfp8 = false;         // J stored as FP8 E4M3 (reduced-precision modes)
     void *dJlp = nullptr;      // J in FP8 or in the operand type
-    // FP32 solvers whose couplings are all exact in FP8 E4M3 (e.g. {-1, 0, +1}):
-    // a one-byte copy of J for the few-trajectory kernels, which stream J from
-    // HBM every step and widen it exactly to FP32, in the FP32 kernels' order
-    // (the same results bit for bit); GD_J8_COPY=0 keeps FP32 J only
+    // FP32 solvers whose couplings are all exact in FP8 E4M3 (e.g. {-1, 0, +1}): a
+    // one-byte copy of J, widened exactly where it is read; GD_J8_COPY=0 keeps
+    // FP32 J only
     void *dJ8 = nullptr;
     void *dJt = nullptr;       // J (FP8, or three BF16 pieces) as the split kernels read it
     float *dJs = nullptr;      // FP32 solvers with Np <= 128: J as the fused small-problem kernel reads it
