@@ -46,7 +46,7 @@ std::string header() {
     }
     std::ostringstream h;
     h << "gd-autotune 1 " << arch << " " << cus << " variants " << split_config_count() << ","
-      << dense_lp_config_count() << "," << gemv_config_count() << ","
+      << split_lp_config_count() << "," << dense_lp_config_count() << "," << gemv_config_count() << ","
       << batch_config_count() << " build " << __DATE__ << "_" << __TIME__;
     return h.str();
 }
