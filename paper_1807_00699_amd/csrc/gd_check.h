@@ -46,6 +46,7 @@ __device__ inline bool last_arrival(unsigned *count, unsigned total) {
 // loads of U trajectories in flight.
 template <int U = 1>
 __device__ inline void check_end(const CheckEnd &c) {
+    const long long stalled = c.stalled ? __hip_atomic_load(c.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     __shared__ double se[16];
     __shared__ int si[16], sc[16];
     double bv = __builtin_inf();
@@ -87,7 +88,6 @@ __device__ inline void check_end(const CheckEnd &c) {
     __syncthreads();
     if (threadIdx.x != 0) return;
     for (unsigned w = 1; w < blockDim.x / 64; ++w) merge(se[w], si[w], sc[w]);
-    const long long stalled = c.stalled ? __hip_atomic_load(c.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     double run = c.first ? c.e0 : 0.0;
     int run_i = c.i0;
     if (c.run_e && !c.first) {

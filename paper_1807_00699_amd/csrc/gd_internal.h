@@ -58,7 +58,7 @@ struct DenseStepArgs {
     unsigned long long noise_key;
     // split kernels and persistent steps: J is split as J / 2^j_exp; 2^sum_exp
     // times the sums of the products of its pieces are those of J Psi, or (0,
-    // modes that step) inv_s carries that factor
+    // modes that step; always for persistent steps) inv_s carries that factor
     int j_exp, sum_exp;
     int *tiny;             // FP32: set when an amplitude other than zero below 2^-100 is written
     // energy mode: weight of the second plane's product (3/4 for the q = 3, 6

@@ -100,8 +100,11 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
     const int g = blockIdx.x % p.groups, m0 = blockIdx.x / p.groups * ROWS;
     const int nf = a.Np / 32;
     const long long ps = a.plane_stride;
-    const bool gone = tid == 0 && __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-    if (tid == 0) stalled = gone || p.patience < 0;
+    long long gone = 0;   // (looked at once the first amplitudes are on their way)
+    if (tid == 0) {
+        gone = __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        stalled = 0;
+    }
 
     // this wave's couplings: fragments w, w + 8, ... of 32 columns, RB blocks of 16 rows
     u32x4 j[J8 ? 1 : FR][J8 ? 1 : RB][3];
@@ -166,6 +169,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
 
     publish(p.base);
     __syncthreads();
+    if (tid == 0 && (gone != 0 || p.patience < 0)) stalled = 1;
     const int evals = p.steps * (RK4 ? 4 : 1);
     for (int ev = 1; ev <= evals; ++ev) {
         f32x4 hi[RB], lo[RB];
@@ -249,13 +253,6 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
                 }
             }
         }
-        if (a.sum_exp != 0) {
-#pragma unroll
-            for (int k = 0; k < IT; ++k) {
-                cr[k] = __builtin_ldexpf(cr[k], a.sum_exp);
-                ci[k] = __builtin_ldexpf(ci[k], a.sum_exp);
-            }
-        }
         if constexpr (JL != 0) __syncthreads();
         const int stage = RK4 ? (ev - 1) & 3 : 0;
 #pragma unroll
@@ -318,7 +315,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
             if (CPLX) store1(mark + 16, kEmpty);
         }
     }
-    if (stalled && tid == 0 && !gone) store_agent(p.stalled, p.tag);
+    if (stalled && tid == 0 && gone == 0) store_agent(p.stalled, p.tag);
 #pragma unroll
     for (int k = 0; k < IT && !stalled; ++k) {
         const int i = m0 + lr + k * LSTEP;
@@ -348,8 +345,11 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
     const int nw = blockDim.x / 64;
     const int col = lane & 15, kq = lane >> 4;
     const int m0 = blockIdx.x * 16, Np = a.Np, R = a.R;
-    const bool gone = tid == 0 && __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-    if (tid == 0) stalled = gone || p.patience < 0;
+    long long gone = 0;   // (looked at once the first amplitudes are on their way)
+    if (tid == 0) {
+        gone = __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        stalled = 0;
+    }
 
     uint2 j8[8];
     u32x4 j[J8 ? 1 : 8][3];
@@ -389,6 +389,7 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
     };
     publish(p.base);
     __syncthreads();
+    if (tid == 0 && (gone != 0 || p.patience < 0)) stalled = 1;
     const int k4 = 256 * wave + 4 * lane;   // this lane polls columns k4 .. k4 + 3
     for (int ev = 1; ev <= p.steps; ++ev) {
         const unsigned *src = p.x + ((p.base + ev - 1) & 3) * bsz + k4;
@@ -464,9 +465,7 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
             lo += __shfl_xor(lo, 16);
             hi += __shfl_xor(hi, 32);
             lo += __shfl_xor(lo, 32);
-            float c = hi + lo;
-            if (a.sum_exp != 0) c = __builtin_ldexpf(c, a.sum_exp);
-            const float rho = x * x;
+            const float c = hi + lo, rho = x * x;
             const float f = x * (gm - a.gamma_c - rho) + c * a.inv_s + hh;
             gm += a.dt * (ep * (a.rho_th - rho));
             x += a.dt * f;
@@ -480,7 +479,7 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
             if (lane < 16) store1(own + ((p.base + ev + 2) & 3) * bsz, kEmpty);
         }
     }
-    if (stalled && tid == 0 && !gone) store_agent(p.stalled, p.tag);
+    if (stalled && tid == 0 && gone == 0) store_agent(p.stalled, p.tag);
     if (inside && lane < 16 && !stalled) {
         a.psi_out[(long long)r * Np + i] = x;
         if (tiny_number(x)) store_agent(a.tiny, 1);
@@ -591,7 +590,7 @@ bool persist_ends_run(int id) { return id >= kFew; }
 
 hipError_t launch_persist(int id, bool cplx, bool rk4, bool j8, const DenseStepArgs &a, const PersistArgs &p,
                           const CheckEnd &ce, hipStream_t st) {
-    if (a.Np % 64 || a.R < 1 || p.steps < 1 || !p.tag || a.psi_out == a.psi_in || a.gam_out == a.gam_in || ce.E ||
+    if (a.Np % 64 || a.R < 1 || p.steps < 1 || !p.tag || a.sum_exp != 0 || a.psi_out == a.psi_in || a.gam_out == a.gam_in || ce.E ||
         (ce.out && (!persist_ends_run(id) || ce.R != a.R || !ce.count || !ce.flags)))
         return hipErrorInvalidValue;
     DenseStepArgs x = a;

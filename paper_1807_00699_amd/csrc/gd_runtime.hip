@@ -612,6 +612,9 @@ int choose_persist(gd_solver *s) {
     if (s->persist_left < 0 && s->prm.check_interval > 0 &&
         (long long)s->prm.check_interval * (s->integrator() == GD_RK4 ? 4 : 1) < kPersistCheckEvals)
         return GD_OK;
+    DenseStepArgs a = base_args(s);
+    set_scales(s, MODE_EULER, kAmpExp, a);
+    if (a.sum_exp != 0) return GD_OK;
     const int id = persist_variant(cx, s->integrator() == GD_RK4, s->dJ8 != nullptr, s->Np, s->R);
     if (id < 0) return GD_OK;
     if (!s->xchg) {
