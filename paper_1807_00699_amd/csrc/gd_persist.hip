@@ -53,10 +53,12 @@ using split::widen8;
 constexpr unsigned kEmpty = 0xFFFFFFFFu;   // a slot not yet published
 constexpr int kWaves = 8;
 // pauses before the first poll, in sleeps of 64 cycles: the time that the
-// published amplitudes take to arrive (N = 300, R = 64 2.1-2.2 us per step for
-// 5-10; XY N = 1000, R = 128 18.6, 17.7 and 18.3 for 5, 10 and 15; N = 4096,
-// R = 1 2.95, 2.66 and 2.35 for 12, 16 and 20-24; N = 1000, R = 4 3.5 for 5, 4.0
-// for 24)
+// published amplitudes take to arrive.  N = 800, R = 100 3.54, 3.20 and 3.30 us
+// per step for 6, 10 and 16; XY N = 1000, R = 128 16.8 per RK4 step for 6 to 10,
+// 17.5 for 16.  Few trajectories, 5 and 24: N = 200 1.4-1.7 and 1.7-2.2; N = 1000,
+// R = 1 to 4, FP8 couplings 1.77, 2.57, 3.18, 3.16 and 1.64, 1.92, 2.46, 2.55,
+// split couplings 2.07, 2.55, 3.65, 3.22 and 1.86, 2.56, 3.71, 3.71; N = 1100
+// 1.89-3.68, 2.11-4.13 and 1.76-3.20, 1.93-4.03; N = 4096, R = 1 2.82 and 2.00
 constexpr int kPause = 10, kPauseFew = 5, kPauseFewLarge = 24;
 
 __device__ inline f32x4 mfma16(const u32x4 &a, const u32x4 &b, const f32x4 &c) {
@@ -557,9 +559,12 @@ long long persist_words(int id, bool cplx, int Np, int R) {
 // reads no empty columns (N = 1000, R = 1 2.25 us per step, 3.5 in a group of
 // 16); a wave updates one trajectory, so R is at most the number of waves.
 // Otherwise the fewest rows per workgroup with at most one workgroup per CU.
-// Every problem that fits is faster this way than with one launch per step
-// (from 1.3 times, N = 2000, R = 128: 8.2 us against 11.1); larger ones have
-// enough work per step to hide its latency.
+// In runs of 40 steps every problem that fits is faster this way than with one
+// launch per step (from 1.04 times, N = 2000, R = 100: 359 us against 375; N = 300,
+// R = 64 102 against 184); larger ones have enough work per step to hide its
+// latency.  A call of one step takes 25-46 us against 18-25 (XY RK4 N = 1000 53
+// against 48), and 3 to 5 steps the same, but a trajectory does not depend on how
+// its steps are cut into calls.  Runs cut by frequent checks: choose_persist.
 int persist_variant(bool cplx, bool rk4, bool j8, int Np, int R) {
     int dev = 0, cus = 0, coop = 0;
     if (hipGetDevice(&dev) != hipSuccess ||

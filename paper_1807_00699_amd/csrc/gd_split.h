@@ -526,7 +526,12 @@ hipError_t launch_modes(int mode, const DenseStepArgs &a, hipStream_t st) {
     case MODE_RK2: GD_LAUNCH(MODE_RK2); break;
     case MODE_RK3: GD_LAUNCH(MODE_RK3); break;
     case MODE_RK4: GD_LAUNCH(MODE_RK4); break;
-    case MODE_ENERGY: GD_LAUNCH(MODE_ENERGY); break;
+    case MODE_ENERGY:
+        // (energies of one plane on FP8 couplings come from the sign kernel, but
+        // for the tiles that compete with the matrix-vector kernels)
+        if constexpr (JK == J_FP8 && !CPLX && OPT == OP_F32 && !(BM == 32 && BN == 32)) return hipErrorInvalidValue;
+        else GD_LAUNCH(MODE_ENERGY);
+        break;
     default: return hipErrorInvalidValue;
     }
 #undef GD_LAUNCH
