@@ -141,22 +141,25 @@ __device__ inline void epi_fill(const DenseStepArgs &a, int i0, const f32x4 *q, 
 }
 
 // Returns true if a written value is non-finite.  cr/ci: raw GEMM sums.
-template <int MODE, bool CPLX, int OPT>
+// STATED: which product of a sum of two is fused into the addition is written
+// down, for kernels whose tiles have to round alike (else the compiler's choice,
+// one per kernel).
+template <int MODE, bool CPLX, int OPT, bool STATED = false>
 __device__ inline bool epi_apply(const DenseStepArgs &a, int i0, int r, bool rvalid, const EpiIn &in,
                                  f32x4 cr, f32x4 ci) {
     const long long idx = (long long)r * a.Np + i0;
     const long long ps = a.plane_stride;
     const float inv_s = a.inv_s, dt = a.dt, gc = a.gamma_c, rho_th = a.rho_th;
     const f32x4 ep = in.ep, hh = in.hh, xr = in.xr, xi = in.xi, gm = in.gm;
-    // (sums of two products: which of them is fused into the addition is stated,
-    // so that every kernel rounds alike)
     f32x4 fr, fi, fg;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const float rho = CPLX ? __builtin_fmaf(xr[e], xr[e], xi[e] * xi[e]) : xr[e] * xr[e];
+        const float rho = !CPLX    ? xr[e] * xr[e]
+                          : STATED ? __builtin_fmaf(xr[e], xr[e], xi[e] * xi[e])
+                                   : xr[e] * xr[e] + xi[e] * xi[e];
         const float lin = gm[e] - gc - rho;
-        fr[e] = __builtin_fmaf(cr[e], inv_s, xr[e] * lin) + hh[e];
-        fi[e] = CPLX ? __builtin_fmaf(ci[e], inv_s, xi[e] * lin) : 0.0f;
+        fr[e] = (STATED ? __builtin_fmaf(cr[e], inv_s, xr[e] * lin) : xr[e] * lin + cr[e] * inv_s) + hh[e];
+        fi[e] = !CPLX ? 0.0f : STATED ? __builtin_fmaf(ci[e], inv_s, xi[e] * lin) : xi[e] * lin + ci[e] * inv_s;
         fg[e] = ep[e] * (rho_th - rho);
     }
     if (CPLX && a.q >= 2) {
@@ -165,8 +168,8 @@ __device__ inline bool epi_apply(const DenseStepArgs &a, int i0, int r, bool rva
         for (int e = 0; e < 4; ++e) {
             float pr = xr[e], pi = -xi[e];
             for (int k = 2; k < a.q; ++k) {
-                const float tr = __builtin_fmaf(pi, xi[e], pr * xr[e]);
-                const float ti = __builtin_fmaf(pi, xr[e], -(pr * xi[e]));
+                const float tr = STATED ? __builtin_fmaf(pi, xi[e], pr * xr[e]) : pr * xr[e] + pi * xi[e];
+                const float ti = STATED ? __builtin_fmaf(pi, xr[e], -(pr * xi[e])) : pi * xr[e] - pr * xi[e];
                 pr = tr;
                 pi = ti;
             }

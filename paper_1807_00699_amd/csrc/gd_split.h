@@ -402,7 +402,8 @@ __global__ void __launch_bounds__(64 * WM * WN * KS) dense_step_split(DenseStepA
                         for (int m = RG / 2; m >= 1; m >>= 1) e += __shfl_xor(e, m);
                         if (row == 0 && r < a.R) a.partial[(long long)mt * a.Rp + r] = e;
                     } else if (inside) {
-                        if (epi_apply<MODE, CPLX, OPT>(a, i0, r, true, EARLY ? pre[u0 + v] : in[v], cr, ci)) a.flags[r] = 1;
+                        if (epi_apply<MODE, CPLX, OPT, true>(a, i0, r, true, EARLY ? pre[u0 + v] : in[v], cr, ci))
+                            a.flags[r] = 1;
                     }
                 }
             }
