@@ -91,8 +91,14 @@ def test_no_state_without_memory_for_it():
     J = np.zeros((n, n), np.float32)
     J[0, 1:] = J[1:, 0] = np.linspace(0.1, 1.0, n - 1, dtype=np.float32)
     with gd.Solver(J) as S:
-        keep = torch.empty(_free() - (1 << 30), dtype=torch.uint8, device="cuda")
-        torch.cuda.synchronize()
+        keep = [torch.empty(max(_free() - (2 << 30), 1), dtype=torch.uint8, device="cuda")]
+        try:        # (more may be free than is reported)
+            while True:
+                keep.append(torch.empty(128 << 20, dtype=torch.uint8, device="cuda"))
+        except torch.cuda.OutOfMemoryError:
+            pass
+        del keep[-8:]
+        torch.cuda.empty_cache()    # 1 GiB and less than 128 MiB more
         with pytest.raises(gd.GDError) as e:
             S.set_init(R)
         assert e.value.code == gd.GD_E_OOM
