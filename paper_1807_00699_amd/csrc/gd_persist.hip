@@ -96,15 +96,15 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
     constexpr int JL = !J8 && FR * RB > 12 ? (RB == 4 ? 15 : FR * RB) : 0;
     __shared__ __attribute__((aligned(16))) float red[JL ? 1 : 2][kWaves][16][RS];
     __shared__ __attribute__((aligned(16))) u32x4 jlds[JL ? JL * kWaves * 64 : 1];
-    __shared__ int stalled;
+    __shared__ int stalled, gone;   // gone: thread 0's, here to take no register
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, kq = lane >> 4;
     const int g = blockIdx.x % p.groups, m0 = blockIdx.x / p.groups * ROWS;
     const int nf = a.Np / 32;
     const long long ps = a.plane_stride;
-    long long gone = 0;   // (looked at once the first amplitudes are on their way)
+    long long before = 0;   // (looked at once the first amplitudes are on their way)
     if (tid == 0) {
-        gone = __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before = __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         stalled = 0;
     }
 
@@ -171,7 +171,10 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
 
     publish(p.base);
     __syncthreads();
-    if (tid == 0 && (gone != 0 || p.patience < 0)) stalled = 1;
+    if (tid == 0) {
+        gone = before != 0;
+        if (gone || p.patience < 0) stalled = 1;
+    }
     const int evals = p.steps * (RK4 ? 4 : 1);
     for (int ev = 1; ev <= evals; ++ev) {
         f32x4 hi[RB], lo[RB];
@@ -317,7 +320,7 @@ persist_step_k(DenseStepArgs a, PersistArgs p) {
             if (CPLX) store1(mark + 16, kEmpty);
         }
     }
-    if (stalled && tid == 0 && gone == 0) store_agent(p.stalled, p.tag);
+    if (stalled && tid == 0 && !gone) store_agent(p.stalled, p.tag);
 #pragma unroll
     for (int k = 0; k < IT && !stalled; ++k) {
         const int i = m0 + lr + k * LSTEP;
@@ -342,14 +345,14 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
     constexpr int NC = 3 * NR, PB = 528, RS = 20;   // LDS bytes of one piece's 256 values, floats of 16 rows (both padded)
     __shared__ __attribute__((aligned(16))) unsigned char xl[16][NC][PB];
     __shared__ __attribute__((aligned(16))) float red[2][16][NC][RS];
-    __shared__ int stalled;
+    __shared__ int stalled, gone;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nw = blockDim.x / 64;
     const int col = lane & 15, kq = lane >> 4;
     const int m0 = blockIdx.x * 16, Np = a.Np, R = a.R;
-    long long gone = 0;   // (looked at once the first amplitudes are on their way)
+    long long before = 0;   // (looked at once the first amplitudes are on their way)
     if (tid == 0) {
-        gone = __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        before = __hip_atomic_load(p.stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         stalled = 0;
     }
 
@@ -391,7 +394,10 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
     };
     publish(p.base);
     __syncthreads();
-    if (tid == 0 && (gone != 0 || p.patience < 0)) stalled = 1;
+    if (tid == 0) {
+        gone = before != 0;
+        if (gone || p.patience < 0) stalled = 1;
+    }
     const int k4 = 256 * wave + 4 * lane;   // this lane polls columns k4 .. k4 + 3
     for (int ev = 1; ev <= p.steps; ++ev) {
         const unsigned *src = p.x + ((p.base + ev - 1) & 3) * bsz + k4;
@@ -481,7 +487,7 @@ persist_few_k(DenseStepArgs a, PersistArgs p, CheckEnd ce) {
             if (lane < 16) store1(own + ((p.base + ev + 2) & 3) * bsz, kEmpty);
         }
     }
-    if (stalled && tid == 0 && gone == 0) store_agent(p.stalled, p.tag);
+    if (stalled && tid == 0 && !gone) store_agent(p.stalled, p.tag);
     if (inside && lane < 16 && !stalled) {
         a.psi_out[(long long)r * Np + i] = x;
         if (tiny_number(x)) store_agent(a.tiny, 1);
