@@ -34,7 +34,14 @@
  *  - A handle is not thread-safe: calls on one handle must not overlap.
  *  - Work is enqueued on params.stream (a hipStream_t; NULL = a stream the
  *    library creates).  Calls synchronise that stream before returning unless
- *    GD_F_ASYNC is set (then only gd_run may return early).
+ *    GD_F_ASYNC is set (then only gd_run may return early; its steps are one
+ *    launch each and may add in another order than a synchronous run's, see
+ *    gd_stats.kernel_config).
+ *  - A dense solver keeps J on the device, with N padded to a multiple of 64:
+ *    4 N^2 bytes (FP32), N^2 more where FP8 holds the couplings exactly (else
+ *    2 N^2 more at reduced precision), and, where its steps or energy checks
+ *    read J in the order of the matrix instruction, N^2 (FP8) or, in FP32,
+ *    6 N^2 bytes (other couplings) more.
  */
 #ifndef GD_H_
 #define GD_H_

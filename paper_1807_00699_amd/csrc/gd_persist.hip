@@ -7,8 +7,8 @@
 // three BF16 pieces of gd_split.h) and its spins' state, and a step is: wait
 // for the amplitudes of its trajectories, split and multiply (as gd_split.h:
 // the same exact products, sums in FP32), add the waves' sums in LDS, update,
-// publish (2^24 Psi, gd_split.h).  Trajectories are independent, so only the workgroups of one group
-// of trajectories wait for each other.
+// publish (2^24 Psi, gd_split.h).  Trajectories are independent, so only the
+// workgroups of one group of trajectories wait for each other.
 //
 // Exchange: an amplitude is its own arrival mark.  Slots hold kEmpty (a NaN
 // pattern that is never published) until the new value is stored; readers poll
@@ -21,9 +21,9 @@
 // reader of the next values of that buffer has seen.  The set counter goes on
 // from launch to launch, which makes the first marks of a launch those of the
 // last sets of the one before.  A poll that comes too early costs a whole
-// round trip, so every wave sleeps first: without the pause N = 4096, R = 1
-// takes 2.95 us per step instead of 2.35, XY N = 1000, R = 128 24.3 instead of
-// 17.7.
+// round trip, so every wave sleeps first: with hardly any pause N = 4096, R = 1
+// takes 2.7 us per step instead of 1.9, XY N = 1000, R = 128 24.3 instead of
+// 17.7 (16.5 now).
 //
 // All workgroups have to be resident at once: at most one per CU, launched
 // cooperatively.  A wait longer than `patience` ends the kernel in every
@@ -32,10 +32,11 @@
 // reads, so the state at the start of the first of them is there for the host
 // to go on from.
 //
-// Per step, before -> after: Ising Euler N = 4096, R = 1 5.7 -> 2.35 us (FP8
-// couplings), 13.3 -> 3.7 (split couplings); N = 300, R = 64 5.4 -> 2.1; N =
-// 800, R = 100 6.3 -> 3.5; N = 2000, R = 64 9.8 -> 6.1; XY RK4 (four
-// evaluations) N = 1000, R = 128 32 -> 17.7; XY N = 1500, R = 48 31 -> 22.
+// Per step in long runs, one launch per step -> persistent: Ising Euler N =
+// 4096, R = 1 5.6 -> 1.9 us (FP8 couplings), 13.2 -> 2.4 (split couplings); N =
+// 300, R = 64 4.2 -> 1.9; N = 800, R = 100 5.5 -> 3.1; N = 2000, R = 64 8.4 ->
+// 5.6; XY RK4 (four evaluations) N = 1000, R = 128 30.5 -> 16.5, N = 1500, R =
+// 48 with FP8 couplings 30.1 -> 23.4.  Each cooperative launch adds about 20 us.
 #include "gd_check.h"
 #include "gd_split.h"
 

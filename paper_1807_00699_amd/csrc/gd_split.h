@@ -25,11 +25,11 @@
 // then the 16-bit copies that the previous step wrote.
 //
 // What bounds it: at N = R = 4096 the matrix cores.  One launch is 3 x 137
-// GFLOP; it takes 318 us (1.30 PFLOP/s; a large BF16 matrix product runs at
+// GFLOP; it takes 322 us (1.28 PFLOP/s; a large BF16 matrix product runs at
 // 1.28 on this card), against 1016 us on the FP32 matrix cores (135 TFLOP/s,
 // 86% of their peak); with BF16 operands, one product, 126 us, where the matrix
 // work (108 us) and the state update of all workgroups at once follow each
-// other.  XY N = R = 1024 31 us per stage (45 before): eight K chunks take 20
+// other.  XY N = R = 1024 31-32 us per stage (45 before): eight K chunks take 20
 // us, at the matrix rate, the state update and the start of the launch 11.
 // Smaller problems are bound by the latency of the first loads and by the LDS
 // reads and the splitting (5.5 vector instructions per amplitude) around each
